@@ -106,6 +106,8 @@ void fill_physics(StepArgs& a, const nyx_params* p) {
   a.eta = p->eta_dual;
   a.small_dens = p->small_dens;
   a.small_pres = p->small_pres;
+  a.small_densf = (float)p->small_dens;
+  a.small_presf = (float)p->small_pres;
   a.riemann_tol = p->riemann_tol;
   // FP32-mixed stopping step: the star state is stored in FP32, so the
   // iteration stops once the next Newton correction would be far below FP32

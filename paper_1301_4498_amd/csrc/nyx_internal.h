@@ -123,7 +123,9 @@ inline long long box_layout(const nyx_box& b, int gidx, long long base, BoxDev* 
 struct StepC {
   double dt, a_h, da, kh, hdt_a, hda_a, pexp, kap1, kap2, k, gm1;
   double xo, xn;  // expansion source of the energy equations at a_old / a_new
-  double pad_;
+  // the tracing's factors in FP32 (the mixed build's; a kernel then reads them
+  // as scalars instead of converting them in every lane)
+  float khf, hdt_af, hda_af, pexpf;
 };
 
 // Which cell range a launch walks: padded cells, the [-1, n]^3 range, valid
@@ -173,6 +175,35 @@ __device__ __forceinline__ T ldu(const T* base, unsigned i) {
 template <class T>
 __device__ __forceinline__ void stu(T* base, unsigned i, T v) {
   *(T*)((char*)base + i * (unsigned)sizeof(T)) = v;
+}
+
+// The same for a base that is uniform over the wavefront, as every stage
+// array's is.  The base is kept opaque in scalar registers: left to itself the
+// compiler folds the strides of neighbouring accesses into one vector address
+// and spends a 64-bit vector add on most of them; this way each access takes
+// the scalar-base form.  With the index extended in the block of the accesses
+// (local_idx, called once in front of them) that costs no vector instruction.
+__device__ __forceinline__ unsigned local_idx(unsigned i) {
+  asm("" : "+v"(i));
+  return i;
+}
+__device__ __forceinline__ unsigned long long wave_base(const void* p) {
+  const unsigned long long a = (unsigned long long)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+  return (unsigned long long)hi << 32 | lo;
+}
+template <class T>
+__device__ __forceinline__ T ldw(const T* base, unsigned i) {
+  typedef const T __attribute__((address_space(1))) * G;
+  typedef const char __attribute__((address_space(1))) * C;
+  return *(G)((C)wave_base(base) + i * (unsigned)sizeof(T));
+}
+template <class T>
+__device__ __forceinline__ void stw(T* base, unsigned i, T v) {
+  typedef T __attribute__((address_space(1))) * G;
+  typedef char __attribute__((address_space(1))) * C;
+  *(G)((C)wave_base(base) + i * (unsigned)sizeof(T)) = v;
 }
 
 // Natural (x fastest, then y, then z) flat index of the cell at position q
@@ -268,6 +299,7 @@ struct StepArgs {
   double dt_host;
   double a_old, a_new;
   double gamma, eta, small_dens, small_pres, riemann_tol, cfl;
+  float small_densf, small_presf;  // the floors in FP32
   double igm1;   // 1 / (gamma - 1), for the mixed build's products
   float igm1f;   // the same in FP32 (the FP32 flux formulas)
   double mixed_stop;  // FP32-mixed stopping rule (see two_shock)

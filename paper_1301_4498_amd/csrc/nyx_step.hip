@@ -108,6 +108,13 @@ __device__ __forceinline__ Loc locate(const StepArgs& A, int stage, int space, c
   return L;
 }
 
+// the floors and the tracing's factors in `real`
+#if defined(NYX_PREC_MIXED)
+#define NYX_REAL(x) x##f
+#else
+#define NYX_REAL(x) x
+#endif
+
 // per-box constants of the step, computed once per box by the prologue
 __device__ __forceinline__ const StepC& step_consts(const StepArgs& A, const BoxDev& b) {
   return A.consts[b.gidx];
@@ -290,21 +297,21 @@ __global__ __launch_bounds__(kBlock) void k_flat(StepArgs A) { flat_body(A, laun
 // stage 3: PPM (O3) and characteristic tracing (O4)
 // ---------------------------------------------------------------------------
 #if defined(NYX_PREC_MIXED)
-// The limited slope without the branch: with s the sign of d2 = q(j+1) -
-// q(j-1), min(|dc|, 2|dl|, 2|dr|) = 2 min(|d2|/4, s dl, s dr) when dl dr > 0
-// (then dl, dr and d2 share their sign), and that minimum is <= 0 otherwise,
-// so clamping it at 0 gives the limiter's zero slope.  Scaling by 2 and 1/4
-// is exact, so the value is the branchy form's (up to the sign of a zero
-// slope, and slopes below the FP32 normal range).
+// Half the limited slope, h = minmod((q(j+1) - q(j-1)) / 4, q(j) - q(j-1),
+// q(j+1) - q(j)), as two medians: med(0, a, b) is the smaller of a and b where
+// they share a sign and 0 where they do not, and the centred difference has
+// the sign the one-sided ones share.  Scaling by 2 and 1/4 is exact, so 2 h is
+// the limited slope's own value (up to the sign of a zero slope and slopes
+// below the FP32 normal range): 4 instructions per slope where the clamped
+// minimum with its sign transfers took 9.
+__device__ __forceinline__ real med3(real a, real b, real c) {
+  return __builtin_amdgcn_fmed3f(a, b, c);
+}
+__device__ __forceinline__ real half_slope(real qm1, real q0, real qp1) {
+  return med3((real)0, (real)0.25 * (qp1 - qm1), med3((real)0, q0 - qm1, qp1 - q0));
+}
 __device__ __forceinline__ real lim_slope(real qm1, real q0, real qp1) {
-  const real d2 = qp1 - qm1;
-  const real dr = qp1 - q0;
-  const real dl = q0 - qm1;
-  const unsigned sg = __float_as_uint(d2) & 0x80000000u;
-  const real sdl = __uint_as_float(__float_as_uint(dl) ^ sg);
-  const real sdr = __uint_as_float(__float_as_uint(dr) ^ sg);
-  const real m = (real)2 * fmaxf(fminf(fminf((real)0.25 * fabsf(d2), sdl), sdr), (real)0);
-  return __uint_as_float(__float_as_uint(m) | sg);
+  return (real)2 * half_slope(qm1, q0, qp1);
 }
 #else
 // Under dr dl > 0 neither dl nor dr is NaN, so fmin (one instruction) takes
@@ -320,24 +327,37 @@ __device__ __forceinline__ real lim_slope(real qm1, real q0, real qp1) {
   return (real)0;
 }
 #endif
-// interface value between cells a and b from their limited slopes sa, sb
+// interface value between cells a and b from their limited slopes sa, sb (in
+// the mixed build from the half slopes: a third of their difference is a sixth
+// of the slopes', bit for bit)
 __device__ __forceinline__ real ppm_face(real qa, real qb, real sa, real sb) {
 #if defined(NYX_PREC_MIXED)
-  return (qa + (real)0.5 * (qb - qa)) - (sb - sa) * (real)(1.0 / 6.0);
+  return (qa + (real)0.5 * (qb - qa)) - (sb - sa) * (real)(1.0 / 3.0);
 #else
   return (qa + (real)0.5 * (qb - qa)) - (sb - sa) / (real)6;
 #endif
 }
-__device__ __forceinline__ void ppm_edges(const real* q5, real chi, real& qm_o, real& qp_o) {
-  real qj = q5[2];
+// edge values of the cell of q5[2] after flattening, before the monotonicity
+// limits
+__device__ __forceinline__ void ppm_flat(const real* q5, real chi, real& qm_o, real& qp_o) {
+  const real qj = q5[2];
   // slopes of cells j-1, j, j+1, each computed once
+#if defined(NYX_PREC_MIXED)
+  const real sm = half_slope(q5[0], q5[1], q5[2]);
+  const real s0 = half_slope(q5[1], q5[2], q5[3]);
+  const real sp = half_slope(q5[2], q5[3], q5[4]);
+#else
   const real sm = lim_slope(q5[0], q5[1], q5[2]);
   const real s0 = lim_slope(q5[1], q5[2], q5[3]);
   const real sp = lim_slope(q5[2], q5[3], q5[4]);
-  real qp = ppm_face(q5[2], q5[3], s0, sp);
-  real qm = ppm_face(q5[1], q5[2], sm, s0);
-  qp = chi * qp + ((real)1 - chi) * qj;
-  qm = chi * qm + ((real)1 - chi) * qj;
+#endif
+  const real qp = ppm_face(q5[2], q5[3], s0, sp);
+  const real qm = ppm_face(q5[1], q5[2], sm, s0);
+  qp_o = chi * qp + ((real)1 - chi) * qj;
+  qm_o = chi * qm + ((real)1 - chi) * qj;
+}
+// monotonicity limits of the parabola (CW84 eq. 1.10)
+__device__ __forceinline__ void ppm_limit(real qj, real& qm, real& qp) {
   if ((qp - qj) * (qj - qm) <= (real)0) {
     qp = qj;
     qm = qj;
@@ -352,8 +372,31 @@ __device__ __forceinline__ void ppm_edges(const real* q5, real chi, real& qm_o, 
     if (t > s) qm = (real)3 * qj - (real)2 * qp;
     else if (-s > t) qp = (real)3 * qj - (real)2 * qm;
   }
-  qm_o = qm;
-  qp_o = qp;
+}
+#if defined(NYX_PREC_MIXED)
+// The same limits as two medians.  With a = q+ - q_j and b = q_j - q- of one
+// sign, t > s says b > 2a: the limit 3 q_j - 2 q+ = q_j - 2a then lies between
+// q_j and q-; otherwise q- lies nearer.  Where a and b differ in sign, q- and
+// the limit lie on either side of q_j and the median is q_j, the flat value.
+// Likewise for q+.  Finite edges only (a median drops NaN).
+__device__ __forceinline__ void ppm_limit_med(real qj, real& qm, real& qp) {
+  const real lm = (real)3 * qj - (real)2 * qp, lp = (real)3 * qj - (real)2 * qm;
+  qm = med3(qj, qm, lm);
+  qp = med3(qj, qp, lp);
+}
+#endif
+// PPM edges of the five variables of a cell
+__device__ __forceinline__ void ppm_cell(const real (*qs)[5], real chi, real* qm, real* qp) {
+  for (int v = 0; v < 5; ++v) ppm_flat(qs[v], chi, qm[v], qp[v]);
+#if defined(NYX_PREC_MIXED)
+  real sum = (real)0;  // finite where every edge is
+  for (int v = 0; v < 5; ++v) sum += fabsf(qm[v]) + fabsf(qp[v]);
+  if (sum <= 3.402823466e+38f) {
+    for (int v = 0; v < 5; ++v) ppm_limit_med(qs[v][2], qm[v], qp[v]);
+    return;
+  }
+#endif
+  for (int v = 0; v < 5; ++v) ppm_limit(qs[v][2], qm[v], qp[v]);
 }
 // PLM variant (Sec. 3.2): the limited centred slope times the flattening
 // coefficient gives the edge values q_j -/+ ds/2 (the tracing below then
@@ -389,30 +432,37 @@ __device__ __forceinline__ void trace_side(const real* qc, real c, const real* q
       I[w][k] = SIDE > 0 ? avg_hi(qe[v], dq[v], q6[v], sig[w]) : avg_lo(qe[v], dq[v], q6[v], sig[w]);
     }
   const int fast = SIDE > 0 ? 2 : 0;  // fastest wave toward the face
+  const int slow = SIDE > 0 ? 0 : 2;
   const bool fast_in = SIDE > 0 ? (lam[2] > (real)0) : (lam[0] < (real)0);
   real ref[3];
   for (int k = 0; k < 3; ++k) ref[k] = fast_in ? I[fast][k] : qe[vid[k]];
+  // The fastest wave's own difference to the reference state is 0: it is the
+  // reference where it moves toward the face and carries nothing where it does
+  // not.  Only the contact's and the slow wave's amplitudes remain (an FP64
+  // cell is spared four divisions, an FP32 one 8 of its instructions).
   real D[3][3];
   for (int w = 0; w < 3; ++w) {
+    if (w == fast) continue;
     bool in = SIDE > 0 ? (lam[w] > (real)0) : (lam[w] < (real)0);
     for (int k = 0; k < 3; ++k) D[w][k] = in ? ref[k] - I[w][k] : (real)0;
   }
+  const real* S = D[slow];
 #if defined(NYX_PREC_MIXED)
   const real ic = (real)1 / c;
   const real icsq = ic * ic;
-  real am = (real)0.5 * (D[0][2] * icsq - (rho * D[0][1]) * ic);
-  real ap = (real)0.5 * (D[2][2] * icsq + (rho * D[2][1]) * ic);
-  real a0 = D[1][0] - D[1][2] * icsq;
-  out[0] = ref[0] - ((am + a0) + ap);
-  out[nv] = ref[1] - (c * __builtin_amdgcn_rcpf(rho)) * (ap - am);
+  const real as = SIDE > 0 ? (real)0.5 * (S[2] * icsq - (rho * S[1]) * ic)
+                           : (real)0.5 * (S[2] * icsq + (rho * S[1]) * ic);
+  const real a0 = D[1][0] - D[1][2] * icsq;
+  out[0] = ref[0] - (SIDE > 0 ? as + a0 : a0 + as);
+  out[nv] = ref[1] - (c * __builtin_amdgcn_rcpf(rho)) * (SIDE > 0 ? -as : as);
 #else
-  real am = (real)0.5 * (D[0][2] / csq - (rho * D[0][1]) / c);
-  real ap = (real)0.5 * (D[2][2] / csq + (rho * D[2][1]) / c);
-  real a0 = D[1][0] - D[1][2] / csq;
-  out[0] = ref[0] - ((am + a0) + ap);
-  out[nv] = ref[1] - (c / rho) * (ap - am);
+  const real as = SIDE > 0 ? (real)0.5 * (S[2] / csq - (rho * S[1]) / c)
+                           : (real)0.5 * (S[2] / csq + (rho * S[1]) / c);
+  const real a0 = D[1][0] - D[1][2] / csq;
+  out[0] = ref[0] - (SIDE > 0 ? as + a0 : a0 + as);
+  out[nv] = ref[1] - (c / rho) * (SIDE > 0 ? -as : as);
 #endif
-  out[4] = ref[2] - csq * (am + ap);
+  out[4] = ref[2] - csq * as;
   const bool c_in = SIDE > 0 ? (lam[1] > (real)0) : (lam[1] < (real)0);
   out[t1] = c_in ? (SIDE > 0 ? avg_hi(qe[t1], dq[t1], q6[t1], sig[1])
                              : avg_lo(qe[t1], dq[t1], q6[t1], sig[1]))
@@ -436,37 +486,39 @@ __device__ __forceinline__ unsigned trace_cell(const StepArgs& A, const BoxDev& 
   unsigned floors = 0;
   {
     const real* prim = (const real*)A.work + b.w_prim;
-    const unsigned c0 = pidx_e(b, ie, je, ke);
+    const unsigned c0 = local_idx(pidx_e(b, ie, je, ke));
     const unsigned s = d == 0 ? 1u : (d == 1 ? (unsigned)b.px : (unsigned)b.px * (unsigned)b.py);
     // every load of the cell is issued before any arithmetic, so a wave
     // waits once for all of them instead of once per variable
-    const real chi = ldu((const real*)A.work + b.w_chi, e);
+    const real chi = ldw((const real*)A.work + b.w_chi, local_idx(e));
     real qs[5][5];
     for (int v = 0; v < 5; ++v)
-      for (int o = -2; o <= 2; ++o) qs[v][o + 2] = ldu(prim + v * b.P + (long long)o * s, c0);
-    const real c = ldu(prim + 5 * b.P, c0);
+      for (int o = -2; o <= 2; ++o) qs[v][o + 2] = ldw(prim + v * b.P + (long long)o * s, c0);
+    const real c = ldw(prim + 5 * b.P, c0);
     const real* G = (const real*)A.grav + b.goff;
-    const real g[3] = {ldu(G, c0), ldu(G + b.gstride, c0), ldu(G + 2 * b.gstride, c0)};
+    const real g[3] = {ldw(G, c0), ldw(G + b.gstride, c0), ldw(G + 2 * b.gstride, c0)};
     real qc[5], qm[5], qp[5], dq[5], q6[5];
+    if (A.recon == NYX_RECON_PLM) {
+      for (int v = 0; v < 5; ++v) plm_edges(qs[v], chi, qm[v], qp[v]);
+    } else {
+      ppm_cell(qs, chi, qm, qp);
+    }
     for (int v = 0; v < 5; ++v) {
-      const real* q5 = qs[v];
-      qc[v] = q5[2];
-      if (A.recon == NYX_RECON_PLM) plm_edges(q5, chi, qm[v], qp[v]);
-      else ppm_edges(q5, chi, qm[v], qp[v]);
+      qc[v] = qs[v][2];
       dq[v] = qp[v] - qm[v];
       q6[v] = (real)6 * qc[v] - (real)3 * (qm[v] + qp[v]);
     }
     const int nv = 1 + d, t1 = 1 + (d + 1) % 3, t2 = 1 + (d + 2) % 3;
     const real u = qc[nv];
     real lam[3] = {u - c, u, u + c};
-    const real kh = (real)C.kh;
+    const real kh = C.NYX_REAL(kh);
     real sig[3];
     for (int w = 0; w < 3; ++w) sig[w] = fabs(lam[w]) * kh;
     trace_side<+1>(qc, c, qp, dq, q6, lam, sig, nv, t1, t2, hi);
     trace_side<-1>(qc, c, qm, dq, q6, lam, sig, nv, t1, t2, lo);
     // half-step gravity and expansion sources, then floors
-    const real hdt_a = (real)C.hdt_a, hda_a = (real)C.hda_a, pexp = (real)C.pexp;
-    const real sd_ = (real)A.small_dens, sp_ = (real)A.small_pres;
+    const real hdt_a = C.NYX_REAL(hdt_a), hda_a = C.NYX_REAL(hda_a), pexp = C.NYX_REAL(pexp);
+    const real sd_ = A.NYX_REAL(small_dens), sp_ = A.NYX_REAL(small_pres);
     real* out[2] = {lo, hi};
     for (int sd = 0; sd < 2; ++sd) {
       real* q = out[sd];
@@ -482,9 +534,10 @@ template <int D>
 __device__ __forceinline__ void store_edges(const StepArgs& A, const BoxDev& b, unsigned e,
                                             const real* lo, const real* hi) {
   real* W = (real*)A.work + b.w_edge;
+  e = local_idx(e);
   for (int v = 0; v < 5; ++v) {
-    stu(W + ((D * 2 + 0) * 5 + v) * b.E, e, lo[v]);
-    stu(W + ((D * 2 + 1) * 5 + v) * b.E, e, hi[v]);
+    stw(W + ((D * 2 + 0) * 5 + v) * b.E, e, lo[v]);
+    stw(W + ((D * 2 + 1) * 5 + v) * b.E, e, hi[v]);
   }
 }
 template <int D>
@@ -2192,7 +2245,7 @@ __device__ __forceinline__ bool grid_barrier(unsigned long long* ctl, int s,
     ok_sh = ok;
   }
   __syncthreads();
-  return ok_sh != 0;
+  return __builtin_amdgcn_readfirstlane(ok_sh) != 0;
 }
 
 // Waves per SIMD the persistent kernel is compiled for: with all seven stage
@@ -2237,8 +2290,11 @@ __global__ __launch_bounds__(kBlock, LMASK ? 2 : kPersistWaves) void k_step_pers
         q_sh[2] = got ? 1u : 0u;
       }
       __syncthreads();
-      const unsigned b0 = q_sh[0], b1 = q_sh[1];
-      const bool got = q_sh[2] != 0;
+      // the same in every lane, and known to be: the stage bodies read their
+      // arrays through scalar bases
+      const unsigned b0 = __builtin_amdgcn_readfirstlane(q_sh[0]);
+      const unsigned b1 = __builtin_amdgcn_readfirstlane(q_sh[1]);
+      const bool got = __builtin_amdgcn_readfirstlane(q_sh[2]) != 0;
       __syncthreads();  // every thread has read q_sh before the next take
       if (!got) break;
       for (unsigned lin = b0; lin < b1; ++lin) run_item<LMASK>(A, s, Item{lin, gx, gy}, mlp_lds, park);

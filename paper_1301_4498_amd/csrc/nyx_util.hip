@@ -121,7 +121,10 @@ __global__ void k_prologue(StepArgs A, int nbox, StepC* consts, BoxDev* single_d
   const double cgam = 2.0 - 3.0 * c.gm1;
   c.xo = cgam * (c.da / A.a_old);
   c.xn = cgam * (c.da / A.a_new);
-  c.pad_ = 0.0;
+  c.khf = (float)c.kh;
+  c.hdt_af = (float)c.hdt_a;
+  c.hda_af = (float)c.hda_a;
+  c.pexpf = (float)c.pexp;
   consts[b.gidx] = c;
 }
 
