@@ -443,6 +443,7 @@ int nyx_batch_create(const nyx_params* p, int nbox, const nyx_box* boxes, void* 
   plan->boxes.assign(boxes, boxes + nbox);
   std::vector<BoxDev> host(nbox);
   std::vector<int> prefix;
+  const int planes = fin_planes(nbox, boxes);
   long long used = 0;
   int g0 = 0;
   size_t span = 0;
@@ -483,7 +484,7 @@ int nyx_batch_create(const nyx_params* p, int nbox, const nyx_box* boxes, void* 
       used = 0;
       if (i == nbox) break;
     }
-    used = box_layout(boxes[i], i, used, &host[i]);
+    used = box_layout(boxes[i], i, used, &host[i], planes);
   }
   char* w = (char*)workspace;
   plan->table = (BoxDev*)w;

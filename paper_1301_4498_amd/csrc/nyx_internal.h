@@ -12,10 +12,15 @@ namespace nyx {
 constexpr int kBlock = 256;  // threads per block: 4 wavefronts of 64
 // Threads per workgroup of the fused final-stage kernel (8 wavefronts): a
 // tile of TX x TY cell columns of a box, TX = min(n_x, 64), TY = min(n_y,
-// kFinBlock / TX), over a chunk of at most kFinPlanes planes in z (tall
-// boxes are cut into several chunks so that the launch has enough tiles).
+// kFinBlock / TX), over a chunk of at most `planes` planes in z, chosen per
+// plan from kFinPlanes down (fin_planes).
 constexpr int kFinBlock = 512;
-constexpr int kFinPlanes = 64;
+constexpr int kFinPlanes = 64, kFinMinPlanes = 8;
+// Tiles that keep the chip's 512 resident workgroups (two per CU) evenly busy
+// to the end of the launch: each extra chunk solves one layer of z-faces again
+// (a face in 3.2 per cell and plane), so chunks are cut only while the launch
+// has fewer tiles than this.
+constexpr long long kFinTiles = 2048;
 // Fused front (tracing and stage-0 solves of x in one kernel): a wavefront
 // holds 64 consecutive cells of the [-1, n]^3 range, the first of them the
 // last of the previous wavefront, so a block owns kFrontOwn cells.
@@ -58,16 +63,46 @@ struct BoxDev {
   unsigned sy[3];          // per Space: rows per plane
   unsigned sc[3];          // per Space: cell count (< 2^31)
   int tx, ty, ntx, nty;    // fused final stage: tile shape, tiles along x and y,
-  int ntiles, pad2_;       // tiles in all (z chunks of kFinPlanes planes included)
+  int ntiles, tz;          // tiles in all (z chunks included), planes per chunk
   int fbx, pad3_;          // fused front: blocks of kFrontOwn cells
 };
 
 // Stage-array element count for a box (before alignment padding).
 inline long long align_elems(long long n) { return (n + 63) / 64 * 64; }
 
+// The fused final stage's tiling of a box: tile shape, and z chunks of equal
+// length (up to rounding) of at most `planes` planes.
+struct FinTiling {
+  int tx, ty, ntx, nty, tz, ntz;
+};
+inline FinTiling fin_tiling(const nyx_box& b, int planes) {
+  FinTiling t;
+  t.tx = b.n[0] < 64 ? b.n[0] : 64;
+  t.ty = b.n[1] < kFinBlock / t.tx ? b.n[1] : kFinBlock / t.tx;
+  t.ntx = (b.n[0] + t.tx - 1) / t.tx;
+  t.nty = (b.n[1] + t.ty - 1) / t.ty;
+  t.ntz = (b.n[2] + planes - 1) / planes;
+  t.tz = (b.n[2] + t.ntz - 1) / t.ntz;
+  return t;
+}
+// Planes per chunk for a plan's boxes: the longest chunk that gives the launch
+// kFinTiles tiles.
+inline int fin_planes(int nbox, const nyx_box* boxes) {
+  for (int planes = kFinPlanes; planes > kFinMinPlanes; planes /= 2) {
+    long long tiles = 0;
+    for (int i = 0; i < nbox; ++i) {
+      const FinTiling t = fin_tiling(boxes[i], planes);
+      tiles += (long long)t.ntx * t.nty * t.ntz;
+    }
+    if (tiles >= kFinTiles) return planes;
+  }
+  return kFinMinPlanes;
+}
+
 // Fill the derived fields and stage offsets of a box starting at `base`;
 // returns the element offset just past its stage arrays.
-inline long long box_layout(const nyx_box& b, int gidx, long long base, BoxDev* out) {
+inline long long box_layout(const nyx_box& b, int gidx, long long base, BoxDev* out,
+                            int planes = kFinPlanes) {
   BoxDev d{};
   for (int i = 0; i < 3; ++i) d.n[i] = b.n[i];
   d.ng = b.ng;
@@ -108,11 +143,13 @@ inline long long box_layout(const nyx_box& b, int gidx, long long base, BoxDev* 
   d.sc[0] = (unsigned)d.P;
   d.sc[1] = (unsigned)d.E;
   d.sc[2] = (unsigned)d.V;
-  d.tx = b.n[0] < 64 ? b.n[0] : 64;
-  d.ty = b.n[1] < kFinBlock / d.tx ? b.n[1] : kFinBlock / d.tx;
-  d.ntx = (b.n[0] + d.tx - 1) / d.tx;
-  d.nty = (b.n[1] + d.ty - 1) / d.ty;
-  d.ntiles = d.ntx * d.nty * ((b.n[2] + kFinPlanes - 1) / kFinPlanes);
+  const FinTiling t = fin_tiling(b, planes);
+  d.tx = t.tx;
+  d.ty = t.ty;
+  d.ntx = t.ntx;
+  d.nty = t.nty;
+  d.tz = t.tz;
+  d.ntiles = t.ntx * t.nty * t.ntz;
   d.fbx = (int)((d.E + kFrontOwn - 1) / kFrontOwn);
   if (out) *out = d;
   return o;
@@ -192,6 +229,13 @@ __device__ __forceinline__ unsigned long long wave_base(const void* p) {
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a);
   const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
   return (unsigned long long)hi << 32 | lo;
+}
+// A descriptor that no kernel of the step writes while it runs (a box, its
+// step constants), through a scalar pointer into the constant address space:
+// its reads stay scalar loads, also behind branches and the stage's stores.
+template <class T>
+__device__ __forceinline__ const T& scalar_ref(const T& r) {
+  return *(const T*)(const T __attribute__((address_space(4)))*)wave_base(&r);
 }
 template <class T>
 __device__ __forceinline__ T ldw(const T* base, unsigned i) {

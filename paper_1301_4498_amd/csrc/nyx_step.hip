@@ -117,7 +117,7 @@ __device__ __forceinline__ Loc locate(const StepArgs& A, int stage, int space, c
 
 // per-box constants of the step, computed once per box by the prologue
 __device__ __forceinline__ const StepC& step_consts(const StepArgs& A, const BoxDev& b) {
-  return A.consts[b.gidx];
+  return scalar_ref(A.consts[b.gidx]);
 }
 
 // ---------------------------------------------------------------------------
@@ -206,12 +206,13 @@ __device__ __forceinline__ void prim_body(const StepArgs& A, const Item& it) {
     if (p < A.small_pres) { p = A.small_pres; floors++; }
     double c = sqrt((A.gamma * p) / rho);
     real* q = (real*)A.work + b.w_prim;
-    stu(q, id, (real)rho);
-    stu(q + b.P, id, (real)u);
-    stu(q + 2 * b.P, id, (real)v);
-    stu(q + 3 * b.P, id, (real)w);
-    stu(q + 4 * b.P, id, (real)p);
-    stu(q + 5 * b.P, id, (real)c);
+    const unsigned pid = local_idx(id);
+    stw(q, pid, (real)rho);
+    stw(q + b.P, pid, (real)u);
+    stw(q + 2 * b.P, pid, (real)v);
+    stw(q + 3 * b.P, pid, (real)w);
+    stw(q + 4 * b.P, pid, (real)p);
+    stw(q + 5 * b.P, pid, (real)c);
   }
   if (A.stats) count(A, kFloorHits, floors);
 }
@@ -253,17 +254,17 @@ __device__ __forceinline__ void flat_body(const StepArgs& A, const Item& it) {
   const real* prim = (const real*)A.work + b.w_prim;
   const real* P = prim + 4 * b.P;
   const real sp = (real)A.small_pres;
-  const unsigned c0 = pidx_e(b, ie, je, ke);
+  const unsigned c0 = local_idx(pidx_e(b, ie, je, ke));
   const unsigned sd[3] = {1u, (unsigned)b.px, (unsigned)b.px * (unsigned)b.py};
   // neighbour shifts go into the (uniform) base; all loads share c0 and are
   // issued before any arithmetic, so a wave waits once for all of them
   real pd[3][7], ud[3][5];
-  const real pc = ldu(P, c0);
+  const real pc = ldw(P, c0);
   for (int d = 0; d < 3; ++d) {
     const unsigned s = sd[d];
     const real* U = prim + (1 + d) * b.P;
-    for (int o = -3; o <= 3; ++o) pd[d][o + 3] = o == 0 ? pc : ldu(P + (long long)o * s, c0);
-    for (int o = -2; o <= 2; ++o) ud[d][o + 2] = ldu(U + (long long)o * s, c0);
+    for (int o = -3; o <= 3; ++o) pd[d][o + 3] = o == 0 ? pc : ldw(P + (long long)o * s, c0);
+    for (int o = -2; o <= 2; ++o) ud[d][o + 2] = ldw(U + (long long)o * s, c0);
   }
   real cmin = (real)1;
   for (int d = 0; d < 3; ++d) {
@@ -289,7 +290,7 @@ __device__ __forceinline__ void flat_body(const StepArgs& A, const Item& it) {
     real cd = (real)1 - f;
     cmin = (d == 0) ? cd : vmin(cmin, cd);
   }
-  stu((real*)A.work + b.w_chi, e, cmin);
+  stw((real*)A.work + b.w_chi, local_idx(e), cmin);
 }
 __global__ __launch_bounds__(kBlock) void k_flat(StepArgs A) { flat_body(A, launch_item(A, kStFlat)); }
 
@@ -1029,19 +1030,24 @@ __device__ __forceinline__ RiemannOut two_shock(const StepArgs& A, const double*
 
 // Godunov state of a d-face as stored (rotated frame: rho, u_n, v_t1, w_t2, p)
 __device__ __forceinline__ void store_god(real* G, long long E, unsigned i, const RiemannOut& g) {
-  stu(G, i, (real)g.r);
-  stu(G + E, i, (real)g.u);
-  stu(G + 2 * E, i, (real)g.v);
-  stu(G + 3 * E, i, (real)g.w);
-  stu(G + 4 * E, i, (real)g.p);
+  i = local_idx(i);
+  stw(G, i, (real)g.r);
+  stw(G + E, i, (real)g.u);
+  stw(G + 2 * E, i, (real)g.v);
+  stw(G + 3 * E, i, (real)g.w);
+  stw(G + 4 * E, i, (real)g.p);
 }
 
 // A stored Godunov state of a face, in the rotated frame of that face.
 struct God {
   real r, u, v, w, p;
 };
-__device__ __forceinline__ God ld_god(const real* G, long long E, unsigned i) {
+// the same where lanes of a wavefront may read different boxes
+__device__ __forceinline__ God ld_god_any(const real* G, long long E, unsigned i) {
   return God{ldu(G, i), ldu(G + E, i), ldu(G + 2 * E, i), ldu(G + 3 * E, i), ldu(G + 4 * E, i)};
+}
+__device__ __forceinline__ God ld_god(const real* G, long long E, unsigned i) {
+  return God{ldw(G, i), ldw(G + E, i), ldw(G + 2 * E, i), ldw(G + 3 * E, i), ldw(G + 4 * E, i)};
 }
 
 // O6: lab-frame fluxes of a d-face from its Godunov state (flux arithmetic
@@ -1114,6 +1120,7 @@ __device__ __forceinline__ void tdiff(const StepArgs& A, int t, const God& glo, 
 template <bool FIRST>
 __device__ __forceinline__ void tdiff(const StepArgs& A, int t, const real* Glo, const real* Ghi,
                                       unsigned i, long long E, double* Dc, double& De) {
+  i = local_idx(i);
   tdiff<FIRST>(A, t, ld_god(Glo, E, i), ld_god(Ghi, E, i), Dc, De);
 }
 
@@ -1229,8 +1236,9 @@ struct Tally {
 };
 
 template <bool LEARNED, int D>
-__device__ __forceinline__ void riem0_dir(const StepArgs& A, const BoxDev& b, unsigned idx,
+__device__ __forceinline__ void riem0_dir(const StepArgs& A, const BoxDev& box, unsigned idx,
                                           __bf16* lds, Tally& T) {
+  const BoxDev& b = scalar_ref(box);
   constexpr int d = D;
   int c[3] = {0, 0, 0};
   if (idx < b.E) e_coords(b, idx, c);
@@ -1239,11 +1247,12 @@ __device__ __forceinline__ void riem0_dir(const StepArgs& A, const BoxDev& b, un
   double ql[5], qr[5];
   if (active) {
     const long long sL = e_stride(b, d);  // left cell: shift in the base, same offset e
+    const unsigned le = local_idx(e);
     const real* W = (const real*)A.work + b.w_edge;
     double Ls[5], Rs[5];
     for (int v = 0; v < 5; ++v) {
-      Ls[v] = (double)ldu(W + ((d * 2 + 1) * 5 + v) * b.E - sL, e);
-      Rs[v] = (double)ldu(W + ((d * 2 + 0) * 5 + v) * b.E, e);
+      Ls[v] = (double)ldw(W + ((d * 2 + 1) * 5 + v) * b.E - sL, le);
+      Rs[v] = (double)ldw(W + ((d * 2 + 0) * 5 + v) * b.E, le);
     }
     rotate(d, Ls, ql);
     rotate(d, Rs, qr);
@@ -1357,7 +1366,7 @@ __global__ __launch_bounds__(kBlock) void k_front(StepArgs A) {
     if (pre[mid] <= (int)x) lo = mid;
     else hi = mid;
   }
-  const BoxDev& b = A.table[lo];
+  const BoxDev& b = scalar_ref(A.table[lo]);
   unsigned floors = 0;
   Tally T;
   front_x(A, b, step_consts(A, b), x - (unsigned)pre[lo], floors, T);
@@ -1374,8 +1383,9 @@ __global__ __launch_bounds__(kBlock) void k_front(StepArgs A) {
 // registers next to the network's accumulators).  The plain form takes both
 // pairs of a direction per thread (riem1_both below).
 template <int D, int K>
-__device__ __forceinline__ void riem1_pair(const StepArgs& A, const BoxDev& b, unsigned idx,
+__device__ __forceinline__ void riem1_pair(const StepArgs& A, const BoxDev& box, unsigned idx,
                                            __bf16* lds, Tally& T) {
+  const BoxDev& b = scalar_ref(box);
   constexpr int d = D;
   constexpr int t = K == 0 ? (D + 1) % 3 : (D + 2) % 3;
   int c[3] = {0, 0, 0};
@@ -1396,7 +1406,7 @@ __device__ __forceinline__ void riem1_pair(const StepArgs& A, const BoxDev& b, u
       const long long sh = s == 0 ? -sdd : 0;
       const int side = s == 0 ? 1 : 0;  // left cell gives its right-face state
       double q[5];
-      for (int v = 0; v < 5; ++v) q[v] = (double)ldu(W + ((d * 2 + side) * 5 + v) * b.E + sh, e);
+      for (int v = 0; v < 5; ++v) q[v] = (double)ldw(W + ((d * 2 + side) * 5 + v) * b.E + sh, e);
       const real* Gc = G0 + sh;
       double Dc[5], De;
       tdiff<true>(A, t, Gc, Gc + stt, e, b.E, Dc, De);
@@ -1421,8 +1431,9 @@ __device__ __forceinline__ void riem1_pair(const StepArgs& A, const BoxDev& b, u
 // a wave per SIMD.
 constexpr int kPark = 10;
 template <int D>
-__device__ __forceinline__ void riem1_both(const StepArgs& A, const BoxDev& b, unsigned idx,
+__device__ __forceinline__ void riem1_both(const StepArgs& A, const BoxDev& box, unsigned idx,
                                            double* park, Tally& T) {
+  const BoxDev& b = scalar_ref(box);
   constexpr int d = D;
   int c[3] = {0, 0, 0};
   if (idx < b.E) e_coords(b, idx, c);
@@ -1437,10 +1448,11 @@ __device__ __forceinline__ void riem1_both(const StepArgs& A, const BoxDev& b, u
     const StepC& C = step_consts(A, b);
     const real* W = (const real*)A.work + b.w_edge;
     double q[2][5];
+    const unsigned le = local_idx(e);
     for (int s = 0; s < 2; ++s) {
       const long long sh = s == 0 ? -sdd : 0;
       const int side = s == 0 ? 1 : 0;  // left cell gives its right-face state
-      for (int v = 0; v < 5; ++v) q[s][v] = (double)ldu(W + ((d * 2 + side) * 5 + v) * b.E + sh, e);
+      for (int v = 0; v < 5; ++v) q[s][v] = (double)ldw(W + ((d * 2 + side) * 5 + v) * b.E + sh, le);
     }
     for (int k = 0; k < 2; ++k) {
       if (!want[k]) continue;
@@ -1546,10 +1558,11 @@ __device__ __forceinline__ void final_states(const StepArgs& A, const BoxDev& b,
   // once for all of them
   real qe[2][5];
   God ga[2][2], gb[2][2];
+  e = local_idx(e);
   for (int s = 0; s < 2; ++s) {
     const long long sh = s == 0 ? -sdd : 0;  // cell shift in the bases, offset e
     const int side = s == 0 ? 1 : 0;
-    for (int v = 0; v < 5; ++v) qe[s][v] = ldu(W + ((d * 2 + side) * 5 + v) * b.E + sh, e);
+    for (int v = 0; v < 5; ++v) qe[s][v] = ldw(W + ((d * 2 + side) * 5 + v) * b.E + sh, e);
     if (CARRY == 2 && s == 0) continue;
     ga[s][0] = ld_god(G1a + sh, b.E, e);
     ga[s][1] = ld_god(G1a + sh + s1, b.E, e);
@@ -1579,8 +1592,9 @@ __device__ __forceinline__ void final_states(const StepArgs& A, const BoxDev& b,
 }
 
 template <int MODE, int D>
-__device__ __forceinline__ void riem2_dir(const StepArgs& A, const BoxDev& b, unsigned idx,
+__device__ __forceinline__ void riem2_dir(const StepArgs& A, const BoxDev& box, unsigned idx,
                                           __bf16* lds, Tally& T) {
+  const BoxDev& b = scalar_ref(box);
   constexpr bool LEARNED = MODE == 1;
   constexpr int d = D;
   constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
@@ -1704,17 +1718,18 @@ struct CellIn {
 };
 __device__ __forceinline__ CellIn load_cell(const StepArgs& A, const BoxDev& b, unsigned id) {
   CellIn x;
+  id = local_idx(id);
   const double* U = A.Uin + b.soff;
-  x.U0 = ldu(U, id);
-  x.Um[0] = ldu(U + b.sstride, id);
-  x.Um[1] = ldu(U + 2 * b.sstride, id);
-  x.Um[2] = ldu(U + 3 * b.sstride, id);
-  x.UE = ldu(U + 4 * b.sstride, id);
-  x.Ue = ldu(U + 5 * b.sstride, id);
+  x.U0 = ldw(U, id);
+  x.Um[0] = ldw(U + b.sstride, id);
+  x.Um[1] = ldw(U + 2 * b.sstride, id);
+  x.Um[2] = ldw(U + 3 * b.sstride, id);
+  x.UE = ldw(U + 4 * b.sstride, id);
+  x.Ue = ldw(U + 5 * b.sstride, id);
   const real* G = (const real*)A.grav + b.goff;
-  x.g[0] = (double)ldu(G, id);
-  x.g[1] = (double)ldu(G + b.gstride, id);
-  x.g[2] = (double)ldu(G + 2 * b.gstride, id);
+  x.g[0] = (double)ldw(G, id);
+  x.g[1] = (double)ldw(G + b.gstride, id);
+  x.g[2] = (double)ldw(G + 2 * b.gstride, id);
   return x;
 }
 
@@ -1801,12 +1816,13 @@ __device__ __forceinline__ double update_apply(const StepArgs& A, const StepC& C
     n.nsync += 1;
   }
   double* O = A.Uout + b.soff;
-  stu(O, id, s0);
-  stu(O + b.sstride, id, nm[0]);
-  stu(O + 2 * b.sstride, id, nm[1]);
-  stu(O + 3 * b.sstride, id, nm[2]);
-  stu(O + 4 * b.sstride, id, nE);
-  stu(O + 5 * b.sstride, id, ne);
+  id = local_idx(id);
+  stw(O, id, s0);
+  stw(O + b.sstride, id, nm[0]);
+  stw(O + 2 * b.sstride, id, nm[1]);
+  stw(O + 3 * b.sstride, id, nm[2]);
+  stw(O + 4 * b.sstride, id, nE);
+  stw(O + 5 * b.sstride, id, ne);
   bool fin = isfinite(s0) && isfinite(nm[0]) && isfinite(nm[1]) && isfinite(nm[2]) &&
              isfinite(nE) && isfinite(ne);
   n.nnf += fin ? 0 : 1;
@@ -1841,11 +1857,12 @@ __device__ __forceinline__ void update_body(const StepArgs& A, const Item& it) {
     const unsigned id = ((unsigned)(k + b.ng) * (unsigned)b.py + (unsigned)(j + b.ng)) *
                             (unsigned)b.px + (unsigned)(i + b.ng);
     // every load of the cell is issued before any arithmetic
+    const unsigned le = local_idx(e);
     God gl[3], gh[3];
     for (int d = 0; d < 3; ++d) {
       const real* G = G2 + (long long)d * kGod * b.E;
-      gl[d] = ld_god(G, b.E, e);
-      gh[d] = ld_god(G + (long long)e_stride(b, d), b.E, e);
+      gl[d] = ld_god(G, b.E, le);
+      gh[d] = ld_god(G + (long long)e_stride(b, d), b.E, le);
     }
     const CellIn x = load_cell(A, b, id);
     double D[6], Pi;
@@ -1862,7 +1879,7 @@ __global__ __launch_bounds__(kBlock) void k_update(StepArgs A) {
 // ---------------------------------------------------------------------------
 // stages 6 and 7 fused (plain solver, no harvest).  A workgroup takes a tile
 // of TX x TY cell columns of a box and marches up one chunk of at most
-// kFinPlanes planes in z (a chunk above the first solves its bottom z-face
+// BoxDev::tz planes in z (a chunk above the first solves its bottom z-face
 // again: the chunk below owns it).  Per plane it
 // solves the low x- and y-faces of its cells and each cell's high z-face,
 // and also the x-faces past the tile's last column and the y-faces past its
@@ -1931,7 +1948,7 @@ __global__ __launch_bounds__(kFinBlock, kFinWaves) void k_final(StepArgs A) {
     if (pre[mid] <= lin) lo = mid;
     else hi = mid;
   }
-  const BoxDev& b = A.table[lo];
+  const BoxDev& b = scalar_ref(A.table[lo]);
   const StepC& C = step_consts(A, b);
   const int TX = b.tx, TY = b.ty;
   const int tile = lin - pre[lo];
@@ -1940,8 +1957,8 @@ __global__ __launch_bounds__(kFinBlock, kFinWaves) void k_final(StepArgs A) {
   const int tyi = (tile - tzi * txy) / b.ntx;
   const int i0 = (tile - tzi * txy - tyi * b.ntx) * TX, j0 = tyi * TY;
   const int nx = b.n[0], ny = b.n[1];
-  const int k0 = tzi * kFinPlanes;
-  const int k1 = b.n[2] < k0 + kFinPlanes ? b.n[2] : k0 + kFinPlanes;
+  const int k0 = tzi * b.tz;
+  const int k1 = b.n[2] < k0 + b.tz ? b.n[2] : k0 + b.tz;
   const int t = (int)threadIdx.x;
   const int tj = t / TX, ti = t - tj * TX;
   const bool lane = t < TX * TY;
@@ -2043,14 +2060,14 @@ __global__ __launch_bounds__(kBlock) void k_flux_record(StepArgs A, const BoxDev
   const real ah = (real)C.a_h;
   double acc[6];
   real f[8];
-  final_flux(A, d, ld_god(G, b.E, e), ah, f);
+  final_flux(A, d, ld_god_any(G, b.E, e), ah, f);
   for (int c = 0; c < 6; ++c) acc[c] = (double)f[c];
   if (R.nsub == 2) {
     const int t1 = d == 0 ? 1 : 0, t2 = d == 2 ? 1 : 2;
     const unsigned o1 = e_stride(b, t1), o2 = e_stride(b, t2);
     const unsigned sub[3] = {e + o1, e + o2, e + o1 + o2};
     for (int q = 0; q < 3; ++q) {
-      final_flux(A, d, ld_god(G, b.E, sub[q]), ah, f);
+      final_flux(A, d, ld_god_any(G, b.E, sub[q]), ah, f);
       for (int c = 0; c < 6; ++c) acc[c] = acc[c] + (double)f[c];
     }
   }
