@@ -292,7 +292,8 @@ int nyx_batch_autotune_mode(nyx_batch* plan, const double* state_in, const void*
  *                        plane by plane along z (z-pencils of row tiles), so
  *                        that a cell's z-neighbours are read soon after it.
  * The order changes no result bit (every cell and face computes the same
- * expressions).  A new plan uses entry 0 for every stage.
+ * expressions).  A new plan uses entry 0, except NYX_TUNE_CELL_MAJOR for the
+ * tracing and the transverse stage.
  *
  * nyx_batch_autotune runs reps + 1 steps per candidate with the arguments of
  * nyx_hydro_step_batched (no counters; state_out and dt_next, when not NULL,

@@ -202,6 +202,7 @@ int step_one_box(const nyx_params* p, const nyx_box* box, const double* state_in
   A.a_new = a_new;
   A.stats = stats;
   A.slots = (unsigned long long*)((char*)workspace + kOffSlots);
+  for (int i = 0; i < kStages; ++i) A.tune[i] = kTuneDefault[i];
   A.dt_next = dt_next;
   BoxDev* tab = (BoxDev*)((char*)workspace + kOffTable);
   int* pre = (int*)((char*)workspace + kOffPrefix);
@@ -366,7 +367,7 @@ struct nyx_batch {
   long long harvest_cap = 0;
   unsigned harvest_keep = 0;
   unsigned long long harvest_seed = 0;
-  int tune[kStages] = {0};        // launch-order candidate per stage
+  int tune[kStages];              // launch-order candidate per stage
   // flux register fed after every group's update (two-level sync)
   const FluxRec* reg_recs = nullptr;  // device, sorted by box
   std::vector<long long> reg_prefix;  // per box, host
@@ -439,6 +440,7 @@ int nyx_batch_create(const nyx_params* p, int nbox, const nyx_box* boxes, void* 
   nyx_batch* plan = new (std::nothrow) nyx_batch();
   if (!plan) return NYX_E_WORKSPACE;
   plan->prm = *p;
+  for (int i = 0; i < kStages; ++i) plan->tune[i] = kTuneDefault[i];
   plan->nbox = nbox;
   plan->boxes.assign(boxes, boxes + nbox);
   std::vector<BoxDev> host(nbox);
