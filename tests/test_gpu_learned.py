@@ -69,6 +69,34 @@ def test_gradients_match_cpu_oracle(env, records):
         f.adam(lr=1e-3)  # move away from the initial point and check again
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 513, 16385, 256 * 512 + 70])
+def test_gradient_tiles_match_cpu_oracle(env, n):
+    """Sample counts at the edges of the training kernel's tiles (64 samples),
+    of a workgroup's tiles (one from 16385 samples on) and of its input chunks
+    (512 samples), one sample in 50 outside the training domain; the bar of
+    the FP32 gradients above."""
+    nyx, learn, torch = env
+    rng = np.random.default_rng(n)
+    rec = np.empty((n, 15))
+    for side in (0, 5):
+        rec[:, side] = np.exp(rng.normal(0.0, 0.4, n))
+        rec[:, side + 1:side + 4] = rng.normal(0.0, 0.5, (n, 3))
+        rec[:, side + 4] = 0.6 * np.exp(rng.normal(0.0, 0.5, n))
+    rec[:, 10] = 0.5 * (rec[:, 4] + rec[:, 9]) * np.exp(rng.normal(0.0, 0.2, n))
+    rec[:, 11] = 0.5 * (rec[:, 1] + rec[:, 6])
+    rec[:, 12:15] = np.exp(rng.normal(0.0, 0.4, (n, 3)))
+    rec[25::50, 2] = 1e4
+    rec = rec.astype(np.float32)
+    f = learn.LearnedFlux(seed=n)
+    loss, grad = f.loss_grad(to_dev(rec))
+    torch.cuda.synchronize()
+    x, y = oracle.mlp_normalize(rec.astype(np.float64))
+    lref, gref = oracle.mlp_loss_grad(f.params.double().cpu().numpy(), x, y)
+    g = grad.double().cpu().numpy()
+    assert float(loss.item()) == pytest.approx(lref, rel=1e-4)
+    assert np.linalg.norm(g - gref) <= 1e-4 * np.linalg.norm(gref)
+
+
 def test_bf16_inference_matches_fp64_forward(env, records):
     nyx, learn, torch = env
     f = learn.LearnedFlux(seed=7)
