@@ -54,6 +54,41 @@ def test_cic_deposit_matches_oracle(nyx):
 
 
 
+@pytest.mark.parametrize("order", ["lattice", "one_cell", "straddling", "scattered", "mixed", "skipped"])
+def test_cic_deposit_by_particle_order(nyx, order):
+    """Particle orders that take the deposit's two paths (a workgroup's 1024
+    particles collected in a box of cells, or added to memory directly), and
+    their edges: a box that wraps around the domain, one that spans an axis
+    whole, a workgroup without a valid particle, a partly filled one.  The
+    bound is that of the atomic sums: 1e-13 of each cell."""
+    import torch
+    rng = np.random.default_rng(5)
+    nx, ny, nz = 48, 20, 32
+    dx = 1.0 / 48
+    L = np.array([nx, ny, nz]) * dx
+    i, j, k = np.meshgrid(np.arange(nx), np.arange(ny), np.arange(nz), indexing="ij")
+    lat = np.stack([a.transpose(2, 1, 0).ravel() + 0.5 for a in (i, j, k)]) * dx
+    pos = lat + 0.3 * dx * rng.normal(size=lat.shape)
+    if order == "one_cell":
+        pos = np.tile(np.array([[7.3], [4.1], [9.9]]) * dx, (1, 3000)) + 0.1 * dx * rng.random((3, 3000))
+    elif order == "straddling":
+        pos = rng.normal(0.0, 1.5 * dx, (3, 5000)) + np.array([[0.0], [L[1]], [5 * L[2]]])
+    elif order == "scattered":
+        pos = rng.uniform(-1, 2, (3, 20001)) * L[:, None]
+    elif order == "mixed":
+        pos[:, 3000:9000] = rng.uniform(0, 1, (3, 6000)) * L[:, None]
+    elif order == "skipped":
+        pos[0, :1024] = np.nan
+        pos[1, 1030:2000:7] = np.inf
+        pos[2, 2100] = 1e30
+    mass = rng.uniform(0.5, 2.0, pos.shape[1])
+    rho = torch.zeros((nz, ny, nx), dtype=torch.float64, device="cuda")
+    nyx.cic_deposit(to_dev(pos), to_dev(mass), (nx, ny, nz), dx, rho)
+    ok = (np.abs(np.nan_to_num(pos / dx, nan=1e30, posinf=1e30)) < 1e15).all(axis=0)
+    ref = oracle.cic_deposit(np.ascontiguousarray(pos[:, ok]), mass[ok], (nz, ny, nx), dx)
+    assert np.allclose(rho.cpu().numpy(), ref, rtol=1e-13, atol=0)
+
+
 def test_cic_deposit_of_no_particles_is_a_no_op(nyx):
     import torch
     rho = torch.full((4, 6, 8), 1.5, dtype=torch.float64, device="cuda")
