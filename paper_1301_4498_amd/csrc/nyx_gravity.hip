@@ -23,6 +23,7 @@ namespace nyx {
 namespace grav {
 
 constexpr int kRedBlocks = 4096;  // block partials of a reduction
+constexpr int kResidBlocks = 2048;
 
 __device__ __forceinline__ unsigned wrap_dec(unsigned i, unsigned n) { return i == 0 ? n - 1 : i - 1; }
 __device__ __forceinline__ unsigned wrap_inc(unsigned i, unsigned n) { return i + 1 == n ? 0 : i + 1; }
@@ -236,12 +237,12 @@ __device__ double block_reduce(double v) {
   return sh[0];
 }
 
-// MODE 0: sum of rho_total (natural order); 1: max |f - L phi|; 2: max |f|;
-// 3: sum of phi (solver order)
+// MODE 0: sum of rho_total (natural order); 2: max |f|; 3: sum of phi
+// (solver order)
 template <int MODE>
 __global__ __launch_bounds__(kBlock) void k_partial(RhoSrc R, const double* __restrict__ phi,
                                                     const double* __restrict__ f, Grid g,
-                                                    double inv_h2, double* __restrict__ part) {
+                                                    double* __restrict__ part) {
   constexpr int OP = (MODE == 0 || MODE == 3) ? 0 : 1;
   const unsigned n = g.nx * g.ny * g.nz;
   double acc = 0.0;
@@ -249,15 +250,6 @@ __global__ __launch_bounds__(kBlock) void k_partial(RhoSrc R, const double* __re
     double v;
     if (MODE == 0) {
       v = rho_total(R, g, c);
-    } else if (MODE == 1) {
-      // c walks the solver's order: the cell's colour, row and half index
-      const unsigned half = g.nx >> 1, hn = n >> 1;
-      const unsigned color = c / hn, r = c - color * hn;
-      const unsigned ih = r % half, row = r / half;
-      const unsigned j = row % g.ny, k = row / g.ny;
-      const unsigned i = 2 * ih + ((j + k + color) & 1);
-      const double lap = (nb_sum(phi, g, i, j, k) - 6.0 * phi[c]) * inv_h2;
-      v = fabs(f[c] - lap);
     } else if (MODE == 2) {
       v = fabs(f[c]);
     } else {
@@ -309,6 +301,17 @@ __global__ __launch_bounds__(kBlock) void k_sub_mean(const double* __restrict__ 
 }
 
 // ---- multigrid kernels ----
+// x / 6, correctly rounded, by a product and one correction instead of the
+// range-scaled division: y = RN(1/6) is within 2^-54 of 1/6, so x y rounded is
+// within one unit in the last place of x / 6, the remainder x - 6 q is exact,
+// and adding its quotient to q rounds to the correctly rounded x / 6
+// (Markstein's theorem).
+__device__ __forceinline__ double div6(double x) {
+  constexpr double y = 1.0 / 6.0;
+  const double q = x * y;
+  return fma(fma(-6.0, q, x), y, q);
+}
+
 // one Gauss-Seidel half sweep: cells with (i + j + k) % 2 == color
 __global__ __launch_bounds__(kBlock) void k_rbgs(double* __restrict__ phi,
                                                  const double* __restrict__ f, Grid g, double h2,
@@ -320,36 +323,205 @@ __global__ __launch_bounds__(kBlock) void k_rbgs(double* __restrict__ phi,
   const unsigned j = r % g.ny, k = r / g.ny;
   const unsigned i = 2 * ih + ((j + k + color) & 1);
   const unsigned c = at(g, i, j, k);
-  phi[c] = (nb_sum(phi, g, i, j, k) - h2 * f[c]) / 6.0;
+  phi[c] = div6(nb_sum(phi, g, i, j, k) - h2 * f[c]);
 }
 
-// All sweeps of a small level in one workgroup (the half sweeps separated
-// by barriers): the same updates, in the same order, as k_rbgs launches.
-__global__ __launch_bounds__(kBlock) void k_rbgs_small(double* __restrict__ phi,
-                                                       const double* __restrict__ f, Grid g,
-                                                       double h2, int sweeps) {
-  const unsigned half = g.nx >> 1, n = half * g.ny * g.nz;
-  for (int it = 0; it < sweeps; ++it)
+// One pair of cells (2 ih, 2 ih + 1) of a row and what its stencils read: in
+// the solver's order a cell's x neighbours are entries ih and ih -+ 1 of the
+// other colour's row, its y and z neighbours the entries ih of the rows beside.
+struct Pair {
+  unsigned row, rs, rn, rb, rt;  // row starts: own, y below and above, z below and above
+  unsigned ih, im, ip;           // half index and its periodic neighbours
+  unsigned par;                  // (j + k) & 1
+};
+__device__ __forceinline__ Pair pair_at(unsigned half, unsigned ny, unsigned nz, unsigned ih,
+                                        unsigned j, unsigned k) {
+  Pair p;
+  p.row = (k * ny + j) * half;
+  p.rs = (k * ny + wrap_dec(j, ny)) * half;
+  p.rn = (k * ny + wrap_inc(j, ny)) * half;
+  p.rb = (wrap_dec(k, nz) * ny + j) * half;
+  p.rt = (wrap_inc(k, nz) * ny + j) * half;
+  p.ih = ih;
+  p.im = wrap_dec(ih, half);
+  p.ip = wrap_inc(ih, half);
+  p.par = (j + k) & 1;
+  return p;
+}
+// nb_sum of the pair's cell of colour `color`; other: the other colour's array
+__device__ __forceinline__ double pair_sum(const double* other, const Pair& p, unsigned color) {
+  const bool odd = ((p.par + color) & 1) != 0;
+  const double sx = other[p.row + (odd ? p.ih : p.im)] + other[p.row + (odd ? p.ip : p.ih)];
+  const double sy = other[p.rs + p.ih] + other[p.rn + p.ih];
+  const double sz = other[p.rb + p.ih] + other[p.rt + p.ih];
+  return (sx + sy) + sz;
+}
+
+// max |f - L phi|: one lane per pair of cells.  Bound by memory (16 bytes a
+// cell): 97 us at 256^3 with a lane per cell, its coordinates divided out, 89
+// with pairs.
+__global__ __launch_bounds__(kBlock) void k_resid_max(const double* __restrict__ phi,
+                                                      const double* __restrict__ f, Grid g,
+                                                      FastDiv dh, FastDiv dy, double inv_h2,
+                                                      double* __restrict__ part) {
+  const unsigned half = g.nx >> 1, hn = half * g.ny * g.nz;
+  double acc = 0.0;
+  for (unsigned t = blockIdx.x * kBlock + threadIdx.x; t < hn; t += gridDim.x * kBlock) {
+    const unsigned r = fast_div(t, dh), ih = t - r * half;
+    const unsigned k = fast_div(r, dy), j = r - k * g.ny;
+    const Pair p = pair_at(half, g.ny, g.nz, ih, j, k);
     for (unsigned color = 0; color < 2; ++color) {
-      for (unsigned t = threadIdx.x; t < n; t += kBlock) {
-        const unsigned ih = t % half, r = t / half;
-        const unsigned j = r % g.ny, k = r / g.ny;
-        const unsigned i = 2 * ih + ((j + k + color) & 1);
-        const unsigned c = at(g, i, j, k);
-        phi[c] = (nb_sum(phi, g, i, j, k) - h2 * f[c]) / 6.0;
-      }
-      __syncthreads();
+      const unsigned c = color * hn + t;
+      const double lap = (pair_sum(phi + (1 - color) * hn, p, color) - 6.0 * phi[c]) * inv_h2;
+      acc = fmax(acc, fabs(f[c] - lap));
     }
+  }
+  const double b = block_reduce<1>(acc);
+  if (threadIdx.x == 0) part[blockIdx.x] = b;
+}
+
+// The V-cycle from a level of at most kSmallCells cells down, in one launch:
+// one workgroup keeps phi and f of these levels in LDS and carries out the
+// same sweeps, restrictions and prolongations, in the same order, as the
+// kernels of the larger levels do.  Bound by latency: the chain of half sweeps
+// (88 from 16^3 down), each an LDS read, seven operations and a barrier.  As
+// 13 launches on arrays in memory a cycle took about 115 us here; in one 54 us;
+// with the pairs' places and right-hand sides kept in registers and div6 33 us.
+constexpr int kCoarseThreads = 512;
+constexpr int kMaxCoarse = 8;  // levels of at most 4096 cells, halved down to 8 cells
+constexpr size_t kSmallCells = 4096;
+struct CoarseArgs {
+  int nlev;
+  Grid g[kMaxCoarse];
+  double h2[kMaxCoarse], inv_h2[kMaxCoarse];
+  double* phi;  // of the finest of these levels
+  const double* f;
+};
+
+// The half sweeps of one of these levels: NP pairs per thread, whose places
+// and right-hand sides stay in registers over the sweeps.
+template <int NP>
+__device__ __forceinline__ void lds_sweeps(double* phi, const double* f, const Grid& g, double h2,
+                                           int sweeps) {
+  const unsigned half = g.nx >> 1, hn = half * g.ny * g.nz;
+  // a level of one wavefront's pairs is swept by the first one alone, whose
+  // LDS accesses keep their order without a barrier
+  const bool one = NP == 1 && hn <= 64;
+  if (one && threadIdx.x >= 64) return;
+  Pair p[NP];
+  double hf[NP][2];
+  for (int q = 0; q < NP; ++q) {
+    const unsigned t = threadIdx.x + q * kCoarseThreads;
+    if (t >= hn) continue;
+    const unsigned r = t / half, ih = t - r * half, k = r / g.ny, j = r - k * g.ny;
+    p[q] = pair_at(half, g.ny, g.nz, ih, j, k);
+    hf[q][0] = h2 * f[t];
+    hf[q][1] = h2 * f[hn + t];
+  }
+  for (int it = 0; it < sweeps; ++it)
+#pragma unroll
+    for (unsigned color = 0; color < 2; ++color) {
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        const unsigned t = threadIdx.x + q * kCoarseThreads;
+        if (t < hn)
+          phi[color * hn + t] = div6(pair_sum(phi + (1 - color) * hn, p[q], color) - hf[q][color]);
+      }
+      if (one) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      } else {
+        __syncthreads();
+      }
+    }
+}
+__device__ __forceinline__ void lds_smooth(double* phi, const double* f, const Grid& g, double h2,
+                                           int sweeps) {
+  const unsigned hn = (g.nx >> 1) * g.ny * g.nz;
+  if (hn > kCoarseThreads) lds_sweeps<kSmallCells / 2 / kCoarseThreads>(phi, f, g, h2, sweeps);
+  else lds_sweeps<1>(phi, f, g, h2, sweeps);
+  __syncthreads();
+}
+
+// Two sweeps (four half sweeps) of a level in one launch, from `src` to `dst`:
+// a workgroup loads a tile of 8^3 cells with a halo of four, one cell per half
+// sweep, relaxes the whole 16^3 block in LDS and stores the tile.  Every cell
+// gets the operations of the half sweeps above on the same values.
+// For levels of at most kTileCells cells, where the four launches it replaces
+// are latency: two sweeps of 64^3 18.8 -> 10.0 us, of 32^3 18.4 -> 5.9 us.  A
+// larger level is bound by its traffic, which the halo multiplies by eight
+// (128^3 takes 28 us in place, and its tiles alone would load 268 MB).
+constexpr int kTileThreads = 512;
+constexpr int kTB = 16, kTBHalf = 8, kTileOwn = 8, kTileHalo = 4;
+constexpr size_t kTileCells = 1 << 18;
+__global__ __launch_bounds__(kTileThreads) void k_smooth_tile(const double* __restrict__ src,
+                                                              double* __restrict__ dst,
+                                                              const double* __restrict__ f, Grid g,
+                                                              unsigned tx, unsigned ty,
+                                                              double h2) {
+  constexpr unsigned hn = kTBHalf * kTB * kTB;      // pairs of the block
+  constexpr int NP = hn / kTileThreads;             // per thread
+  constexpr int SJ = kTBHalf, SK = kTBHalf * kTB;   // LDS strides of a row and a plane
+  __shared__ double u[2 * hn];
+  const unsigned half = g.nx >> 1, gn = half * g.ny * g.nz;
+  const unsigned b = blockIdx.x, bz = b / (tx * ty), by = (b - bz * tx * ty) / tx;
+  const unsigned bx = b - bz * tx * ty - by * tx;
+  auto wrap = [](int x, unsigned n) { return (unsigned)(((x % (int)n) + (int)n) % (int)n); };
+  unsigned at_[NP];        // the pair's place in the level's colour arrays
+  int li[NP];              // and in the block
+  double hf[NP][2];
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const int t = (int)threadIdx.x + q * kTileThreads;
+    const int lh = t % kTBHalf, lj = t / SJ % kTB, lk = t / SK;
+    const unsigned ih = wrap((int)(bx * (kTileOwn / 2)) + lh - kTileHalo / 2, half);
+    const unsigned j = wrap((int)(by * kTileOwn) + lj - kTileHalo, g.ny);
+    const unsigned k = wrap((int)(bz * kTileOwn) + lk - kTileHalo, g.nz);
+    at_[q] = (k * g.ny + j) * half + ih;
+    li[q] = t;
+    u[t] = src[at_[q]];
+    u[hn + t] = src[gn + at_[q]];
+    hf[q][0] = h2 * f[at_[q]];
+    hf[q][1] = h2 * f[gn + at_[q]];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int stage = 0; stage < 4; ++stage) {
+    const int color = stage & 1;
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int t = li[q], lh = t % kTBHalf, lj = t / SJ % kTB, lk = t / SK;
+      // block origins are even, so the block's parity is the level's
+      const bool odd = ((lj + lk + color) & 1) != 0;
+      const int i = 2 * lh + (odd ? 1 : 0);
+      if (i >= 1 && i < kTB - 1 && lj >= 1 && lj < kTB - 1 && lk >= 1 && lk < kTB - 1) {
+        const double* o = u + (1 - color) * hn;
+        const double sx = o[odd ? t : t - 1] + o[odd ? t + 1 : t];
+        const double sy = o[t - SJ] + o[t + SJ];
+        const double sz = o[t - SK] + o[t + SK];
+        u[color * hn + t] = div6(((sx + sy) + sz) - hf[q][color]);
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const int t = li[q], lh = t % kTBHalf, lj = t / SJ % kTB, lk = t / SK;
+    const bool own = lh >= kTileHalo / 2 && lh < (kTileHalo + kTileOwn) / 2 && lj >= kTileHalo &&
+                     lj < kTileHalo + kTileOwn && lk >= kTileHalo && lk < kTileHalo + kTileOwn &&
+                     bx * (kTileOwn / 2) + lh - kTileHalo / 2 < half &&
+                     by * kTileOwn + lj - kTileHalo < g.ny && bz * kTileOwn + lk - kTileHalo < g.nz;
+    if (own) {
+      dst[at_[q]] = u[t];
+      dst[gn + at_[q]] = u[hn + t];
+    }
+  }
 }
 
 // coarse f = mean of the eight children's residuals f - L phi; coarse phi = 0
-__global__ __launch_bounds__(kBlock) void k_restrict(const double* __restrict__ phi,
-                                                     const double* __restrict__ f, Grid g,
-                                                     double inv_h2, Grid gc,
-                                                     double* __restrict__ fc,
-                                                     double* __restrict__ phic) {
-  const unsigned C = blockIdx.x * kBlock + threadIdx.x;
-  if (C >= gc.nx * gc.ny * gc.nz) return;
+__device__ __forceinline__ void restrict_cell(unsigned C, const double* phi, const double* f,
+                                              const Grid& g, double inv_h2, const Grid& gc,
+                                              double* fc, double* phic) {
   const unsigned I = C % gc.nx, J = (C / gc.nx) % gc.ny, K = C / (gc.nx * gc.ny);
   double s = 0.0;
   for (int q = 0; q < 8; ++q) {
@@ -362,16 +534,22 @@ __global__ __launch_bounds__(kBlock) void k_restrict(const double* __restrict__ 
   fc[a] = 0.125 * s;
   phic[a] = 0.0;
 }
+__global__ __launch_bounds__(kBlock) void k_restrict(const double* __restrict__ phi,
+                                                     const double* __restrict__ f, Grid g,
+                                                     double inv_h2, Grid gc,
+                                                     double* __restrict__ fc,
+                                                     double* __restrict__ phic) {
+  const unsigned C = blockIdx.x * kBlock + threadIdx.x;
+  if (C < gc.nx * gc.ny * gc.nz) restrict_cell(C, phi, f, g, inv_h2, gc, fc, phic);
+}
 
 // fine phi += trilinear (cell-centred) interpolation of the coarse
 // correction: one lane per coarse cell reads its 3 x 3 x 3 neighbourhood
 // once and corrects its eight children; child (a, b, c) takes the parent
 // with weight 27/64, the three face neighbours on its side 9/64, the three
 // edge neighbours 3/64 and the corner 1/64
-__global__ __launch_bounds__(kBlock) void k_prolong(double* __restrict__ phi, Grid g,
-                                                    const double* __restrict__ ec, Grid gc) {
-  const unsigned C = blockIdx.x * kBlock + threadIdx.x;
-  if (C >= gc.nx * gc.ny * gc.nz) return;
+__device__ __forceinline__ void prolong_cell(unsigned C, double* phi, const Grid& g,
+                                             const double* ec, const Grid& gc) {
   unsigned I, J, K;
   coords(gc, C, &I, &J, &K);
   const unsigned xs[3] = {wrap_dec(I, gc.nx), I, wrap_inc(I, gc.nx)};
@@ -394,6 +572,47 @@ __global__ __launch_bounds__(kBlock) void k_prolong(double* __restrict__ phi, Gr
     const unsigned f = at(g, 2 * I + a, 2 * J + b, 2 * K + c);
     phi[f] = phi[f] + v;
   }
+}
+__global__ __launch_bounds__(kBlock) void k_prolong(double* __restrict__ phi, Grid g,
+                                                    const double* __restrict__ ec, Grid gc) {
+  const unsigned C = blockIdx.x * kBlock + threadIdx.x;
+  if (C < gc.nx * gc.ny * gc.nz) prolong_cell(C, phi, g, ec, gc);
+}
+
+constexpr int kPre = 2, kPost = 2, kCoarseSweeps = 32;
+
+__global__ __launch_bounds__(kCoarseThreads) void k_coarse(CoarseArgs A) {
+  // every level an eighth of the one above: at most 4096 (1 + 1/8 + 1/64 + ...)
+  // cells in all
+  __shared__ double sphi[kSmallCells + kSmallCells / 7 + 8], sf[kSmallCells + kSmallCells / 7 + 8];
+  const unsigned n0 = A.g[0].nx * A.g[0].ny * A.g[0].nz;
+  for (unsigned i = threadIdx.x; i < n0; i += kCoarseThreads) {
+    sphi[i] = A.phi[i];
+    sf[i] = A.f[i];
+  }
+  __syncthreads();
+  unsigned o = 0;  // offset of the level's cells
+  int l = 0;
+  for (; l + 1 < A.nlev; ++l) {
+    const Grid g = A.g[l], gc = A.g[l + 1];
+    const unsigned n = g.nx * g.ny * g.nz, nc = gc.nx * gc.ny * gc.nz;
+    lds_smooth(sphi + o, sf + o, g, A.h2[l], kPre);
+    for (unsigned C = threadIdx.x; C < nc; C += kCoarseThreads)
+      restrict_cell(C, sphi + o, sf + o, g, A.inv_h2[l], gc, sf + o + n, sphi + o + n);
+    __syncthreads();
+    o += n;
+  }
+  lds_smooth(sphi + o, sf + o, A.g[l], A.h2[l], kCoarseSweeps);
+  for (--l; l >= 0; --l) {
+    const Grid g = A.g[l], gc = A.g[l + 1];
+    const unsigned nc = gc.nx * gc.ny * gc.nz, oc = o;
+    o -= g.nx * g.ny * g.nz;
+    for (unsigned C = threadIdx.x; C < nc; C += kCoarseThreads)
+      prolong_cell(C, sphi + o, g, sphi + oc, gc);
+    __syncthreads();
+    lds_smooth(sphi + o, sf + o, g, A.h2[l], kPost);
+  }
+  for (unsigned i = threadIdx.x; i < n0; i += kCoarseThreads) A.phi[i] = sphi[i];
 }
 
 // ---- g = -grad(phi) into the padded layout of a box covering the domain ----
@@ -424,6 +643,7 @@ struct Level {
   double h2, inv_h2;
   double* phi;
   double* f;
+  double* alt;  // a second phi array, free while the level is worked on
 };
 
 static int check_dom(const int32_t* dom) {
@@ -466,41 +686,66 @@ static size_t mg_bytes(const int32_t* dom) {
 }
 
 template <int MODE, int OP>
-static void reduce(const RhoSrc& R, const double* phi, const double* f, const Grid& g, double inv_h2,
-            unsigned nb, double* part, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_partial<MODE>, dim3(nb), dim3(kBlock), 0, s, R, phi, f, g, inv_h2, part);
+static void reduce(const RhoSrc& R, const double* phi, const double* f, const Grid& g,
+                   unsigned nb, double* part, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_partial<MODE>, dim3(nb), dim3(kBlock), 0, s, R, phi, f, g, part);
   hipLaunchKernelGGL(k_final<OP>, dim3(1), dim3(kBlock), 0, s, part, (int)nb, out);
 }
 
-constexpr int kPre = 2, kPost = 2, kCoarseSweeps = 32;
-
-// levels up to this many cells are smoothed by one workgroup
-constexpr size_t kSmallCells = 4096;
-
+// `iters` sweeps of a level's phi in place
 static hipError_t smooth(const Level& v, int iters, hipStream_t s) {
-  if (cells(v.g) <= kSmallCells) {
-    hipLaunchKernelGGL(k_rbgs_small, dim3(1), dim3(kBlock), 0, s, v.phi, v.f, v.g, v.h2, iters);
-    return hipGetLastError();
-  }
   const unsigned nb = blocks_for((unsigned long long)(v.g.nx / 2) * v.g.ny * v.g.nz);
   for (int it = 0; it < iters; ++it)
     for (unsigned color = 0; color < 2; ++color)
       hipLaunchKernelGGL(k_rbgs, dim3(nb), dim3(kBlock), 0, s, v.phi, v.f, v.g, v.h2, color);
   return hipGetLastError();
 }
+// two sweeps from src to dst
+static hipError_t smooth_tile(const Level& v, const double* src, double* dst, hipStream_t s) {
+  const unsigned tx = (v.g.nx + kTileOwn - 1) / kTileOwn, ty = (v.g.ny + kTileOwn - 1) / kTileOwn,
+                 tz = (v.g.nz + kTileOwn - 1) / kTileOwn;
+  hipLaunchKernelGGL(k_smooth_tile, dim3(tx * ty * tz), dim3(kTileThreads), 0, s, src, dst, v.f, v.g,
+                     tx, ty, v.h2);
+  return hipGetLastError();
+}
 
 static hipError_t vcycle(std::vector<Level>& L, size_t l, hipStream_t s) {
+  if (cells(L[l].g) <= kSmallCells) {
+    CoarseArgs A{};
+    A.nlev = (int)(L.size() - l);
+    for (int i = 0; i < A.nlev; ++i) {
+      A.g[i] = L[l + i].g;
+      A.h2[i] = L[l + i].h2;
+      A.inv_h2[i] = L[l + i].inv_h2;
+    }
+    A.phi = L[l].phi;
+    A.f = L[l].f;
+    hipLaunchKernelGGL(k_coarse, dim3(1), dim3(kCoarseThreads), 0, s, A);
+    return hipGetLastError();
+  }
   if (l + 1 == L.size()) return smooth(L[l], kCoarseSweeps, s);
-  hipError_t e = smooth(L[l], kPre, s);
-  if (e != hipSuccess) return e;
+  static_assert(kPre == 2 && kPost == 2, "the tiled smoother does two sweeps");
   const Level& f = L[l];
   Level& c = L[l + 1];
-  hipLaunchKernelGGL(k_restrict, dim3(blocks_for(cells(c.g))), dim3(kBlock), 0, s, f.phi, f.f,
-                     f.g, f.inv_h2, c.g, c.f, c.phi);
+  const bool tiled = cells(f.g) <= kTileCells;
+  double* u = tiled ? f.alt : f.phi;  // phi during the coarse correction
+  hipError_t e = tiled ? smooth_tile(f, f.phi, u, s) : smooth(f, kPre, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_restrict, dim3(blocks_for(cells(c.g))), dim3(kBlock), 0, s, u, f.f, f.g,
+                     f.inv_h2, c.g, c.f, c.phi);
   if ((e = vcycle(L, l + 1, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_prolong, dim3(blocks_for(cells(c.g))), dim3(kBlock), 0, s, f.phi, f.g,
-                     c.phi, c.g);
-  return smooth(f, kPost, s);
+  hipLaunchKernelGGL(k_prolong, dim3(blocks_for(cells(c.g))), dim3(kBlock), 0, s, u, f.g, c.phi,
+                     c.g);
+  return tiled ? smooth_tile(f, u, f.phi, s) : smooth(f, kPost, s);
+}
+
+// max |f - L phi| of a level into *out
+static void resid_max(const Level& v, double* part, double* out, hipStream_t s) {
+  const unsigned half = v.g.nx / 2;
+  const unsigned nb = std::min<unsigned>(kResidBlocks, blocks_for(cells(v.g) / 2));
+  hipLaunchKernelGGL(k_resid_max, dim3(nb), dim3(kBlock), 0, s, v.phi, v.f, v.g, make_fastdiv(half),
+                     make_fastdiv(v.g.ny), v.inv_h2, part);
+  hipLaunchKernelGGL(k_final<1>, dim3(1), dim3(kBlock), 0, s, part, (int)nb, out);
 }
 
 }  // namespace grav
@@ -581,10 +826,20 @@ int nyx_poisson_solve(const int32_t* dom, double dx, double coef, const double* 
     w += r256(cells(G[l]) * sizeof(double));
     h *= 2.0;
   }
+  // Second phi arrays for the tiled smoother: on the finest level the caller's
+  // phi, which after the right-hand side has been set up is not read before
+  // the end; the coarser levels' (together a seventh of its cells) lie in
+  // whichever of the finest level's two arrays is free while they are worked on.
+  L[0].alt = phi;
+  double* spare = cells(L[0].g) <= kTileCells ? L[0].phi : phi;
+  for (size_t l = 1; l < L.size(); ++l) {
+    L[l].alt = spare;
+    spare += cells(L[l].g);
+  }
   const Level& F = L[0];
   const unsigned nb = std::min<unsigned>(kRedBlocks, blocks_for(cells(F.g)));
   // right-hand side and its size
-  reduce<0, 0>(R, F.phi, F.f, F.g, F.inv_h2, nb, part, scal + 0, s);
+  reduce<0, 0>(R, F.phi, F.f, F.g, nb, part, scal + 0, s);
   hipLaunchKernelGGL(k_rhs, dim3(blocks_for(cells(F.g))), dim3(kBlock), 0, s, R, F.g, coef,
                      scal + 0, F.f, phi, F.phi);
   if (hipGetLastError() != hipSuccess) return NYX_E_HIP;
@@ -597,7 +852,7 @@ int nyx_poisson_solve(const int32_t* dom, double dx, double coef, const double* 
   };
   double fnorm = 0.0, rmax = 0.0, rel = 0.0;
   if (check) {
-    reduce<2, 1>(R, F.phi, F.f, F.g, F.inv_h2, nb, part, scal + 1, s);
+    reduce<2, 1>(R, F.phi, F.f, F.g, nb, part, scal + 1, s);
     if (!read(scal + 1, &fnorm)) return NYX_E_HIP;
   }
   int done = 0;
@@ -605,14 +860,14 @@ int nyx_poisson_solve(const int32_t* dom, double dx, double coef, const double* 
     if (vcycle(L, 0, s) != hipSuccess) return NYX_E_HIP;
     ++done;
     if (tol > 0.0 || (check && cyc + 1 == max_vcycles)) {
-      reduce<1, 1>(R, F.phi, F.f, F.g, F.inv_h2, nb, part, scal + 2, s);
+      resid_max(F, part, scal + 2, s);
       if (!read(scal + 2, &rmax)) return NYX_E_HIP;
       rel = fnorm > 0.0 ? rmax / fnorm : rmax;
       if (tol > 0.0 && rel <= tol) break;
     }
   }
   // the periodic problem fixes phi up to a constant: remove its mean
-  reduce<3, 0>(R, F.phi, F.f, F.g, F.inv_h2, nb, part, scal + 3, s);
+  reduce<3, 0>(R, F.phi, F.f, F.g, nb, part, scal + 3, s);
   hipLaunchKernelGGL(k_sub_mean, dim3(blocks_for(cells(F.g))), dim3(kBlock), 0, s, F.phi, F.g,
                      scal + 3, phi);
   if (hipGetLastError() != hipSuccess) return NYX_E_HIP;
