@@ -575,56 +575,110 @@ struct RiemannOut {
   int iters;
 };
 
-// Wave structure of a star state and its sample at x/t = 0 (O5, exact
-// divisions and square roots): a shock (p* >= p_K) is one front at
-// u_K -/+ W_K / rho_K; a rarefaction has its head at u_K -/+ c_K and its tail
-// at u* -/+ c*_K with linear interpolation between them; u* = 0 takes the
-// mean of both sides.
-__device__ __forceinline__ void sample_star(double gam, const double* qL, const double* qR,
-                                            double pstar, double ustar, double rsL, double rsR,
-                                            double WL, double WR, RiemannOut& o) {
-  const double rl = qL[0], ul = qL[1], pl = qL[4];
-  const double rr = qR[0], ur = qR[1], pr = qR[4];
-  const double cL = sqrt((gam * pl) / rl), cR = sqrt((gam * pr) / rr);
-  const double csL = sqrt((gam * pstar) / rsL), csR = sqrt((gam * pstar) / rsR);
-  double shdL, stlL, shdR, stlR;
-  if (pstar >= pl) { shdL = ul - WL / rl; stlL = shdL; }
-  else { shdL = ul - cL; stlL = ustar - csL; }
-  if (pstar >= pr) { shdR = ur + WR / rr; stlR = shdR; }
-  else { shdR = ur + cR; stlR = ustar + csR; }
-  double sL0, sL1, sL2, sR0, sR1, sR2;
-  if (shdL >= 0.0) { sL0 = rl; sL1 = ul; sL2 = pl; }
-  else if (stlL <= 0.0) { sL0 = rsL; sL1 = ustar; sL2 = pstar; }
-  else {
-    double f = (0.0 - shdL) / (stlL - shdL);
-    sL0 = rl + f * (rsL - rl);
-    sL1 = ul + f * (ustar - ul);
-    sL2 = pl + f * (pstar - pl);
+#if !defined(NYX_PREC_MIXED)
+// Correctly rounded division and square root without their range handling.
+// The compiler's expansions scale operands of extreme exponents, which no
+// operand here is where in_plain_range holds; without the scaling steps the
+// same reciprocal estimate, Newton steps and final correction remain, so the
+// result is the same bits: 8 instructions for 11 per division, 10 for 17 per
+// square root.  The FP64 Riemann kernels are bound by the vector units (and,
+// through their power, by the clock they run at), which makes a third of their
+// instructions divisions and square roots.
+struct PlainOps {
+  static __device__ __forceinline__ double div(double a, double b) {
+    double y = __builtin_amdgcn_rcp(b);
+    y = fma(y, fma(-b, y, 1.0), y);
+    y = fma(y, fma(-b, y, 1.0), y);
+    const double q = a * y;
+    return fma(fma(-b, q, a), y, q);
   }
-  if (shdR <= 0.0) { sR0 = rr; sR1 = ur; sR2 = pr; }
-  else if (stlR >= 0.0) { sR0 = rsR; sR1 = ustar; sR2 = pstar; }
-  else {
-    double f = (0.0 - shdR) / (stlR - shdR);
-    sR0 = rr + f * (rsR - rr);
-    sR1 = ur + f * (ustar - ur);
-    sR2 = pr + f * (pstar - pr);
+  static __device__ __forceinline__ double root(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double e = fma(-h, g, 0.5);
+    h = fma(h, e, h);
+    g = fma(g, e, g);
+    g = fma(fma(-g, g, x), h, g);
+    return fma(fma(-g, g, x), h, g);
   }
-  if (ustar > 0.0) {
-    o.r = sL0; o.u = sL1; o.p = sL2; o.v = qL[2]; o.w = qL[3];
-  } else if (ustar < 0.0) {
-    o.r = sR0; o.u = sR1; o.p = sR2; o.v = qR[2]; o.w = qR[3];
+};
+struct FullOps {
+  static __device__ __forceinline__ double div(double a, double b) { return a / b; }
+  static __device__ __forceinline__ double root(double x) { return sqrt(x); }
+};
+// densities and pressures of both states between 2^-100 and 2^100, normal
+// velocities 0 or likewise, and gamma away from 1: every product, quotient and
+// square root of the two-shock relations then stays between 2^-700 and 2^700
+// (or is 0), far from where a division or square root scales its operands
+__device__ __forceinline__ bool in_plain_range(double gamma, const double* qL, const double* qR) {
+  auto expo = [](double x) { return (unsigned)__double2hiint(x) & 0x7fffffffu; };
+  constexpr unsigned lo = (1023u - 100u) << 20, span = 200u << 20;
+  auto in = [&](unsigned h) { return h - lo < span; };
+  const unsigned ul = expo(qL[1]), ur = expo(qR[1]);
+  return gamma > 1.0 + 0x1p-20 && in(expo(qL[0])) && in(expo(qR[0])) && in(expo(qL[4])) &&
+         in(expo(qR[4])) && (in(ul) || ul == 0u) && (in(ur) || ur == 0u);
+}
+
+// Wave of one side of a star state and its sample at x/t = 0 (O5), written
+// for the left side; the right side's normal velocities are mirrored (u -> -u,
+// u* -> -u*), which negates every front speed and velocity exactly.  A shock
+// (p* >= p_K) is one front at u_K - W_K / rho_K; a rarefaction has its head at
+// u_K - c_K and its tail at u* - c*_K with linear interpolation between them.
+template <class OPS>
+__device__ __forceinline__ void sample_side(double gam, double r, double u, double pk, double W,
+                                            double rs, double us, double ps, double* out) {
+  double shd, stl;
+  if (ps >= pk) {
+    shd = u - OPS::div(W, r);
+    stl = shd;
   } else {
-    o.r = 0.5 * (sL0 + sR0);
-    o.u = 0.5 * (sL1 + sR1);
-    o.p = 0.5 * (sL2 + sR2);
+    shd = u - OPS::root(OPS::div(gam * pk, r));
+    stl = us - OPS::root(OPS::div(gam * ps, rs));
+  }
+  if (shd >= 0.0) {
+    out[0] = r; out[1] = u; out[2] = pk;
+  } else if (stl <= 0.0) {
+    out[0] = rs; out[1] = us; out[2] = ps;
+  } else {
+    const double f = (0.0 - shd) / (stl - shd);
+    out[0] = r + f * (rs - r);
+    out[1] = u + f * (us - u);
+    out[2] = pk + f * (ps - pk);
+  }
+}
+// Sample of a star state: the side the contact moves away from; u* = 0 takes
+// the mean of both sides.  star_density(side) gives rho*_K (side 0 left).
+template <class OPS, class RHO>
+__device__ __forceinline__ void sample_star(double gam, const double* qL, const double* qR,
+                                            double pstar, double ustar, double WL, double WR,
+                                            RHO star_density, RiemannOut& o) {
+  const bool one = ustar > 0.0 || ustar < 0.0;
+  const bool left = !(ustar < 0.0);
+  const double sg = left ? 1.0 : -1.0;
+  const double r = left ? qL[0] : qR[0], u = left ? qL[1] : qR[1], pk = left ? qL[4] : qR[4];
+  const double W = left ? WL : WR;
+  const double rs = star_density(r, pk, W);
+  double s1[3];
+  sample_side<OPS>(gam, r, sg * u, pk, W, rs, sg * ustar, pstar, s1);
+  o.r = s1[0];
+  o.u = sg * s1[1];
+  o.p = s1[2];
+  o.v = left ? qL[2] : qR[2];
+  o.w = left ? qL[3] : qR[3];
+  if (!one) {
+    double s2[3];
+    const double rsR = star_density(qR[0], qR[4], WR);
+    sample_side<OPS>(gam, qR[0], -qR[1], qR[4], WR, rsR, -ustar, pstar, s2);
+    o.r = 0.5 * (s1[0] + s2[0]);
+    o.u = 0.5 * (s1[1] + -s2[1]);
+    o.p = 0.5 * (s1[2] + s2[2]);
     o.v = 0.5 * (qL[2] + qR[2]);
     o.w = 0.5 * (qL[3] + qR[3]);
   }
   o.pstar = pstar;
   o.ustar = ustar;
-  o.rsL = rsL;
-  o.rsR = rsR;
 }
+#endif
 
 #if !defined(NYX_PREC_MIXED)
 // Linearised approximate solver (the alternative Sec. 3.2 compares the
@@ -649,7 +703,13 @@ __device__ __forceinline__ RiemannOut lin_solve(const StepArgs& A, const double*
   const double WL = sqrt(CL + (g2 * rl) * (p - pl));
   const double WR = sqrt(CR + (g2 * rr) * (p - pr));
   RiemannOut o;
-  sample_star(gam, qL, qR, p, ustar, rsL, rsR, WL, WR, o);
+  const double ps = p;
+  // rho*_K from the side's own values (the same expression as rsL, rsR)
+  sample_star<FullOps>(gam, qL, qR, p, ustar, WL, WR,
+                       [=](double r, double pk, double) { return r + (ps - pk) / ((gam * pk) / r); },
+                       o);
+  o.rsL = rsL;
+  o.rsR = rsR;
   o.iters = 0;
   return o;
 }
@@ -979,12 +1039,9 @@ __device__ __forceinline__ RiemannOut learned_solve(const StepArgs& A, const dou
 }
 #else
 
-// BOTH and RS are the mixed build's choices of star densities and of the
-// iteration's reciprocal square roots; this build always computes both
-// densities with correctly rounded arithmetic
-template <bool BOTH = true, int RS = 0>
-__device__ __forceinline__ RiemannOut two_shock(const StepArgs& A, const double* qL,
-                                                const double* qR) {
+template <bool BOTH, class OPS>
+__device__ __forceinline__ RiemannOut two_shock_ops(const StepArgs& A, const double* qL,
+                                                    const double* qR) {
   const double gam = A.gamma;
   const double g2 = 0.5 * (gam + 1.0);
   const double sp = A.small_pres;
@@ -992,39 +1049,51 @@ __device__ __forceinline__ RiemannOut two_shock(const StepArgs& A, const double*
   const double rr = qR[0], ur = qR[1], pr = qR[4];
   const double CL = (gam * pl) * rl;
   const double CR = (gam * pr) * rr;
-  const double W0L = sqrt(CL), W0R = sqrt(CR);
-  double p = ((W0R * pl + W0L * pr) + (W0L * W0R) * (ul - ur)) / (W0L + W0R);
+  const double W0L = OPS::root(CL), W0R = OPS::root(CR);
+  double p = OPS::div((W0R * pl + W0L * pr) + (W0L * W0R) * (ul - ur), W0L + W0R);
   p = vmax(p, sp);
   int it = 0;
   double WL, WR, usL, usR, ZL, ZR;
   while (it < A.maxiter) {
-    WL = sqrt(CL + (g2 * rl) * (p - pl));
-    WR = sqrt(CR + (g2 * rr) * (p - pr));
-    usL = ul - (p - pl) / WL;
-    usR = ur + (p - pr) / WR;
-    ZL = ((2.0 * WL) * WL) * WL / (WL * WL + CL);
-    ZR = ((2.0 * WR) * WR) * WR / (WR * WR + CR);
-    double pn = p - ((ZL * ZR) * (usR - usL)) / (ZL + ZR);
+    WL = OPS::root(CL + (g2 * rl) * (p - pl));
+    WR = OPS::root(CR + (g2 * rr) * (p - pr));
+    usL = ul - OPS::div(p - pl, WL);
+    usR = ur + OPS::div(p - pr, WR);
+    ZL = OPS::div(((2.0 * WL) * WL) * WL, WL * WL + CL);
+    ZR = OPS::div(((2.0 * WR) * WR) * WR, WR * WR + CR);
+    double pn = p - OPS::div((ZL * ZR) * (usR - usL), ZL + ZR);
     pn = vmax(pn, sp);
     ++it;
     bool conv = fabs(pn - p) <= A.riemann_tol * pn;
     p = pn;
     if (conv) break;
   }
-  WL = sqrt(CL + (g2 * rl) * (p - pl));
-  WR = sqrt(CR + (g2 * rr) * (p - pr));
-  usL = ul - (p - pl) / WL;
-  usR = ur + (p - pr) / WR;
-  ZL = ((2.0 * WL) * WL) * WL / (WL * WL + CL);
-  ZR = ((2.0 * WR) * WR) * WR / (WR * WR + CR);
-  const double ustar = (ZL * usL + ZR * usR) / (ZL + ZR);
+  WL = OPS::root(CL + (g2 * rl) * (p - pl));
+  WR = OPS::root(CR + (g2 * rr) * (p - pr));
+  usL = ul - OPS::div(p - pl, WL);
+  usR = ur + OPS::div(p - pr, WR);
+  ZL = OPS::div(((2.0 * WL) * WL) * WL, WL * WL + CL);
+  ZR = OPS::div(((2.0 * WR) * WR) * WR, WR * WR + CR);
+  const double ustar = OPS::div(ZL * usL + ZR * usR, ZL + ZR);
   const double pstar = p;
-  const double rsL = 1.0 / (1.0 / rl - (pstar - pl) / (WL * WL));
-  const double rsR = 1.0 / (1.0 / rr - (pstar - pr) / (WR * WR));
+  auto rho_star = [=](double r, double pk, double W) {
+    return OPS::div(1.0, OPS::div(1.0, r) - OPS::div(pstar - pk, W * W));
+  };
   RiemannOut o;
-  sample_star(gam, qL, qR, pstar, ustar, rsL, rsR, WL, WR, o);
+  sample_star<OPS>(gam, qL, qR, pstar, ustar, WL, WR, rho_star, o);
+  o.rsL = BOTH ? rho_star(rl, pl, WL) : 0.0;
+  o.rsR = BOTH ? rho_star(rr, pr, WR) : 0.0;
   o.iters = it;
   return o;
+}
+// BOTH: the star densities of both sides (training records); otherwise none is
+// returned.  RS is the mixed build's choice of the iteration's reciprocal
+// square roots.
+template <bool BOTH = false, int RS = 0>
+__device__ __forceinline__ RiemannOut two_shock(const StepArgs& A, const double* qL,
+                                                const double* qR) {
+  if (in_plain_range(A.gamma, qL, qR)) return two_shock_ops<BOTH, PlainOps>(A, qL, qR);
+  return two_shock_ops<BOTH, FullOps>(A, qL, qR);
 }
 #endif  // NYX_PREC_MIXED
 
