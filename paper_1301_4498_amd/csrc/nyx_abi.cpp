@@ -207,18 +207,23 @@ int step_one_box(const nyx_params* p, const nyx_box* box, const double* state_in
   BoxDev* tab = (BoxDev*)((char*)workspace + kOffTable);
   int* pre = (int*)((char*)workspace + kOffPrefix);
   StepC* cst = (StepC*)((char*)workspace + kOffConsts);
-  if (launch_prologue(A, 1, cst, tab, pre, s) != hipSuccess) return NYX_E_HIP;
+  // the first stage kernel sets these up for the others, with the running CFL
+  // maximum and the count of finished workgroups at zero
+  A.single_dst = tab;
+  A.prefix_dst = pre;
+  A.consts_dst = cst;
+  if (A.nblocks[kSpaceV] <= kDoneBlocks) A.done = (unsigned*)(A.smax + 1);
   A.table = tab;
   A.nb = 1;
   for (int k = 0; k < kSpaces; ++k) A.prefix[k] = pre + 2 * k;
   A.consts = cst;
-  // the running CFL maximum and the partial counters start from zero (fill
-  // kernels, so that a captured graph holds no memset node)
-  if (dt_next && launch_zero_u64(A.smax, 1, s) != hipSuccess) return NYX_E_HIP;
+  // the partial counters start from zero (a fill kernel, so that a captured
+  // graph holds no memset node); the first stage already counts
   if (stats && launch_zero_u64(A.slots, kStatSlots * kStatFields, s) != hipSuccess) return NYX_E_HIP;
   if (run_stages(p, A, s, timed) != hipSuccess) return NYX_E_HIP;
   if (stats && launch_stats_reduce(A.slots, stats, s) != hipSuccess) return NYX_E_HIP;
-  if (dt_next && launch_dt_finalize(A, a_new, p->cfl, dt_next, s) != hipSuccess) return NYX_E_HIP;
+  if (dt_next && !A.done && launch_dt_finalize(A, a_new, p->cfl, dt_next, s) != hipSuccess)
+    return NYX_E_HIP;
   return NYX_OK;
 }
 
@@ -386,6 +391,10 @@ namespace {
 
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
 
+static_assert(sizeof(unsigned long long) * (kCtlDone + 1) <= 1024 &&
+                  sizeof(unsigned long long) * kCtlWords > 768,
+              "the rounding of the control block leaves room for `done`");
+
 // bytes of the table region for a plan with `ngroups` groups
 size_t table_bytes(int nbox, int ngroups) {
   return round256(sizeof(BoxDev) * (size_t)nbox) +
@@ -514,7 +523,7 @@ int nyx_batch_create(const nyx_params* p, int nbox, const nyx_box* boxes, void* 
                      st) != hipSuccess ||
       hipMemcpyAsync(pre_dev, prefix.data(), sizeof(int) * prefix.size(), hipMemcpyHostToDevice,
                      st) != hipSuccess ||
-      launch_zero_u64(plan->ctl, kCtlWords, st) != hipSuccess ||  // no abort before any launch
+      launch_zero_u64(plan->ctl, kCtlWords + 1, st) != hipSuccess ||  // no abort before any launch
       hipStreamSynchronize(st) != hipSuccess) {
     delete plan;
     return NYX_E_HIP;
@@ -604,16 +613,24 @@ int enqueue_batched(nyx_batch* plan, const double* state_in, const void* grav, c
                     double a_old, double a_new, double* state_out, double* dt_next,
                     nyx_stats* stats, hipStream_t s, hipEvent_t* const* group_ev,
                     bool record = true) {
-  if (dt_next && launch_zero_u64(plan->smax, plan->nbox, s) != hipSuccess) return NYX_E_HIP;
-  if (stats && launch_zero_u64(plan->slots, kStatSlots * kStatFields, s) != hipSuccess)
-    return NYX_E_HIP;
+  const bool persistent = plan->mode == NYX_LAUNCH_PERSISTENT && !plan->harvest && !group_ev;
+  // dt_next from the final kernel's last workgroup: every group's grid small
+  // enough (the staged update's blocks, which outnumber the fused stage's
+  // tiles), and a final kernel there is (the persistent launch has none)
+  bool small = !persistent;
+  for (const auto& g : plan->groups)
+    small = small && g.nblocks[kSpaceV] <= kDoneBlocks && g.nblocks[kSpaceT] <= kDoneBlocks;
+  unsigned* done = small ? (unsigned*)(plan->ctl + kCtlDone) : nullptr;
   {
     StepArgs P = all_boxes_args(plan);
     P.dt_dev = dt;
     P.a_old = a_old;
     P.a_new = a_new;
-    if (launch_prologue(P, plan->nbox, plan->consts, nullptr, nullptr, s) != hipSuccess)
-      return NYX_E_HIP;
+    P.dt_next = dt_next;
+    P.stats = stats;
+    P.slots = plan->slots;
+    P.done = done;
+    if (launch_prologue(P, plan->nbox, plan->consts, s) != hipSuccess) return NYX_E_HIP;
   }
   for (const auto& g : plan->groups) {
     StepArgs A = group_args(plan, g);
@@ -625,6 +642,7 @@ int enqueue_batched(nyx_batch* plan, const double* state_in, const void* grav, c
     A.a_new = a_new;
     A.stats = stats;
     A.dt_next = dt_next;
+    A.done = done;
     // the fused kernels where the plan allows them (flux registers read the
     // final face states the fused final stage does not store; the fused
     // front stores everything the staged kernels do); the launch-order sweep
@@ -635,7 +653,7 @@ int enqueue_batched(nyx_batch* plan, const double* state_in, const void* grav, c
     if (group_ev) {
       A.ev = group_ev[&g - plan->groups.data()];
       e = plan->prm.precision == NYX_MIXED ? mixed::launch_step(A, s) : fp64::launch_step(A, s);
-    } else if (plan->mode == NYX_LAUNCH_PERSISTENT && !plan->harvest) {
+    } else if (persistent) {
       e = plan->prm.precision == NYX_MIXED ? mixed::launch_step_persistent(A, s)
                                            : fp64::launch_step_persistent(A, s);
     } else {
@@ -655,7 +673,7 @@ int enqueue_batched(nyx_batch* plan, const double* state_in, const void* grav, c
     }
   }
   if (stats && launch_stats_reduce(plan->slots, stats, s) != hipSuccess) return NYX_E_HIP;
-  if (dt_next &&
+  if (dt_next && !done &&
       launch_dt_finalize(all_boxes_args(plan), a_new, plan->prm.cfl, dt_next, s) != hipSuccess)
     return NYX_E_HIP;
   return NYX_OK;

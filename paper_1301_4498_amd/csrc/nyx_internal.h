@@ -332,6 +332,10 @@ constexpr int kCtlXcdBar = kStages * 8;
 constexpr int kCtlBarrier = kCtlXcdBar + kStages * 8;
 constexpr int kCtlAbort = kCtlBarrier + kStages;
 constexpr int kCtlWords = kCtlAbort + 1;
+constexpr int kCtlDone = kCtlWords;  // StepArgs::done of a plan, behind the block
+
+// Largest grid of the final kernel whose last workgroup writes dt_next.
+constexpr int kDoneBlocks = 1024;
 
 // Launch-wide arguments of a step.
 struct StepArgs {
@@ -362,6 +366,15 @@ struct StepArgs {
   double* dt_next;
   hipEvent_t* ev;          // kStages + 1 events recorded around the stages, or nullptr
   const StepC* consts;     // per-box step constants, indexed by gidx
+  // Single-box step: where the first kernel puts the box (`single`), its block
+  // prefixes and its constants for the kernels after it, or nullptr.
+  BoxDev* single_dst;
+  int* prefix_dst;
+  StepC* consts_dst;
+  // Workgroups of the final kernel that have finished (device, zero between
+  // launches): the last one then writes dt_next itself.  nullptr for larger
+  // grids, whose dt_next takes a launch of its own.
+  unsigned* done;
   // learned Riemann flux (FP32-mixed build only)
   const void* mlp;         // packed network, or nullptr
   int learned_mask;        // bit s: stage s (0, 1, 2) uses the network
@@ -426,6 +439,40 @@ struct SyncLevelView {
   long long nslots;
 };
 
+#ifdef __HIPCC__
+// Step constants of a box (built without contraction in every build: they are
+// the expressions the oracle evaluates).
+__device__ __forceinline__ StepC step_constants(const StepArgs& A, const BoxDev& b) {
+#pragma clang fp contract(off)
+  StepC c;
+  c.dt = A.dt_dev ? A.dt_dev[b.gidx] : A.dt_host;
+  c.gm1 = A.gamma - 1.0;
+  c.a_h = 0.5 * (A.a_old + A.a_new);
+  c.da = A.a_new - A.a_old;
+  c.kh = c.dt / (c.a_h * b.dx);
+  c.hdt_a = (0.5 * c.dt) / c.a_h;
+  c.hda_a = (0.5 * c.da) / c.a_h;
+  c.pexp = (1.5 * c.gm1) * (c.da / c.a_h);
+  c.kap1 = c.kh / 3.0;
+  c.kap2 = c.kh / 2.0;
+  c.k = c.dt / b.dx;
+  // a adot (2 - 3(gamma-1)) rho e = (adot / a) cgam U_e; integrated over the
+  // step at a_old (predictor) and a_new (corrector)
+  const double cgam = 2.0 - 3.0 * c.gm1;
+  c.xo = cgam * (c.da / A.a_old);
+  c.xn = cgam * (c.da / A.a_new);
+  c.khf = (float)c.kh;
+  c.hdt_af = (float)c.hdt_a;
+  c.hda_af = (float)c.hda_a;
+  c.pexpf = (float)c.pexp;
+  return c;
+}
+// dt = cfl a dx / s_max of a box (Sec. 3.5)
+__device__ __forceinline__ double dt_of_max(double cfl, double a, double dx, double smax) {
+  return ((cfl * a) * dx) / smax;
+}
+#endif
+
 // The two precision builds of the stage kernels.
 // launch_step_persistent: the seven stages of a group as one launch of
 // co-resident workgroups (NYX_E_UNSUPPORTED-worthy cases return
@@ -452,11 +499,10 @@ hipError_t launch_dt_finalize(const StepArgs& a, double a_state, double cfl, dou
                               hipStream_t s);
 hipError_t launch_min_dt(double* dt, int n, hipStream_t s);
 hipError_t launch_stats_reduce(const unsigned long long* slots, nyx_stats* stats, hipStream_t s);
-// Step prologue: per-box step constants of boxes [0, nbox) of `a.table` (or
-// of a.single when single_dst is given, which also receives a.single and the
-// one-box block prefixes).
-hipError_t launch_prologue(const StepArgs& a, int nbox, StepC* consts, BoxDev* single_dst,
-                           int* prefix_dst, hipStream_t s);
+// Prologue of a batched step: per-box step constants of boxes [0, nbox) of
+// `a.table`; clears the CFL maxima (with a.dt_next), the partial counters
+// (with a.stats) and the count of finished workgroups.
+hipError_t launch_prologue(const StepArgs& a, int nbox, StepC* consts, hipStream_t s);
 // learned flux (nyx_mlp.hip)
 hipError_t launch_mlp_init(float* P, unsigned long long seed, hipStream_t st);
 hipError_t launch_mlp_loss_grad(const float* P, const float* rec, long long n, double gamma,

@@ -211,12 +211,9 @@ __device__ __forceinline__ void ghost_source(const StepArgs& A, const BoxDev& b,
         (unsigned)(c[0] + sb->ng);
 }
 
-__device__ __forceinline__ void prim_body(const StepArgs& A, const Item& it) {
-  Loc L = locate(A, kStPrim, kSpaceP, it);
-  const BoxDev& b = *L.bd;
+__device__ __forceinline__ void prim_cell(const StepArgs& A, const BoxDev& b, unsigned id) {
   unsigned floors = 0;
-  if (L.idx < b.P) {
-    const unsigned id = L.idx;
+  if (id < b.P) {
     const double* U = A.Uin + b.soff;
     long long ss = b.sstride;
     unsigned sid = id;  // the cell read for padded cell id
@@ -242,7 +239,28 @@ __device__ __forceinline__ void prim_body(const StepArgs& A, const Item& it) {
   }
   if (A.stats) count(A, kFloorHits, floors);
 }
+__device__ __forceinline__ void prim_body(const StepArgs& A, const Item& it) {
+  const Loc L = locate(A, kStPrim, kSpaceP, it);
+  prim_cell(A, *L.bd, L.idx);
+}
 __global__ __launch_bounds__(kBlock) void k_prim(StepArgs A) { prim_body(A, launch_item(A, kStPrim)); }
+// The first kernel of a single-box step: reads the box from its arguments and
+// leaves it, its constants and the cleared maximum for the kernels after it (a
+// prologue and two clearing launches, 3 us each, less).
+__global__ __launch_bounds__(kBlock) void k_prim_single(StepArgs A) {
+  const unsigned lin = xcd_linear_block(true);
+  if (lin == 0 && threadIdx.x == 0) {
+    *A.single_dst = A.single;
+    for (int s = 0; s < kSpaces; ++s) {
+      A.prefix_dst[2 * s] = 0;
+      A.prefix_dst[2 * s + 1] = A.nblocks[s];
+    }
+    *A.consts_dst = step_constants(A, A.single);
+    *A.smax = 0ull;
+    if (A.done) *A.done = 0u;
+  }
+  prim_cell(A, A.single, lin * (unsigned)kBlock + threadIdx.x);
+}
 
 // padded index of the cell at E-array coordinates (ie, je, ke) (cell ie - 1)
 __device__ __forceinline__ unsigned pidx_e(const BoxDev& b, int ie, int je, int ke) {
@@ -1823,6 +1841,34 @@ __device__ __forceinline__ void block_max_atomic(double s, unsigned long long* d
   __syncthreads();  // red is free again when the block's next item reduces
 }
 
+// The last workgroup of the final kernel to finish turns every box's maximum
+// into its next time step and clears the count for the next launch: one launch
+// of 4 us less per step, for grids of at most kDoneBlocks workgroups (they all
+// count on one address, 4 ns each).  A workgroup's maximum was raised by an
+// atomic of its first thread, which is complete (waited for) before the same
+// thread counts; both act on memory, so no cache has to be written back, as a
+// device-wide fence would do for every workgroup (350 us on a 128^3 box).
+// Every thread of the workgroup calls this.
+template <int NT = kBlock>
+__device__ __forceinline__ void finish_dt(const StepArgs& A) {
+  if (!A.dt_next || !A.done) return;
+  __shared__ int last;
+  if (threadIdx.x == 0) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    last = __hip_atomic_fetch_add(A.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+           gridDim.x * gridDim.y;
+    if (last) __hip_atomic_store(A.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!last) return;
+  for (int i = (int)threadIdx.x; i < A.nb; i += NT) {
+    const BoxDev& b = A.table[i];
+    const unsigned long long m =
+        __hip_atomic_load(A.smax + b.gidx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    A.dt_next[b.gidx] = dt_of_max(A.cfl, A.a_new, b.dx, __longlong_as_double((long long)m));
+  }
+}
+
 // ---------------------------------------------------------------------------
 // stage 7: conservative update, gravity corrector, dual-energy sync
 // ---------------------------------------------------------------------------
@@ -1988,6 +2034,7 @@ __device__ __forceinline__ void update_body(const StepArgs& A, const Item& it) {
 }
 __global__ __launch_bounds__(kBlock) void k_update(StepArgs A) {
   update_body(A, launch_item(A, kStUpdate));
+  finish_dt(A);
 }
 
 // ---------------------------------------------------------------------------
@@ -2151,6 +2198,7 @@ __global__ __launch_bounds__(kFinBlock, kFinWaves) void k_final(StepArgs A) {
   }
   count_cells<kFinBlock>(A, n);
   if (A.dt_next) block_max_atomic<kFinBlock>(smax, A.smax + b.gidx);
+  finish_dt<kFinBlock>(A);
 }
 
 // ---------------------------------------------------------------------------
@@ -2207,7 +2255,8 @@ hipError_t launch_step(const StepArgs& a, hipStream_t s) {
   };
   auto learned = [&](int stage) { return kHasLearned && a.mlp && (a.learned_mask >> stage & 1); };
   mark(0);
-  hipLaunchKernelGGL(k_prim, dim3(a.nblocks[kSpaceP]), blk, 0, s, a);
+  if (a.single_dst) hipLaunchKernelGGL(k_prim_single, dim3(a.nblocks[kSpaceP]), blk, 0, s, a);
+  else hipLaunchKernelGGL(k_prim, dim3(a.nblocks[kSpaceP]), blk, 0, s, a);
   mark(1);
   hipLaunchKernelGGL(k_flat, dim3(a.nblocks[kSpaceE]), blk, 0, s, a);
   mark(2);

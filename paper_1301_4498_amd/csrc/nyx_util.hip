@@ -81,7 +81,7 @@ __global__ void k_dt_finalize(StepArgs A, double a, double cfl, double* dt, int 
   if (i >= nbox) return;
   const BoxDev& b = A.table ? A.table[i] : A.single;
   double smax = __longlong_as_double((long long)A.smax[b.gidx]);
-  dt[b.gidx] = ((cfl * a) * b.dx) / smax;
+  dt[b.gidx] = dt_of_max(cfl, a, b.dx, smax);
 }
 
 hipError_t launch_dt_finalize(const StepArgs& a, double a_state, double cfl, double* dt_out,
@@ -92,46 +92,20 @@ hipError_t launch_dt_finalize(const StepArgs& a, double a_state, double cfl, dou
   return hipGetLastError();
 }
 
-__global__ void k_prologue(StepArgs A, int nbox, StepC* consts, BoxDev* single_dst,
-                           int* prefix_dst) {
+__global__ void k_prologue(StepArgs A, int nbox, StepC* consts) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nbox) return;
-  const BoxDev& b = single_dst ? A.single : A.table[i];
-  if (single_dst && i == 0) {
-    *single_dst = A.single;
-    for (int s = 0; s < kSpaces; ++s) {
-      prefix_dst[2 * s] = 0;
-      prefix_dst[2 * s + 1] = A.nblocks[s];
-    }
+  if (i < nbox) {
+    const BoxDev& b = A.table[i];
+    consts[b.gidx] = step_constants(A, b);
+    if (A.dt_next) A.smax[b.gidx] = 0ull;
   }
-  StepC c;
-  c.dt = A.dt_dev ? A.dt_dev[b.gidx] : A.dt_host;
-  c.gm1 = A.gamma - 1.0;
-  c.a_h = 0.5 * (A.a_old + A.a_new);
-  c.da = A.a_new - A.a_old;
-  c.kh = c.dt / (c.a_h * b.dx);
-  c.hdt_a = (0.5 * c.dt) / c.a_h;
-  c.hda_a = (0.5 * c.da) / c.a_h;
-  c.pexp = (1.5 * c.gm1) * (c.da / c.a_h);
-  c.kap1 = c.kh / 3.0;
-  c.kap2 = c.kh / 2.0;
-  c.k = c.dt / b.dx;
-  // a adot (2 - 3(gamma-1)) rho e = (adot / a) cgam U_e; integrated over the
-  // step at a_old (predictor) and a_new (corrector)
-  const double cgam = 2.0 - 3.0 * c.gm1;
-  c.xo = cgam * (c.da / A.a_old);
-  c.xn = cgam * (c.da / A.a_new);
-  c.khf = (float)c.kh;
-  c.hdt_af = (float)c.hdt_a;
-  c.hda_af = (float)c.hda_a;
-  c.pexpf = (float)c.pexp;
-  consts[b.gidx] = c;
+  if (A.stats)
+    for (int k = i; k < kStatSlots * kStatFields; k += gridDim.x * blockDim.x) A.slots[k] = 0ull;
+  if (A.done && i == 0) *A.done = 0u;
 }
 
-hipError_t launch_prologue(const StepArgs& a, int nbox, StepC* consts, BoxDev* single_dst,
-                           int* prefix_dst, hipStream_t s) {
-  hipLaunchKernelGGL(k_prologue, dim3((nbox + 63) / 64), dim3(64), 0, s, a, nbox, consts, single_dst,
-                     prefix_dst);
+hipError_t launch_prologue(const StepArgs& a, int nbox, StepC* consts, hipStream_t s) {
+  hipLaunchKernelGGL(k_prologue, dim3((nbox + 63) / 64), dim3(64), 0, s, a, nbox, consts);
   return hipGetLastError();
 }
 
