@@ -1511,10 +1511,11 @@ __global__ __launch_bounds__(kBlock) void k_front(StepArgs A) {
 // by stage-0 t-fluxes (t = t1 and t = t2), Riemann -> F^{d|t1}, F^{d|t2}.
 // Both pairs share the loads of the d-states.
 // ---------------------------------------------------------------------------
-// Learned form: grid.y = 6, one (direction, pair K) per thread (fewer live
-// registers next to the network's accumulators).  The plain form takes both
+// One (direction, pair K) per thread, grid.y = 6: the learned form (fewer live
+// registers next to the network's accumulators), and the plain form of grids
+// that leave the chip idle (kPairBlocks).  Otherwise the plain form takes both
 // pairs of a direction per thread (riem1_both below).
-template <int D, int K>
+template <bool LEARNED, int D, int K>
 __device__ __forceinline__ void riem1_pair(const StepArgs& A, const BoxDev& box, unsigned idx,
                                            __bf16* lds, Tally& T) {
   const BoxDev& b = scalar_ref(box);
@@ -1547,7 +1548,7 @@ __device__ __forceinline__ void riem1_pair(const StepArgs& A, const BoxDev& box,
     rotate(d, qs[0], ql);
     rotate(d, qs[1], qr);
   }
-  RiemannOut g = solve<true>(A, active, ql, qr, lds, &T.used, &T.fb);
+  RiemannOut g = solve<LEARNED>(A, active, ql, qr, lds, &T.used, &T.fb);
   if (active) {
     T.calls += 1;
     T.iters += g.iters;
@@ -1624,7 +1625,7 @@ __device__ __forceinline__ void riem1_both(const StepArgs& A, const BoxDev& box,
 }
 
 // park: kPark x kBlock doubles (plain form); mlp_lds as in riem0_body
-template <bool LEARNED>
+template <bool LEARNED, bool PAIRS = LEARNED>
 __device__ __forceinline__ void riem1_body(const StepArgs& A, const Item& it, __bf16* mlp_lds,
                                            double* park) {
   int y;
@@ -1632,14 +1633,14 @@ __device__ __forceinline__ void riem1_body(const StepArgs& A, const Item& it, __
   const BoxDev& b = *L.bd;
   __bf16* lds = mlp_lds + (threadIdx.x >> 6) * kMlpWaveLds * LEARNED;
   Tally T;
-  if constexpr (LEARNED) {
+  if constexpr (PAIRS) {
     switch (y) {
-      case 0: riem1_pair<0, 0>(A, b, L.idx, lds, T); break;
-      case 1: riem1_pair<0, 1>(A, b, L.idx, lds, T); break;
-      case 2: riem1_pair<1, 0>(A, b, L.idx, lds, T); break;
-      case 3: riem1_pair<1, 1>(A, b, L.idx, lds, T); break;
-      case 4: riem1_pair<2, 0>(A, b, L.idx, lds, T); break;
-      default: riem1_pair<2, 1>(A, b, L.idx, lds, T); break;
+      case 0: riem1_pair<LEARNED, 0, 0>(A, b, L.idx, lds, T); break;
+      case 1: riem1_pair<LEARNED, 0, 1>(A, b, L.idx, lds, T); break;
+      case 2: riem1_pair<LEARNED, 1, 0>(A, b, L.idx, lds, T); break;
+      case 3: riem1_pair<LEARNED, 1, 1>(A, b, L.idx, lds, T); break;
+      case 4: riem1_pair<LEARNED, 2, 0>(A, b, L.idx, lds, T); break;
+      default: riem1_pair<LEARNED, 2, 1>(A, b, L.idx, lds, T); break;
     }
   } else {
     if (y == 0) riem1_both<0>(A, b, L.idx, park, T);
@@ -1648,12 +1649,17 @@ __device__ __forceinline__ void riem1_body(const StepArgs& A, const Item& it, __
   }
   count_tally<LEARNED>(A, T, true);
 }
-template <bool LEARNED>
+template <bool LEARNED, bool PAIRS = LEARNED>
 __global__ __launch_bounds__(kBlock) void k_riem1(StepArgs A) {
   __shared__ __bf16 mlp_lds[LEARNED ? (kBlock / 64) * kMlpWaveLds : 1];
-  __shared__ double park[LEARNED ? 1 : kPark * kBlock];
-  riem1_body<LEARNED>(A, launch_item(A, kStRiem1), mlp_lds, park);
+  __shared__ double park[PAIRS ? 1 : kPark * kBlock];
+  riem1_body<LEARNED, PAIRS>(A, launch_item(A, kStRiem1), mlp_lds, park);
 }
+// Largest grid row of the plain form with one pair per thread.  With both
+// pairs per thread such a grid has at most kPairBlocks x 3 x 4 wavefronts,
+// three per SIMD, and takes the latency of two solves one after the other;
+// split, it takes one.
+constexpr int kPairBlocks = 256;
 
 // 32-bit hash of a face for the training-sample harvest
 __device__ __forceinline__ unsigned face_hash(unsigned long long seed, int box, long long e, int d) {
@@ -2278,6 +2284,8 @@ hipError_t launch_step(const StepArgs& a, hipStream_t s) {
   }
   mark(4);
   if (learned(1)) hipLaunchKernelGGL(k_riem1<kHasLearned>, dim3(a.nblocks[kSpaceE], 6), blk, 0, s, a);
+  else if (a.nblocks[kSpaceE] <= kPairBlocks)
+    hipLaunchKernelGGL((k_riem1<false, true>), dim3(a.nblocks[kSpaceE], 6), blk, 0, s, a);
   else hipLaunchKernelGGL(k_riem1<false>, dim3(a.nblocks[kSpaceE], 3), blk, 0, s, a);
   mark(5);
   if (a.fuse_final && !learned(2) && !a.harvest) {

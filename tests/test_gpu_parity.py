@@ -163,3 +163,37 @@ def test_floor_and_negative_density_are_counted(nyx):
         assert st[0][key] == v, key
     assert np.array_equal(U[:, NG:-NG, NG:-NG, NG:-NG], U_ref[:, NG:-NG, NG:-NG, NG:-NG],
                           equal_nan=True)
+
+
+@pytest.mark.parametrize("n", [(38, 38, 38), (40, 38, 38), (64, 64, 64), (66, 64, 64)])
+def test_fp64_step_at_launch_rule_edges(nyx, n):
+    """Boxes on either side of the sizes at which the step changes its
+    launches: the transverse stage with one or two solves per thread (256
+    blocks of the cells [-1, n]), the next dt from the last workgroup of the
+    update or from a launch of its own (1024 blocks of valid cells)."""
+    a0, a1, dx = 0.5, 0.5025, 1.0 / 64
+    U, g = synth.random_box(n, seed=n[0], a=a0)
+    dt = oracle.estimate_dt(U, NG, a0, dx, 0.5)
+    ref, _ = oracle.hydro_step(U, g, NG, dt, dx, a0, a1)
+    got, dt_next, _ = gpu_run(U, g, n, dx, [a0, a1], [dt], nyx.default_params(), periodic=False)
+    assert np.array_equal(got[:, NG:-NG, NG:-NG, NG:-NG], ref[:, NG:-NG, NG:-NG, NG:-NG])
+    assert dt_next[0] == oracle.estimate_dt(ref, NG, a1, dx, 0.5)
+
+
+@pytest.mark.parametrize("lo,hi", [(1e-33, 1e-33), (1e33, 1e33), (1e-33, 1.0), (1e-33, 1e33)])
+def test_fp64_step_out_of_ordinary_range(nyx, lo, hi):
+    """Densities and pressures below 2^-100 or above 2^100, whole boxes of
+    them or every second column: faces that take the Riemann solver's general
+    divisions and square roots, alone and beside ordinary ones in a wavefront;
+    bit for bit the oracle's step."""
+    n, a0, a1, dx = (14, 10, 12), 0.5, 0.5025, 1.0 / 16
+    U, g = synth.random_box(n, seed=31, a=a0)
+    scale = np.where(np.arange(U.shape[3]) % 2 == 0, lo, hi)
+    U = np.ascontiguousarray(U * scale)
+    par = oracle.Params(small_dens=1e-60, small_pres=1e-60)
+    prm = nyx.default_params(small_dens=1e-60, small_pres=1e-60)
+    dt = 0.2 * oracle.estimate_dt(U, NG, a0, dx, 0.5, par)
+    ref, st = oracle.hydro_step(U, g, NG, dt, dx, a0, a1, par)
+    got, _, gst = gpu_run(U, g, n, dx, [a0, a1], [dt], prm, periodic=False)
+    assert np.array_equal(got[:, NG:-NG, NG:-NG, NG:-NG], ref[:, NG:-NG, NG:-NG, NG:-NG])
+    assert gst[0]["riemann_iters"] == st["riemann_iters"]
