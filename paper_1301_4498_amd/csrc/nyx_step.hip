@@ -1012,12 +1012,21 @@ __device__ __forceinline__ RiemannOut lin_solve(const StepArgs& A, const double*
 // true where the stopping step lies far enough above the raw estimates'
 // error for the iteration to use them (see ts_iterate)
 __host__ __device__ __forceinline__ bool raw_stop(const StepArgs& A) { return A.mixed_stop >= 0x1p-20; }
+// The step is written on the velocity jump itself,
+//   u*_R - u*_L = (u_R - u_L) + (p - p_R) w_R + (p - p_L) w_L,
+// and on the slopes' weighted sum, 20 vector instructions an iteration.
 template <bool RAW>
 __device__ __forceinline__ double ts_iterate(const StepArgs& A, const TwoShock& t, double p,
                                              int& it) {
+  const double du = t.ur - t.ul;
   while (it < A.maxiter) {
-    const TwoShockEval e = RAW ? ts_eval_est(t, p) : ts_eval(t, p);
-    const double pn = ts_newton(t, e, p);
+    const double dl = p - t.pl, dr = p - t.pr;
+    const double XL = t.CL + t.gl * dl, XR = t.CR + t.gr * dr;
+    const double wL = RAW ? rsq_est(XL) : rsq64(XL), wR = RAW ? rsq_est(XR) : rsq64(XR);
+    const double jump = fma(dl, wL, fma(dr, wR, du));
+    const double slope = fma(0.5 + t.hCL * (wL * wL), wL, (0.5 + t.hCR * (wR * wR)) * wR);
+    // fmax is the floor max(p', small_pres): small_pres is never NaN
+    const double pn = fmax(fma(-jump, rcp_est(slope), p), t.sp);
     ++it;
     const bool conv = fabs(pn - p) <= A.mixed_stop * pn;
     p = pn;
@@ -1296,14 +1305,23 @@ __device__ __forceinline__ bool trans_correct(const StepArgs& A, const double* q
   for (int d = 0; d < 3; ++d) r[1 + d] = vel[d];
 #endif
   r[4] = pn;
-  bool ok = (r[0] > 0.0) && (r[4] > 0.0);
-  for (int c = 0; c < 5; ++c) ok = ok && isfinite(r[c]);
-  if (!ok) {
-    for (int c = 0; c < 5; ++c) out[c] = q[c];
-    return true;
-  }
+  // density and pressure positive and finite, velocities finite.  In the mixed
+  // build the momenta come from FP32 values, so a finite kinetic energy says
+  // that they and the density's reciprocal are.
+  constexpr int kPositive = 0x180, kFinite = 0x1f8;  // classes: normal and denormal (and 0)
+  bool ok = __builtin_amdgcn_class(r[0], kPositive) && __builtin_amdgcn_class(r[4], kPositive);
+#if defined(NYX_PREC_MIXED)
+  ok = ok && __builtin_amdgcn_class(ke, kFinite);
+#else
+  for (int d = 0; d < 3; ++d) ok = ok && __builtin_amdgcn_class(vel[d], kFinite);
+#endif
   for (int c = 0; c < 5; ++c) out[c] = r[c];
-  return false;
+  if (__builtin_expect(!ok, 0)) {
+    // rare: a branch of its own instead of ten selects per state
+    asm volatile("");
+    for (int c = 0; c < 5; ++c) out[c] = q[c];
+  }
+  return !ok;
 }
 
 __device__ __forceinline__ int pair_index(int d, int t) { return d * 2 + (t == (d + 1) % 3 ? 0 : 1); }
