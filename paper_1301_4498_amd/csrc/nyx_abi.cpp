@@ -80,12 +80,17 @@ size_t real_bytes(const nyx_params* p) { return p->precision == NYX_MIXED ? 4 : 
 
 long long blocks_for(long long n) { return (n + kBlock - 1) / kBlock; }
 
+// lanes of a box's flattening and tracing tiles over all their planes
+long long edge_slots(const BoxDev& b) {
+  return (long long)b.etiles * b.etz * kEdgeBlock;
+}
+
 void set_blocks(const BoxDev& b, int* nb) {
   nb[kSpaceP] = (int)blocks_for(b.P);
   nb[kSpaceE] = (int)blocks_for(b.E);
   nb[kSpaceV] = (int)blocks_for(b.V);
   nb[kSpaceT] = b.ntiles;
-  nb[kSpaceF] = b.fbx;
+  nb[kSpaceF] = b.etiles;
 }
 
 // [a0, a0 + alen) and [b0, b0 + blen) in bytes
@@ -189,8 +194,9 @@ int step_one_box(const nyx_params* p, const nyx_box* box, const double* state_in
                  double* dt_next, nyx_stats* stats, void* workspace, hipStream_t s,
                  bool timed) {
   StepArgs A{};
-  box_layout(*box, 0, 0, &A.single);
+  box_layout(*box, 0, 0, &A.single, kFinPlanes, edge_planes(1, box));
   set_blocks(A.single, A.nblocks);
+  A.edges = p->precision == NYX_MIXED && edges_pay(A.single.E, edge_slots(A.single)) ? 1 : 0;
   fill_physics(A, p);
   A.Uin = state_in;
   A.Uout = state_out;
@@ -358,6 +364,7 @@ struct nyx_batch {
     int b0, b1;
     int nblocks[kSpaces];
     const int* prefix[kSpaces];  // device
+    bool edges;                  // flattening and tracing in one pass
   };
   std::vector<Group> groups;
   BoxDev* table;                 // device, nbox entries in box order
@@ -454,7 +461,7 @@ int nyx_batch_create(const nyx_params* p, int nbox, const nyx_box* boxes, void* 
   plan->boxes.assign(boxes, boxes + nbox);
   std::vector<BoxDev> host(nbox);
   std::vector<int> prefix;
-  const int planes = fin_planes(nbox, boxes);
+  const int planes = fin_planes(nbox, boxes), eplanes = edge_planes(nbox, boxes);
   long long used = 0;
   int g0 = 0;
   size_t span = 0;
@@ -481,7 +488,7 @@ int nyx_batch_create(const nyx_params* p, int nbox, const nyx_box* boxes, void* 
             continue;
           }
           if (s == kSpaceF) {
-            acc += host[b].fbx;
+            acc += host[b].etiles;
             continue;
           }
           long long cnt = s == kSpaceP ? host[b].P : (s == kSpaceE ? host[b].E : host[b].V);
@@ -490,12 +497,18 @@ int nyx_batch_create(const nyx_params* p, int nbox, const nyx_box* boxes, void* 
         prefix.push_back(acc);
         g.nblocks[s] = acc;
       }
+      long long cells = 0, slots = 0;
+      for (int b = g0; b < i; ++b) {
+        cells += host[b].E;
+        slots += edge_slots(host[b]);
+      }
+      g.edges = p->precision == NYX_MIXED && edges_pay(cells, slots);
       if (i > g0) plan->groups.push_back(g);
       g0 = i;
       used = 0;
       if (i == nbox) break;
     }
-    used = box_layout(boxes[i], i, used, &host[i], planes);
+    used = box_layout(boxes[i], i, used, &host[i], planes, eplanes);
   }
   char* w = (char*)workspace;
   plan->table = (BoxDev*)w;
@@ -643,12 +656,11 @@ int enqueue_batched(nyx_batch* plan, const double* state_in, const void* grav, c
     A.stats = stats;
     A.dt_next = dt_next;
     A.done = done;
-    // the fused kernels where the plan allows them (flux registers read the
-    // final face states the fused final stage does not store; the fused
-    // front stores everything the staged kernels do); the launch-order sweep
-    // times the staged kernels
+    // the fused final stage where the plan allows it (flux registers read the
+    // final face states it does not store), one pass for the edges where it
+    // pays; the launch-order sweep times the staged kernels
     A.fuse_final = plan->mode == NYX_LAUNCH_FUSED && !plan->reg && !group_ev ? 1 : 0;
-    A.fuse_front = plan->mode == NYX_LAUNCH_FUSED && !group_ev ? 1 : 0;
+    A.edges = g.edges && !group_ev ? 1 : 0;
     hipError_t e;
     if (group_ev) {
       A.ev = group_ev[&g - plan->groups.data()];

@@ -21,10 +21,30 @@ constexpr int kFinPlanes = 64, kFinMinPlanes = 8;
 // (a face in 3.2 per cell and plane), so chunks are cut only while the launch
 // has fewer tiles than this.
 constexpr long long kFinTiles = 2048;
-// Fused front (tracing and stage-0 solves of x in one kernel): a wavefront
-// holds 64 consecutive cells of the [-1, n]^3 range, the first of them the
-// last of the previous wavefront, so a block owns kFrontOwn cells.
-constexpr int kFrontOwn = kBlock / 64 * 63;
+// Threads per workgroup of the flattening and tracing pass (k_edges): a tile of
+// at most kEdgeBlock cell columns of the [-1, n]^3 range, whose planes with a
+// halo of three cells have at most kEdgeLds cells, over a chunk of planes in
+// z.  Tiles span a box of up to kEdgeWide columns in x whole (the 66 of a 64^3
+// patch), so that rows are loaded and stored whole.  Chunks are cut down to
+// kEdgeMinPlanes while the launch has fewer than kEdgeWant tiles (256^3, 5
+// chunks of 52 planes against 33 of 8: 5050 and 4915 us a step).
+constexpr int kEdgeBlock = 512;
+constexpr int kEdgeLds = 1100;
+constexpr int kEdgeWide = 72;
+constexpr int kEdgePlanes = 64, kEdgeMinPlanes = 8;
+constexpr long long kEdgeWant = 4096;
+// Whether an FP32 launch over `cells` cells, whose tiles have `slots` lanes in
+// all planes together, takes the pass.  It has to fill the chip several times
+// over, as each workgroup marches up its planes, and a third of its lanes have
+// to have a cell.  Step in us, separate kernels against the pass: 64^3 168 and
+// 189, 96^3 379 and 389, 112^3 522 and 509, 160^3 1377 and 1323, 256^3 5215 and
+// 4915; 3000 boxes of 8^3 (20% of the lanes) 1394 and 1450, 900 of 12^3 (38%)
+// 962 and 933, 256 of 16^3 536 and 510, 64 of 64^3 5610 and 5200.  In FP64 the
+// pass needs 228 registers, two wavefronts a SIMD, and loses: 256 boxes of 16^3
+// 1204 and 1240 us, 128^3 1631 and 1652.
+inline bool edges_pay(long long cells, long long slots) {
+  return cells >= 5 * (1ll << 18) && 3 * cells >= slots;
+}
 // Stored per face: the Godunov state (rho_g, u_g normal, v_g, w_g transverse,
 // p_g) in the face's rotated frame; every flux is recomputed from it.
 constexpr int kGod = 5;
@@ -64,7 +84,8 @@ struct BoxDev {
   unsigned sc[3];          // per Space: cell count (< 2^31)
   int tx, ty, ntx, nty;    // fused final stage: tile shape, tiles along x and y,
   int ntiles, tz;          // tiles in all (z chunks included), planes per chunk
-  int fbx, pad3_;          // fused front: blocks of kFrontOwn cells
+  int etx, ety, entx, enty;  // flattening and tracing pass: tile shape, tiles along x and y,
+  int etiles, etz;         // tiles in all (z chunks included), planes per chunk
 };
 
 // Stage-array element count for a box (before alignment padding).
@@ -99,10 +120,41 @@ inline int fin_planes(int nbox, const nyx_box* boxes) {
   return kFinMinPlanes;
 }
 
+// The same for the flattening and tracing pass (cells [-1, n]).
+typedef FinTiling EdgeTiling;
+inline EdgeTiling edge_tiling(const nyx_box& b, int planes) {
+  const int ex = b.n[0] + 2, ey = b.n[1] + 2, ez = b.n[2] + 2;
+  EdgeTiling t;
+  t.ntx = (ex + kEdgeWide - 1) / kEdgeWide;
+  t.tx = (ex + t.ntx - 1) / t.ntx;
+  int ty = kEdgeBlock / t.tx;
+  const int lds = kEdgeLds / (t.tx + 6) - 6;
+  ty = ty < lds ? ty : lds;
+  t.nty = (ey + ty - 1) / ty;
+  t.ty = (ey + t.nty - 1) / t.nty;
+  t.ntz = (ez + planes - 1) / planes;
+  t.tz = (ez + t.ntz - 1) / t.ntz;
+  return t;
+}
+inline long long edge_tiles(int nbox, const nyx_box* boxes, int planes) {
+  long long n = 0;
+  for (int i = 0; i < nbox; ++i) {
+    const EdgeTiling t = edge_tiling(boxes[i], planes);
+    n += (long long)t.ntx * t.nty * t.ntz;
+  }
+  return n;
+}
+// Planes per chunk: the longest chunk that gives the launch kFinTiles tiles.
+inline int edge_planes(int nbox, const nyx_box* boxes) {
+  int planes = kEdgePlanes;
+  while (planes > kEdgeMinPlanes && edge_tiles(nbox, boxes, planes) < kEdgeWant) planes /= 2;
+  return planes;
+}
+
 // Fill the derived fields and stage offsets of a box starting at `base`;
 // returns the element offset just past its stage arrays.
 inline long long box_layout(const nyx_box& b, int gidx, long long base, BoxDev* out,
-                            int planes = kFinPlanes) {
+                            int planes = kFinPlanes, int eplanes = kEdgePlanes) {
   BoxDev d{};
   for (int i = 0; i < 3; ++i) d.n[i] = b.n[i];
   d.ng = b.ng;
@@ -150,7 +202,13 @@ inline long long box_layout(const nyx_box& b, int gidx, long long base, BoxDev* 
   d.nty = t.nty;
   d.tz = t.tz;
   d.ntiles = t.ntx * t.nty * t.ntz;
-  d.fbx = (int)((d.E + kFrontOwn - 1) / kFrontOwn);
+  const EdgeTiling w = edge_tiling(b, eplanes);
+  d.etx = w.tx;
+  d.ety = w.ty;
+  d.entx = w.ntx;
+  d.enty = w.nty;
+  d.etz = w.tz;
+  d.etiles = w.ntx * w.nty * w.ntz;
   if (out) *out = d;
   return o;
 }
@@ -166,9 +224,9 @@ struct StepC {
 };
 
 // Which cell range a launch walks: padded cells, the [-1, n]^3 range, valid
-// cells, the column tiles of the fused final stage (counted in tiles, not in
-// blocks of cells; no cell coordinates of their own), and the fused front's
-// blocks of kFrontOwn cells of the [-1, n]^3 range.
+// cells, the column tiles of the fused final stage and those of the flattening
+// and tracing pass (counted in tiles, not in blocks of cells; no cell
+// coordinates of their own).
 enum Space { kSpaceP = 0, kSpaceE = 1, kSpaceV = 2, kSpaceT = 3, kSpaceF = 4 };
 constexpr int kSpaces = 5;
 
@@ -397,12 +455,8 @@ struct StepArgs {
   unsigned long long barrier_ticks;
   // 1: stages riem2 and update run fused (k_final) where the step allows it
   int fuse_final;
-  // 1: stages trace and riem0 of x run fused (k_front) where the step
-  // allows it; their launches then take y and z only
-  int fuse_front;
-  // direction of row 0 of the trace and riem0 launches (1 when k_front has
-  // taken x)
-  int dir0;
+  // 1: stages flat and trace run as one pass (k_edges)
+  int edges;
   // where stage 1 reads a ghost cell of the input state: 0 the input's own
   // ghost cell; 1 its periodic image in the same box; 2 its source cell in
   // the neighbouring box of boxes that tile a periodic domain as a

@@ -287,29 +287,9 @@ __device__ __forceinline__ real flat_tilde(real sp, real pm2, real pm1, real pp1
   return w ? vmax((real)0, vmin((real)1, (real)FLAT_OMEGA2 * (z - (real)FLAT_OMEGA1))) : (real)0;
 }
 
-__device__ __forceinline__ void flat_body(const StepArgs& A, const Item& it) {
-  Loc L = locate(A, kStFlat, kSpaceE, it);
-  const BoxDev& b = *L.bd;
-  if (L.idx >= b.E) return;
-  const unsigned e = L.idx;
-  int ec[3];
-  space_coords(b, kSpaceE, L.idx, ec);
-  const int ie = ec[0], je = ec[1], ke = ec[2];
-  const real* prim = (const real*)A.work + b.w_prim;
-  const real* P = prim + 4 * b.P;
-  const real sp = (real)A.small_pres;
-  const unsigned c0 = local_idx(pidx_e(b, ie, je, ke));
-  const unsigned sd[3] = {1u, (unsigned)b.px, (unsigned)b.px * (unsigned)b.py};
-  // neighbour shifts go into the (uniform) base; all loads share c0 and are
-  // issued before any arithmetic, so a wave waits once for all of them
-  real pd[3][7], ud[3][5];
-  const real pc = ldw(P, c0);
-  for (int d = 0; d < 3; ++d) {
-    const unsigned s = sd[d];
-    const real* U = prim + (1 + d) * b.P;
-    for (int o = -3; o <= 3; ++o) pd[d][o + 3] = o == 0 ? pc : ldw(P + (long long)o * s, c0);
-    for (int o = -2; o <= 2; ++o) ud[d][o + 2] = ldw(U + (long long)o * s, c0);
-  }
+// chi of a cell from the pressures (offsets -3..3) and normal velocities
+// (-2..2) along each direction
+__device__ __forceinline__ real flat_core(real sp, const real (*pd)[7], const real (*ud)[5]) {
   real cmin = (real)1;
   for (int d = 0; d < 3; ++d) {
     const real* p = pd[d];
@@ -334,6 +314,31 @@ __device__ __forceinline__ void flat_body(const StepArgs& A, const Item& it) {
     real cd = (real)1 - f;
     cmin = (d == 0) ? cd : vmin(cmin, cd);
   }
+  return cmin;
+}
+__device__ __forceinline__ void flat_body(const StepArgs& A, const Item& it) {
+  Loc L = locate(A, kStFlat, kSpaceE, it);
+  const BoxDev& b = *L.bd;
+  if (L.idx >= b.E) return;
+  const unsigned e = L.idx;
+  int ec[3];
+  space_coords(b, kSpaceE, L.idx, ec);
+  const int ie = ec[0], je = ec[1], ke = ec[2];
+  const real* prim = (const real*)A.work + b.w_prim;
+  const real* P = prim + 4 * b.P;
+  const unsigned c0 = local_idx(pidx_e(b, ie, je, ke));
+  const unsigned sd[3] = {1u, (unsigned)b.px, (unsigned)b.px * (unsigned)b.py};
+  // neighbour shifts go into the (uniform) base; all loads share c0 and are
+  // issued before any arithmetic, so a wave waits once for all of them
+  real pd[3][7], ud[3][5];
+  const real pc = ldw(P, c0);
+  for (int d = 0; d < 3; ++d) {
+    const unsigned s = sd[d];
+    const real* U = prim + (1 + d) * b.P;
+    for (int o = -3; o <= 3; ++o) pd[d][o + 3] = o == 0 ? pc : ldw(P + (long long)o * s, c0);
+    for (int o = -2; o <= 2; ++o) ud[d][o + 2] = ldw(U + (long long)o * s, c0);
+  }
+  const real cmin = flat_core((real)A.small_pres, pd, ud);
   stw((real*)A.work + b.w_chi, local_idx(e), cmin);
 }
 __global__ __launch_bounds__(kBlock) void k_flat(StepArgs A) { flat_body(A, launch_item(A, kStFlat)); }
@@ -529,63 +534,68 @@ __device__ __forceinline__ void trace_side(const real* qc, real c, const real* q
                  : qe[t2];
 }
 
-// The direction of a launch row is uniform per workgroup; each stage body is
-// instantiated per direction so that component and stride choices are
-// compile-time constants instead of selects.
-// The tracing of one cell of the [-1, n]^3 range in direction D (E-index e,
-// E-coordinates ie, je, ke): its low- and high-side edge states after the
-// half-step sources and the floors, in lo and hi; returns the floors applied.
+// The tracing of one cell in direction D from its stencil values qs[v][offset
+// + 2], its flattening coefficient, sound speed and gravity: the low- and
+// high-side edge states after the half-step sources and the floors, in lo and
+// hi; returns the floors applied.  Instantiated per direction, so component
+// choices are compile-time constants.
+template <int D>
+__device__ __forceinline__ unsigned trace_core(const StepArgs& A, const StepC& C,
+                                               const real (*qs)[5], real chi, real c,
+                                               const real* g, real* lo, real* hi) {
+  constexpr int d = D;
+  unsigned floors = 0;
+  real qc[5], qm[5], qp[5], dq[5], q6[5];
+  if (A.recon == NYX_RECON_PLM) {
+    for (int v = 0; v < 5; ++v) plm_edges(qs[v], chi, qm[v], qp[v]);
+  } else {
+    ppm_cell(qs, chi, qm, qp);
+  }
+  for (int v = 0; v < 5; ++v) {
+    qc[v] = qs[v][2];
+    dq[v] = qp[v] - qm[v];
+    q6[v] = (real)6 * qc[v] - (real)3 * (qm[v] + qp[v]);
+  }
+  const int nv = 1 + d, t1 = 1 + (d + 1) % 3, t2 = 1 + (d + 2) % 3;
+  const real u = qc[nv];
+  real lam[3] = {u - c, u, u + c};
+  const real kh = C.NYX_REAL(kh);
+  real sig[3];
+  for (int w = 0; w < 3; ++w) sig[w] = fabs(lam[w]) * kh;
+  trace_side<+1>(qc, c, qp, dq, q6, lam, sig, nv, t1, t2, hi);
+  trace_side<-1>(qc, c, qm, dq, q6, lam, sig, nv, t1, t2, lo);
+  // half-step gravity and expansion sources, then floors
+  const real hdt_a = C.NYX_REAL(hdt_a), hda_a = C.NYX_REAL(hda_a), pexp = C.NYX_REAL(pexp);
+  const real sd_ = A.NYX_REAL(small_dens), sp_ = A.NYX_REAL(small_pres);
+  real* out[2] = {lo, hi};
+  for (int sd = 0; sd < 2; ++sd) {
+    real* q = out[sd];
+    for (int dd = 0; dd < 3; ++dd) q[1 + dd] = q[1 + dd] + (hdt_a * g[dd] - hda_a * qc[1 + dd]);
+    q[4] = q[4] - pexp * qc[4];
+    if (q[0] < sd_) { q[0] = sd_; floors++; }
+    if (q[4] < sp_) { q[4] = sp_; floors++; }
+  }
+  return floors;
+}
+// The same for a cell of the [-1, n]^3 range (E-index e, E-coordinates ie, je,
+// ke) with its values loaded from the stage arrays.
 template <int D>
 __device__ __forceinline__ unsigned trace_cell(const StepArgs& A, const BoxDev& b, const StepC& C,
                                                unsigned e, int ie, int je, int ke, real* lo,
                                                real* hi) {
-  constexpr int d = D;
-  unsigned floors = 0;
-  {
-    const real* prim = (const real*)A.work + b.w_prim;
-    const unsigned c0 = local_idx(pidx_e(b, ie, je, ke));
-    const unsigned s = d == 0 ? 1u : (d == 1 ? (unsigned)b.px : (unsigned)b.px * (unsigned)b.py);
-    // every load of the cell is issued before any arithmetic, so a wave
-    // waits once for all of them instead of once per variable
-    const real chi = ldw((const real*)A.work + b.w_chi, local_idx(e));
-    real qs[5][5];
-    for (int v = 0; v < 5; ++v)
-      for (int o = -2; o <= 2; ++o) qs[v][o + 2] = ldw(prim + v * b.P + (long long)o * s, c0);
-    const real c = ldw(prim + 5 * b.P, c0);
-    const real* G = (const real*)A.grav + b.goff;
-    const real g[3] = {ldw(G, c0), ldw(G + b.gstride, c0), ldw(G + 2 * b.gstride, c0)};
-    real qc[5], qm[5], qp[5], dq[5], q6[5];
-    if (A.recon == NYX_RECON_PLM) {
-      for (int v = 0; v < 5; ++v) plm_edges(qs[v], chi, qm[v], qp[v]);
-    } else {
-      ppm_cell(qs, chi, qm, qp);
-    }
-    for (int v = 0; v < 5; ++v) {
-      qc[v] = qs[v][2];
-      dq[v] = qp[v] - qm[v];
-      q6[v] = (real)6 * qc[v] - (real)3 * (qm[v] + qp[v]);
-    }
-    const int nv = 1 + d, t1 = 1 + (d + 1) % 3, t2 = 1 + (d + 2) % 3;
-    const real u = qc[nv];
-    real lam[3] = {u - c, u, u + c};
-    const real kh = C.NYX_REAL(kh);
-    real sig[3];
-    for (int w = 0; w < 3; ++w) sig[w] = fabs(lam[w]) * kh;
-    trace_side<+1>(qc, c, qp, dq, q6, lam, sig, nv, t1, t2, hi);
-    trace_side<-1>(qc, c, qm, dq, q6, lam, sig, nv, t1, t2, lo);
-    // half-step gravity and expansion sources, then floors
-    const real hdt_a = C.NYX_REAL(hdt_a), hda_a = C.NYX_REAL(hda_a), pexp = C.NYX_REAL(pexp);
-    const real sd_ = A.NYX_REAL(small_dens), sp_ = A.NYX_REAL(small_pres);
-    real* out[2] = {lo, hi};
-    for (int sd = 0; sd < 2; ++sd) {
-      real* q = out[sd];
-      for (int dd = 0; dd < 3; ++dd) q[1 + dd] = q[1 + dd] + (hdt_a * g[dd] - hda_a * qc[1 + dd]);
-      q[4] = q[4] - pexp * qc[4];
-      if (q[0] < sd_) { q[0] = sd_; floors++; }
-      if (q[4] < sp_) { q[4] = sp_; floors++; }
-    }
-  }
-  return floors;
+  const real* prim = (const real*)A.work + b.w_prim;
+  const unsigned c0 = local_idx(pidx_e(b, ie, je, ke));
+  const unsigned s = D == 0 ? 1u : (D == 1 ? (unsigned)b.px : (unsigned)b.px * (unsigned)b.py);
+  // every load of the cell is issued before any arithmetic, so a wave
+  // waits once for all of them instead of once per variable
+  const real chi = ldw((const real*)A.work + b.w_chi, local_idx(e));
+  real qs[5][5];
+  for (int v = 0; v < 5; ++v)
+    for (int o = -2; o <= 2; ++o) qs[v][o + 2] = ldw(prim + v * b.P + (long long)o * s, c0);
+  const real c = ldw(prim + 5 * b.P, c0);
+  const real* G = (const real*)A.grav + b.goff;
+  const real g[3] = {ldw(G, c0), ldw(G + b.gstride, c0), ldw(G + 2 * b.gstride, c0)};
+  return trace_core<D>(A, C, qs, chi, c, g, lo, hi);
 }
 template <int D>
 __device__ __forceinline__ void store_edges(const StepArgs& A, const BoxDev& b, unsigned e,
@@ -610,7 +620,6 @@ __device__ __forceinline__ unsigned trace_dir(const StepArgs& A, const BoxDev& b
 __device__ __forceinline__ void trace_body(const StepArgs& A, const Item& it) {
   int d;
   Loc L = locate(A, kStTrace, kSpaceE, it, &d);
-  d += A.dir0;
   const BoxDev& b = *L.bd;
   unsigned floors = 0;
   if (L.idx < b.E) {
@@ -621,6 +630,157 @@ __device__ __forceinline__ void trace_body(const StepArgs& A, const Item& it) {
   if (A.stats) count(A, kFloorHits, floors);
 }
 __global__ __launch_bounds__(kBlock) void k_trace(StepArgs A) { trace_body(A, launch_item(A, kStTrace)); }
+
+#if defined(NYX_PREC_MIXED)
+// ---------------------------------------------------------------------------
+// stages 2 and 3 in one pass (k_edges): a workgroup takes a tile of TX x TY
+// cell columns of the [-1, n]^3 range and marches up a chunk of planes.  A
+// thread keeps its column's stencil along z in registers (one load per
+// variable and plane instead of one per variable and offset), the plane with
+// its halo of three cells is in LDS for the stencils along x and y, and the
+// flattening coefficient is used where it is computed.
+// Why: the stage kernels issued 35 + 3 x 40 memory instructions per cell and
+// were bound by the CUs' address units (TA busy 81 to 86% of the time; vector
+// issue 42%, memory 2.9 TB/s), not by what these move.  Here it is about 14
+// loads and the 30 stores of the edge states.  64 shocked 64^3 patches: 791 us
+// at 4.5 TB/s (vector issue 77%) against 171 us of flattening and the tracing
+// behind it, the whole step 5610 -> 5200 us; 256^3 5215 -> 4915.
+// Neighbouring tiles in x are launched next to each other, so that the cache
+// lines that their rows share are completed in one L2 (256^3 with y first: 5450).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kEdgeBlock) void k_edges(StepArgs A) {
+  __shared__ real pl[5 * kEdgeLds];
+  const int lin = (int)xcd_linear_block(true);
+  const int* pre = A.prefix[kSpaceF];
+  int lo_ = 0, hi_ = A.nb;
+  while (hi_ - lo_ > 1) {
+    const int mid = (lo_ + hi_) >> 1;
+    if (pre[mid] <= lin) lo_ = mid;
+    else hi_ = mid;
+  }
+  const BoxDev& b = scalar_ref(A.table[lo_]);
+  const StepC& C = step_consts(A, b);
+  const int TX = b.etx, TY = b.ety, LX = TX + 6;
+  const int tile = lin - pre[lo_];
+  const int txi = tile % b.entx, q = tile / b.entx, tyi = q % b.enty, tzi = q / b.enty;
+  const int x0 = txi * TX, y0 = tyi * TY, z0 = tzi * b.etz;
+  const int z1 = b.ez < z0 + b.etz ? b.ez : z0 + b.etz;
+  const int t = (int)threadIdx.x;
+  const int tj = t / TX, ti = t - tj * TX;
+  const bool lane = tj < TY;
+  const bool on = lane && x0 + ti < b.ex && y0 + tj < b.ey;
+  const unsigned px = (unsigned)b.px, pxy = px * (unsigned)b.py;
+  // padded cell of E-coordinates (x, y) in the plane, kept inside the box
+  // (cells past it are loaded but not used)
+  auto pcell = [&](int x, int y) {
+    const int i = x - 1 + b.ng, j = y - 1 + b.ng;
+    return (unsigned)(j < b.py ? j : b.py - 1) * px + (unsigned)(i < b.px ? i : b.px - 1);
+  };
+  const int li = lane ? (tj + 3) * LX + ti + 3 : 0;
+  // up to two halo cells of the plane per thread
+  const int nh = LX * (TY + 6) - TX * TY;
+  int hl[2];
+  unsigned hg[2];
+  for (int k = 0; k < 2; ++k) {
+    int h = t + k * kEdgeBlock, lx, ly;
+    const bool in = h < nh;
+    h = in ? h : 0;
+    if (h < 6 * LX) {
+      ly = h / LX;
+      lx = h - ly * LX;
+      ly = ly < 3 ? ly : ly + TY;
+    } else {
+      h -= 6 * LX;
+      ly = h / 6;
+      lx = h - ly * 6;
+      ly += 3;
+      lx = lx < 3 ? lx : lx + TX;
+    }
+    hl[k] = in ? ly * LX + lx : -1;
+    hg[k] = pcell(x0 + lx - 3, y0 + ly - 3);
+  }
+  const real* prim = (const real*)A.work + b.w_prim;
+  const real* G = (const real*)A.grav + b.goff;
+  unsigned id = pcell(x0 + ti, y0 + (lane ? tj : 0)) + (unsigned)(z0 - 1 + b.ng) * pxy;  // plane z
+  for (int k = 0; k < 2; ++k) hg[k] += (unsigned)(z0 - 1 + b.ng) * pxy;
+  unsigned e = ((unsigned)z0 * (unsigned)b.ey + (unsigned)(y0 + tj)) * (unsigned)b.ex +
+               (unsigned)(x0 + ti);
+  // the column: rho, u, v, w at z - 2 .. z + 2, p at z - 3 .. z + 3, and c, g
+  real col[4][5], pz[7], cg[4], halo[2][5];
+  for (int v = 0; v < 4; ++v)
+    for (int o = -2; o <= 2; ++o) col[v][o + 2] = ldw(prim + v * b.P + (long long)o * pxy, id);
+  for (int o = -3; o <= 3; ++o) pz[o + 3] = ldw(prim + 4 * b.P + (long long)o * pxy, id);
+  cg[0] = ldw(prim + 5 * b.P, id);
+  for (int d = 0; d < 3; ++d) cg[1 + d] = ldw(G + d * b.gstride, id);
+  for (int k = 0; k < 2; ++k)
+    if (hl[k] >= 0)
+      for (int v = 0; v < 5; ++v) halo[k][v] = ldw(prim + v * b.P, hg[k]);
+  unsigned floors = 0;
+  for (int z = z0; z < z1; ++z) {
+    if (lane) {
+      for (int v = 0; v < 4; ++v) pl[v * kEdgeLds + li] = col[v][2];
+      pl[4 * kEdgeLds + li] = pz[3];
+    }
+    for (int k = 0; k < 2; ++k)
+      if (hl[k] >= 0)
+        for (int v = 0; v < 5; ++v) pl[v * kEdgeLds + hl[k]] = halo[k][v];
+    __syncthreads();
+    // the next plane's values are on their way during this plane's arithmetic
+    const real c = cg[0], g[3] = {cg[1], cg[2], cg[3]};
+    real nc[4] = {}, np = (real)0;
+    if (z + 1 < z1) {
+      id += pxy;
+      for (int v = 0; v < 4; ++v) nc[v] = ldw(prim + v * b.P + 2ll * pxy, id);
+      np = ldw(prim + 4 * b.P + 3ll * pxy, id);
+      cg[0] = ldw(prim + 5 * b.P, id);
+      for (int d = 0; d < 3; ++d) cg[1 + d] = ldw(G + d * b.gstride, id);
+      for (int k = 0; k < 2; ++k) {
+        hg[k] += pxy;
+        if (hl[k] >= 0)
+          for (int v = 0; v < 5; ++v) halo[k][v] = ldw(prim + v * b.P, hg[k]);
+      }
+    }
+    if (on) {
+      real pd[3][7], ud[3][5];
+      for (int o = -3; o <= 3; ++o) {
+        pd[0][o + 3] = pl[4 * kEdgeLds + li + o];
+        pd[1][o + 3] = pl[4 * kEdgeLds + li + o * LX];
+        pd[2][o + 3] = pz[o + 3];
+      }
+      for (int o = -2; o <= 2; ++o) {
+        ud[0][o + 2] = pl[1 * kEdgeLds + li + o];
+        ud[1][o + 2] = pl[2 * kEdgeLds + li + o * LX];
+        ud[2][o + 2] = col[3][o + 2];
+      }
+      const real chi = flat_core((real)A.small_pres, pd, ud);
+      real qs[5][5], lo[5], hi[5];
+      for (int v = 0; v < 5; ++v)
+        for (int o = -2; o <= 2; ++o) qs[v][o + 2] = pl[v * kEdgeLds + li + o];
+      floors += trace_core<0>(A, C, qs, chi, c, g, lo, hi);
+      store_edges<0>(A, b, e, lo, hi);
+      for (int v = 0; v < 5; ++v)
+        for (int o = -2; o <= 2; ++o) qs[v][o + 2] = pl[v * kEdgeLds + li + o * LX];
+      floors += trace_core<1>(A, C, qs, chi, c, g, lo, hi);
+      store_edges<1>(A, b, e, lo, hi);
+      for (int o = -2; o <= 2; ++o) {
+        for (int v = 0; v < 4; ++v) qs[v][o + 2] = col[v][o + 2];
+        qs[4][o + 2] = pz[o + 3];
+      }
+      floors += trace_core<2>(A, C, qs, chi, c, g, lo, hi);
+      store_edges<2>(A, b, e, lo, hi);
+    }
+    for (int v = 0; v < 4; ++v) {
+      for (int o = 0; o < 4; ++o) col[v][o] = col[v][o + 1];
+      col[v][4] = nc[v];
+    }
+    for (int o = 0; o < 6; ++o) pz[o] = pz[o + 1];
+    pz[6] = np;
+    e += (unsigned)b.ex * (unsigned)b.ey;
+    __syncthreads();
+  }
+  if (A.stats) count<kEdgeBlock>(A, kFloorHits, floors);
+}
+#endif
 
 // ---------------------------------------------------------------------------
 // two-shock Riemann solver (O5), always FP64
@@ -1433,7 +1593,6 @@ template <bool LEARNED>
 __device__ __forceinline__ void riem0_body(const StepArgs& A, const Item& it, __bf16* mlp_lds) {
   int d;
   Loc L = locate(A, kStRiem0, kSpaceE, it, &d);
-  d += A.dir0;
   const BoxDev& b = *L.bd;
   __bf16* lds = mlp_lds + (threadIdx.x >> 6) * kMlpWaveLds * LEARNED;
   Tally T;
@@ -1446,82 +1605,6 @@ template <bool LEARNED>
 __global__ __launch_bounds__(kBlock) void k_riem0(StepArgs A) {
   __shared__ __bf16 mlp_lds[LEARNED ? (kBlock / 64) * kMlpWaveLds : 1];
   riem0_body<LEARNED>(A, launch_item(A, kStRiem0), mlp_lds);
-}
-
-// ---------------------------------------------------------------------------
-// fused front (launch mode NYX_LAUNCH_FUSED): stages 3 and 4 of x in one
-// kernel.  Each cell is traced as k_trace traces it and its edge states are
-// stored, and each x-face is solved as k_riem0 solves it, from the high-side
-// state of the cell below and the low-side state of the cell above, which
-// the kernel still holds instead of reading them back.  (A thread walking a
-// column along y or z, carrying the high-side state in registers, was
-// slower than the staged kernels for those directions.)
-// ---------------------------------------------------------------------------
-// the stage-0 solve of the D-face at E-index e from the stage-array states L
-// (high side of the cell below) and R (low side of the cell above)
-template <int D>
-__device__ __forceinline__ void riem0_face(const StepArgs& A, const BoxDev& b, unsigned e,
-                                           bool active, const real* L, const real* R, Tally& T) {
-  double ql[5], qr[5];
-  if (active) {
-    double Ls[5], Rs[5];
-    for (int v = 0; v < 5; ++v) {
-      Ls[v] = (double)L[v];
-      Rs[v] = (double)R[v];
-    }
-    rotate(D, Ls, ql);
-    rotate(D, Rs, qr);
-  }
-  RiemannOut g = solve<false>(A, active, ql, qr, nullptr, &T.used, &T.fb);
-  if (active) {
-    T.calls += 1;
-    T.iters += g.iters;
-    store_god((real*)A.work + b.w_f0 + (long long)D * kGod * b.E, b.E, e, g);
-  }
-}
-
-// x: wavefront w of block bb holds E-cells bb kFrontOwn + 63 w - 1 + lane.
-// Lane 0's cell is the previous wavefront's last: lane 0 only traces it,
-// for the high-side state lane 1 takes.  Every other lane stores its
-// cell's edge states and solves the x-face below the cell (none at the
-// range's first column) with the state of lane - 1.
-__device__ __forceinline__ void front_x(const StepArgs& A, const BoxDev& b, const StepC& C,
-                                        unsigned bb, unsigned& floors, Tally& T) {
-  const int lane = (int)(threadIdx.x & 63);
-  const long long e = (long long)bb * kFrontOwn + (long long)(threadIdx.x >> 6) * 63 + lane - 1;
-  const bool on = e >= 0 && e < b.E;
-  const bool own = on && lane > 0;
-  int ec[3] = {0, 0, 0};
-  real lo[5] = {}, hi[5] = {};
-  unsigned fl = 0;
-  if (on) {
-    space_coords(b, kSpaceE, (unsigned)e, ec);
-    fl = trace_cell<0>(A, b, C, (unsigned)e, ec[0], ec[1], ec[2], lo, hi);
-  }
-  if (own) {
-    floors += fl;
-    store_edges<0>(A, b, (unsigned)e, lo, hi);
-  }
-  real left[5];
-  for (int v = 0; v < 5; ++v) left[v] = __shfl_up(hi[v], 1, 64);
-  riem0_face<0>(A, b, (unsigned)e, own && ec[0] >= 1, left, lo, T);
-}
-
-__global__ __launch_bounds__(kBlock) void k_front(StepArgs A) {
-  const unsigned x = xcd_linear_block(true);
-  const int* pre = A.prefix[kSpaceF];
-  int lo = 0, hi = A.nb;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (pre[mid] <= (int)x) lo = mid;
-    else hi = mid;
-  }
-  const BoxDev& b = scalar_ref(A.table[lo]);
-  unsigned floors = 0;
-  Tally T;
-  front_x(A, b, step_consts(A, b), x - (unsigned)pre[lo], floors, T);
-  if (A.stats) count(A, kFloorHits, floors);
-  count_tally<false>(A, T, false);
 }
 
 // ---------------------------------------------------------------------------
@@ -2282,24 +2365,21 @@ hipError_t launch_step(const StepArgs& a, hipStream_t s) {
   if (a.single_dst) hipLaunchKernelGGL(k_prim_single, dim3(a.nblocks[kSpaceP]), blk, 0, s, a);
   else hipLaunchKernelGGL(k_prim, dim3(a.nblocks[kSpaceP]), blk, 0, s, a);
   mark(1);
-  hipLaunchKernelGGL(k_flat, dim3(a.nblocks[kSpaceE]), blk, 0, s, a);
-  mark(2);
-  if (a.fuse_front && !learned(0)) {
-    // trace and riem0 of x fused, then the staged kernels for y and z
-    // (rows 0 and 1 of their grids); stage 3's time holds k_front and the
-    // y, z tracing, stage 4's the y, z solves
-    StepArgs yz = a;
-    yz.dir0 = 1;
-    hipLaunchKernelGGL(k_front, dim3(a.nblocks[kSpaceF]), blk, 0, s, a);
-    hipLaunchKernelGGL(k_trace, dim3(a.nblocks[kSpaceE], 2), blk, 0, s, yz);
-    mark(3);
-    hipLaunchKernelGGL(k_riem0<false>, dim3(a.nblocks[kSpaceE], 2), blk, 0, s, yz);
-  } else {
+#if defined(NYX_PREC_MIXED)
+  if (a.edges) {
+    // flattening and tracing as one launch; its time is stage 3's
+    mark(2);
+    hipLaunchKernelGGL(k_edges, dim3(a.nblocks[kSpaceF]), dim3(kEdgeBlock), 0, s, a);
+  } else
+#endif
+  {
+    hipLaunchKernelGGL(k_flat, dim3(a.nblocks[kSpaceE]), blk, 0, s, a);
+    mark(2);
     hipLaunchKernelGGL(k_trace, dim3(a.nblocks[kSpaceE], 3), blk, 0, s, a);
-    mark(3);
-    if (learned(0)) hipLaunchKernelGGL(k_riem0<kHasLearned>, dim3(a.nblocks[kSpaceE], 3), blk, 0, s, a);
-    else hipLaunchKernelGGL(k_riem0<false>, dim3(a.nblocks[kSpaceE], 3), blk, 0, s, a);
   }
+  mark(3);
+  if (learned(0)) hipLaunchKernelGGL(k_riem0<kHasLearned>, dim3(a.nblocks[kSpaceE], 3), blk, 0, s, a);
+  else hipLaunchKernelGGL(k_riem0<false>, dim3(a.nblocks[kSpaceE], 3), blk, 0, s, a);
   mark(4);
   if (learned(1)) hipLaunchKernelGGL(k_riem1<kHasLearned>, dim3(a.nblocks[kSpaceE], 6), blk, 0, s, a);
   else if (a.nblocks[kSpaceE] <= kPairBlocks)

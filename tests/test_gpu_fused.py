@@ -220,6 +220,39 @@ def test_fused_equals_staged_variants(nyx, prec, variant):
     plan.close()
 
 
+@pytest.mark.parametrize("recon", ["ppm", "plm"])
+@pytest.mark.parametrize("mode", ["staged", "fused"])
+def test_edge_pass_equals_separate_kernels(nyx, recon, mode):
+    """Flattening and tracing in one marching pass (FP32-mixed launches of
+    5/4 2^20 cells and more: all boxes in one group) against their separate
+    kernels (the same boxes in groups of at most the largest one's size), bit
+    for bit.  Tiles span up to 72 columns of [-1, n] in x: whole (72), halved
+    (73 and up), partial in x and y, boxes 2 cells across each way, chunks of
+    unequal length and taller than 64 planes."""
+    import torch
+    shapes = [(70, 44, 52), (72, 30, 46), (2, 6, 298), (298, 2, 10), (6, 298, 2), (146, 26, 14)]
+    shapes += [(64, 64, 64)] * 3 + [(20, 18, 130), (110, 62, 38)]
+    E = [(a + 2) * (b + 2) * (c + 2) for a, b, c in shapes]
+    assert sum(E) > 5 * 2**18 > 2 * max(E)
+    prm = nyx.default_params(precision=nyx.NYX_MIXED, recon=1 if recon == "plm" else 0)
+    boxes, _, _, flat, gflat = _pack(nyx, shapes)
+    mn, one = nyx.Batch.workspace_bytes(prm, boxes)
+    Ui, G = to_dev(flat), to_dev(gflat, torch.float32)
+    m = nyx.NYX_LAUNCH_STAGED if mode == "staged" else nyx.NYX_LAUNCH_FUSED
+    res = []
+    for ws in (one, mn):
+        plan = nyx.Batch(prm, boxes, aligned_ws(ws))
+        assert (plan.num_groups == 1) == (ws == one)
+        dt = torch.zeros(len(boxes), dtype=torch.float64, device="cuda")
+        plan.estimate_dt(Ui, 0.25, 0.5, dt)
+        res.append(_steps(nyx, torch, plan, Ui, G, dt, [0.25, 0.2505, 0.251], m))
+        plan.close()
+    assert torch.equal(res[0][0], res[1][0])
+    for a, b in zip(res[0][1], res[1][1]):
+        assert np.array_equal(a, b)
+    assert res[0][2] == res[1][2] and res[0][2]["riemann_calls"] > 0
+
+
 @pytest.mark.parametrize("stages", [3, 4, 7])
 def test_fused_with_learned_flux(nyx, stages):
     """The learned flux on stages 0-1 (the x front stays staged, the fused
