@@ -82,11 +82,15 @@ struct BoxDev {
   FastDiv dz[3];           // per Space: number of planes
   unsigned sy[3];          // per Space: rows per plane
   unsigned sc[3];          // per Space: cell count (< 2^31)
-  int tx, ty, ntx, nty;    // fused final stage: tile shape, tiles along x and y,
-  int ntiles, tz;          // tiles in all (z chunks included), planes per chunk
-  int etx, ety, entx, enty;  // flattening and tracing pass: tile shape, tiles along x and y,
-  int etiles, etz;         // tiles in all (z chunks included), planes per chunk
+  int ntx, nty, ntiles;    // fused final stage: tiles along x and y, and in all
+  int etiles;              // flattening and tracing pass: tiles in all
+  unsigned short tx, ty;   // final stage: tile shape
+  unsigned char tz;        // final stage: planes per chunk (at most kFinPlanes)
+  unsigned char etx, ety, etz;  // flattening and tracing pass: tile shape, planes per chunk
 };
+// a plan's workspace holds one per box: a larger one would refuse workspaces
+// that held the plan before
+static_assert(sizeof(BoxDev) <= 328, "box descriptor grown");
 
 // Stage-array element count for a box (before alignment padding).
 inline long long align_elems(long long n) { return (n + 63) / 64 * 64; }
@@ -196,18 +200,16 @@ inline long long box_layout(const nyx_box& b, int gidx, long long base, BoxDev* 
   d.sc[1] = (unsigned)d.E;
   d.sc[2] = (unsigned)d.V;
   const FinTiling t = fin_tiling(b, planes);
-  d.tx = t.tx;
-  d.ty = t.ty;
+  d.tx = (unsigned short)t.tx;
+  d.ty = (unsigned short)t.ty;
   d.ntx = t.ntx;
   d.nty = t.nty;
-  d.tz = t.tz;
+  d.tz = (unsigned char)t.tz;
   d.ntiles = t.ntx * t.nty * t.ntz;
   const EdgeTiling w = edge_tiling(b, eplanes);
-  d.etx = w.tx;
-  d.ety = w.ty;
-  d.entx = w.ntx;
-  d.enty = w.nty;
-  d.etz = w.tz;
+  d.etx = (unsigned char)w.tx;
+  d.ety = (unsigned char)w.ty;
+  d.etz = (unsigned char)w.tz;
   d.etiles = w.ntx * w.nty * w.ntz;
   if (out) *out = d;
   return o;
@@ -216,7 +218,7 @@ inline long long box_layout(const nyx_box& b, int gidx, long long base, BoxDev* 
 // Per-box constants of a step, computed once per box by the step's prologue
 // kernel (the same expressions the oracle evaluates on the host).
 struct StepC {
-  double dt, a_h, da, kh, hdt_a, hda_a, pexp, kap1, kap2, k, gm1;
+  double dt, a_h, da, kh, hdt_a, hda_a, pexp, kap1, kap2, k;
   double xo, xn;  // expansion source of the energy equations at a_old / a_new
   // the tracing's factors in FP32 (the mixed build's; a kernel then reads them
   // as scalars instead of converting them in every lane)
@@ -500,19 +502,19 @@ __device__ __forceinline__ StepC step_constants(const StepArgs& A, const BoxDev&
 #pragma clang fp contract(off)
   StepC c;
   c.dt = A.dt_dev ? A.dt_dev[b.gidx] : A.dt_host;
-  c.gm1 = A.gamma - 1.0;
+  const double gm1 = A.gamma - 1.0;
   c.a_h = 0.5 * (A.a_old + A.a_new);
   c.da = A.a_new - A.a_old;
   c.kh = c.dt / (c.a_h * b.dx);
   c.hdt_a = (0.5 * c.dt) / c.a_h;
   c.hda_a = (0.5 * c.da) / c.a_h;
-  c.pexp = (1.5 * c.gm1) * (c.da / c.a_h);
+  c.pexp = (1.5 * gm1) * (c.da / c.a_h);
   c.kap1 = c.kh / 3.0;
   c.kap2 = c.kh / 2.0;
   c.k = c.dt / b.dx;
   // a adot (2 - 3(gamma-1)) rho e = (adot / a) cgam U_e; integrated over the
   // step at a_old (predictor) and a_new (corrector)
-  const double cgam = 2.0 - 3.0 * c.gm1;
+  const double cgam = 2.0 - 3.0 * gm1;
   c.xo = cgam * (c.da / A.a_old);
   c.xn = cgam * (c.da / A.a_new);
   c.khf = (float)c.kh;

@@ -662,7 +662,8 @@ __global__ __launch_bounds__(kEdgeBlock) void k_edges(StepArgs A) {
   const StepC& C = step_consts(A, b);
   const int TX = b.etx, TY = b.ety, LX = TX + 6;
   const int tile = lin - pre[lo_];
-  const int txi = tile % b.entx, q = tile / b.entx, tyi = q % b.enty, tzi = q / b.enty;
+  const int ntx = (b.ex + TX - 1) / TX, nty = (b.ey + TY - 1) / TY;
+  const int txi = tile % ntx, q = tile / ntx, tyi = q % nty, tzi = q / nty;
   const int x0 = txi * TX, y0 = tyi * TY, z0 = tzi * b.etz;
   const int z1 = b.ez < z0 + b.etz ? b.ez : z0 + b.etz;
   const int t = (int)threadIdx.x;

@@ -293,3 +293,11 @@ def test_noalloc_step_validates_before_launch(nyx):
         assert _noalloc(nyx, q, big) == -8
         assert nyx.lib().nyx_status_string(-8).decode().startswith("box needs more scratch")
     assert fits[-1] >= 48  # FP32-mixed holds the 48^3 boxes of the level workload
+
+
+@pytest.mark.parametrize("nbox, n, most", [(1, 16, 4917504), (256, 16, 5041152), (5000, 2, 2541568)])
+def test_batch_workspace_never_grows(nyx, nbox, n, most):
+    """A workspace of the size that once held a plan of one-box groups still
+    holds it (FP64; the bytes beside the stage arrays are the box tables)."""
+    mn, _ = nyx.Batch.workspace_bytes(nyx.default_params(), [nyx.make_box((n, n, n), 4, 1.0)] * nbox)
+    assert mn <= most
