@@ -312,12 +312,16 @@ __device__ __forceinline__ double div6(double x) {
   return fma(fma(-6.0, q, x), y, q);
 }
 
-// one Gauss-Seidel half sweep: cells with (i + j + k) % 2 == color
+// one Gauss-Seidel half sweep: cells with (i + j + k) % 2 == color.  Bound by
+// memory (12 bytes a cell: 41 us at 256^3, 4.9 TB/s).  Workgroups are numbered
+// XCD by XCD, here and in the kernels below: the rows and planes beside a cell
+// are then read through the L2 that holds them (256^3: 42 us in launch order,
+// the residual's maximum 89 and 79, a solve 8045 and 7720).
 __global__ __launch_bounds__(kBlock) void k_rbgs(double* __restrict__ phi,
                                                  const double* __restrict__ f, Grid g, double h2,
                                                  unsigned color) {
   const unsigned half = g.nx >> 1;
-  const unsigned t = blockIdx.x * kBlock + threadIdx.x;
+  const unsigned t = xcd_linear_block() * kBlock + threadIdx.x;
   if (t >= half * g.ny * g.nz) return;
   const unsigned ih = t % half, r = t / half;
   const unsigned j = r % g.ny, k = r / g.ny;
@@ -359,14 +363,14 @@ __device__ __forceinline__ double pair_sum(const double* other, const Pair& p, u
 
 // max |f - L phi|: one lane per pair of cells.  Bound by memory (16 bytes a
 // cell): 97 us at 256^3 with a lane per cell, its coordinates divided out, 89
-// with pairs.
+// with pairs, 79 with the workgroups numbered XCD by XCD.
 __global__ __launch_bounds__(kBlock) void k_resid_max(const double* __restrict__ phi,
                                                       const double* __restrict__ f, Grid g,
                                                       FastDiv dh, FastDiv dy, double inv_h2,
                                                       double* __restrict__ part) {
   const unsigned half = g.nx >> 1, hn = half * g.ny * g.nz;
   double acc = 0.0;
-  for (unsigned t = blockIdx.x * kBlock + threadIdx.x; t < hn; t += gridDim.x * kBlock) {
+  for (unsigned t = xcd_linear_block() * kBlock + threadIdx.x; t < hn; t += gridDim.x * kBlock) {
     const unsigned r = fast_div(t, dh), ih = t - r * half;
     const unsigned k = fast_div(r, dy), j = r - k * g.ny;
     const Pair p = pair_at(half, g.ny, g.nz, ih, j, k);
@@ -539,7 +543,7 @@ __global__ __launch_bounds__(kBlock) void k_restrict(const double* __restrict__ 
                                                      double inv_h2, Grid gc,
                                                      double* __restrict__ fc,
                                                      double* __restrict__ phic) {
-  const unsigned C = blockIdx.x * kBlock + threadIdx.x;
+  const unsigned C = xcd_linear_block() * kBlock + threadIdx.x;
   if (C < gc.nx * gc.ny * gc.nz) restrict_cell(C, phi, f, g, inv_h2, gc, fc, phic);
 }
 
@@ -575,7 +579,7 @@ __device__ __forceinline__ void prolong_cell(unsigned C, double* phi, const Grid
 }
 __global__ __launch_bounds__(kBlock) void k_prolong(double* __restrict__ phi, Grid g,
                                                     const double* __restrict__ ec, Grid gc) {
-  const unsigned C = blockIdx.x * kBlock + threadIdx.x;
+  const unsigned C = xcd_linear_block() * kBlock + threadIdx.x;
   if (C < gc.nx * gc.ny * gc.nz) prolong_cell(C, phi, g, ec, gc);
 }
 
@@ -620,7 +624,7 @@ template <class T>
 __global__ __launch_bounds__(kBlock) void k_gradient(const double* __restrict__ phi, Grid g,
                                                      double two_dx, BoxDev b,
                                                      T* __restrict__ grav) {
-  const unsigned c = blockIdx.x * kBlock + threadIdx.x;
+  const unsigned c = xcd_linear_block() * kBlock + threadIdx.x;
   if (c >= (unsigned)b.P) return;
   const unsigned px = (unsigned)b.px, py = (unsigned)b.py;
   const int pi = (int)(c % px), pj = (int)((c / px) % py), pk = (int)(c / (px * py));
