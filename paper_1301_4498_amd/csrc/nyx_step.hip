@@ -1173,21 +1173,12 @@ __device__ __forceinline__ RiemannOut lin_solve(const StepArgs& A, const double*
 // true where the stopping step lies far enough above the raw estimates'
 // error for the iteration to use them (see ts_iterate)
 __host__ __device__ __forceinline__ bool raw_stop(const StepArgs& A) { return A.mixed_stop >= 0x1p-20; }
-// The step is written on the velocity jump itself,
-//   u*_R - u*_L = (u_R - u_L) + (p - p_R) w_R + (p - p_L) w_L,
-// and on the slopes' weighted sum, 20 vector instructions an iteration.
 template <bool RAW>
 __device__ __forceinline__ double ts_iterate(const StepArgs& A, const TwoShock& t, double p,
                                              int& it) {
-  const double du = t.ur - t.ul;
   while (it < A.maxiter) {
-    const double dl = p - t.pl, dr = p - t.pr;
-    const double XL = t.CL + t.gl * dl, XR = t.CR + t.gr * dr;
-    const double wL = RAW ? rsq_est(XL) : rsq64(XL), wR = RAW ? rsq_est(XR) : rsq64(XR);
-    const double jump = fma(dl, wL, fma(dr, wR, du));
-    const double slope = fma(0.5 + t.hCL * (wL * wL), wL, (0.5 + t.hCR * (wR * wR)) * wR);
-    // fmax is the floor max(p', small_pres): small_pres is never NaN
-    const double pn = fmax(fma(-jump, rcp_est(slope), p), t.sp);
+    const TwoShockEval e = RAW ? ts_eval_est(t, p) : ts_eval(t, p);
+    const double pn = ts_newton(t, e, p);
     ++it;
     const bool conv = fabs(pn - p) <= A.mixed_stop * pn;
     p = pn;
