@@ -522,8 +522,104 @@ __global__ __launch_bounds__(kTileThreads) void k_smooth_tile(const double* __re
   }
 }
 
-// coarse f = mean of the eight children's residuals f - L phi; coarse phi = 0
-__device__ __forceinline__ void restrict_cell(unsigned C, const double* phi, const double* f,
+// Two sweeps of a large level in one pass over its arrays.  A workgroup takes a
+// tile of 64 x 16 cell columns with a halo of four cells and marches up a chunk
+// of planes; a thread keeps one column of pairs.  With plane K the newest one
+// loaded, the four half sweeps work on planes K - 1, K - 3, K - 5 and K - 7: each
+// then needs only what earlier steps have finished, so that a step takes one
+// barrier (the planes that the four read across columns alternate between two
+// LDS buffers).  Along z the neighbours are in the thread's registers.
+// The first half sweep reads black cells only, so red is written in place and
+// black from one array to another: 20 bytes a cell instead of the four
+// launches' 48.  Every cell gets the operations of the half sweeps above on the
+// same values.
+// Bound by a step's chain of LDS accesses, arithmetic and barrier (75 steps of
+// 1.2 us for 256^3; loads two steps ahead change nothing), with the halo's work
+// on top (1.7 x): two sweeps of 256^3 164 -> 92 us.  Blocks of 16 rows, two a
+// CU, take 152.
+constexpr int kMarchX = 36, kMarchY = 24;  // block: pairs in x, rows in y
+constexpr int kMarchOwnX = 32, kMarchOwnY = 16;
+constexpr int kMarchThreads = kMarchX * kMarchY;
+// one workgroup per CU, whose chunk is at least kMarchPlanes planes
+constexpr unsigned kMarchBlocks = 256, kMarchPlanes = 8;
+// Levels of at least this many cells are swept so: a V-cycle of 80^3 106 us in
+// place and 111 marching, of 96^3 125 and 120, 128^3 171 and 152, 192^3 309 and
+// 253, 256^3 673 and 546, 320^3 1410 and 1010.
+constexpr size_t kMarchCells = 3 << 18;
+__global__ __launch_bounds__(kMarchThreads) void k_smooth_march(
+    const double* __restrict__ bsrc, const double* __restrict__ f, double* __restrict__ red,
+    double* __restrict__ bdst, Grid g, unsigned tx, unsigned ty, unsigned chunk, double h2) {
+  __shared__ double sh[2][4][kMarchThreads];
+  const unsigned half = g.nx >> 1, ps = half * g.ny, hn = ps * g.nz;
+  const unsigned b = xcd_linear_block(), bz = b / (tx * ty), by = (b - bz * tx * ty) / tx;
+  const unsigned bx = b - bz * tx * ty - by * tx;
+  auto wrap = [](int x, unsigned n) { return (unsigned)(((x % (int)n) + (int)n) % (int)n); };
+  const int t = (int)threadIdx.x, lj = t / kMarchX, lh = t - lj * kMarchX;
+  const int oi = (int)(bx * kMarchOwnX) + lh - 2, oj = (int)(by * kMarchOwnY) + lj - 4;
+  const unsigned j = wrap(oj, g.ny), col = j * half + wrap(oi, half);
+  const int z0 = (int)(bz * chunk);
+  const int z1 = z0 + (int)chunk < (int)g.nz ? z0 + (int)chunk : (int)g.nz;
+  const bool own = lh >= 2 && lh < 2 + kMarchOwnX && lj >= 4 && lj < 4 + kMarchOwnY &&
+                   oi < (int)half && oj < (int)g.ny;
+  // neighbours in the block; at its rim any entry, whose values never reach
+  // the tile
+  const int im = lh > 0 ? t - 1 : t, ip = lh < kMarchX - 1 ? t + 1 : t;
+  const int jm = lj > 0 ? t - kMarchX : t, jp = lj < kMarchY - 1 ? t + kMarchX : t;
+  // planes of the next loads: black K + 1, f of red K, f of black K - 2
+  unsigned kb = wrap(z0 - 3, g.nz), kr = wrap(z0 - 4, g.nz), kf = wrap(z0 - 6, g.nz);
+  double b0 = bsrc[kr * ps + col], b1 = 0.0, b2 = 0.0;       // black as loaded, planes K ..
+  double r1 = 0.0, r2 = 0.0, r3 = 0.0;                       // red after 1, planes K - 2 ..
+  double c1 = 0.0, c2 = 0.0, c3 = 0.0;                       // black after 2, planes K - 4 ..
+  double d1 = 0.0, d2 = 0.0, d3 = 0.0;                       // red after 3, planes K - 6 ..
+  double fr[5] = {}, fb[5] = {};  // h2 f of red, planes K - 1 .., of black, K - 3 ..
+  // five steps an iteration, so that the values' moves from plane to plane are
+  // renamings (the steps past the last plane store nothing)
+  for (int K0 = z0 - 4; K0 < z1 + 7; K0 += 5) {
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+      const int K = K0 + q;
+      double(*L)[kMarchThreads] = sh[K & 1];
+      L[0][t] = b1;
+      L[1][t] = r2;
+      L[2][t] = c2;
+      L[3][t] = d2;
+      __syncthreads();
+      const double nb = (bsrc + (size_t)kb * ps)[col];
+      const double nr = h2 * (f + (size_t)kr * ps)[col];
+      const double nf = h2 * (f + ((size_t)kf * ps + hn))[col];
+      kb = wrap_inc(kb, g.nz);
+      kr = wrap_inc(kr, g.nz);
+      kf = wrap_inc(kf, g.nz);
+      // the four planes have one parity; a red cell of odd column has its
+      // other neighbour in the next pair, a black one's pair the other way round
+      const bool odd = ((j + (unsigned)(K - 1)) & 1u) != 0;
+      const int xr = odd ? ip : im, xb = odd ? im : ip;
+      const double rn = div6((((b1 + L[0][xr]) + (L[0][jm] + L[0][jp])) + (b2 + b0)) - fr[0]);
+      const double cn = div6((((r2 + L[1][xb]) + (L[1][jm] + L[1][jp])) + (r3 + r1)) - fb[0]);
+      const double dn = div6((((c2 + L[2][xr]) + (L[2][jm] + L[2][jp])) + (c3 + c1)) - fr[4]);
+      const double on = div6((((d2 + L[3][xb]) + (L[3][jm] + L[3][jp])) + (d3 + d1)) - fb[4]);
+      if (own && K >= z0 + 7 && K < z1 + 7) {
+        (red + (size_t)(K - 7) * ps)[col] = d2;
+        (bdst + (size_t)(K - 7) * ps)[col] = on;
+      }
+      b2 = b1; b1 = b0; b0 = nb;
+      r3 = r2; r2 = r1; r1 = rn;
+      c3 = c2; c2 = c1; c1 = cn;
+      d3 = d2; d2 = d1; d1 = dn;
+      for (int m = 4; m > 0; --m) {
+        fr[m] = fr[m - 1];
+        fb[m] = fb[m - 1];
+      }
+      fr[0] = nr;
+      fb[0] = nf;
+    }
+  }
+}
+
+// coarse f = mean of the eight children's residuals f - L phi; coarse phi = 0.
+// Red and black cells may lie in different arrays (both indexed by at()).
+__device__ __forceinline__ void restrict_cell(unsigned C, const double* red,
+                                              const double* black, const double* f,
                                               const Grid& g, double inv_h2, const Grid& gc,
                                               double* fc, double* phic) {
   const unsigned I = C % gc.nx, J = (C / gc.nx) % gc.ny, K = C / (gc.nx * gc.ny);
@@ -531,20 +627,23 @@ __device__ __forceinline__ void restrict_cell(unsigned C, const double* phi, con
   for (int q = 0; q < 8; ++q) {
     const unsigned i = 2 * I + (q & 1), j = 2 * J + ((q >> 1) & 1), k = 2 * K + (q >> 2);
     const unsigned c = at(g, i, j, k);
-    const double r = f[c] - (nb_sum(phi, g, i, j, k) - 6.0 * phi[c]) * inv_h2;
+    const bool odd = ((q ^ (q >> 1) ^ (q >> 2)) & 1) != 0;  // the child's colour
+    const double lap = nb_sum(odd ? red : black, g, i, j, k) - 6.0 * (odd ? black : red)[c];
+    const double r = f[c] - lap * inv_h2;
     s = q == 0 ? r : s + r;
   }
   const unsigned a = at(gc, I, J, K);
   fc[a] = 0.125 * s;
   phic[a] = 0.0;
 }
-__global__ __launch_bounds__(kBlock) void k_restrict(const double* __restrict__ phi,
+__global__ __launch_bounds__(kBlock) void k_restrict(const double* __restrict__ red,
+                                                     const double* __restrict__ black,
                                                      const double* __restrict__ f, Grid g,
                                                      double inv_h2, Grid gc,
                                                      double* __restrict__ fc,
                                                      double* __restrict__ phic) {
   const unsigned C = xcd_linear_block() * kBlock + threadIdx.x;
-  if (C < gc.nx * gc.ny * gc.nz) restrict_cell(C, phi, f, g, inv_h2, gc, fc, phic);
+  if (C < gc.nx * gc.ny * gc.nz) restrict_cell(C, red, black, f, g, inv_h2, gc, fc, phic);
 }
 
 // fine phi += trilinear (cell-centred) interpolation of the coarse
@@ -552,7 +651,8 @@ __global__ __launch_bounds__(kBlock) void k_restrict(const double* __restrict__ 
 // once and corrects its eight children; child (a, b, c) takes the parent
 // with weight 27/64, the three face neighbours on its side 9/64, the three
 // edge neighbours 3/64 and the corner 1/64
-__device__ __forceinline__ void prolong_cell(unsigned C, double* phi, const Grid& g,
+__device__ __forceinline__ void prolong_cell(unsigned C, double* red, double* black,
+                                             const Grid& g,
                                              const double* ec, const Grid& gc) {
   unsigned I, J, K;
   coords(gc, C, &I, &J, &K);
@@ -574,13 +674,14 @@ __device__ __forceinline__ void prolong_cell(unsigned C, double* phi, const Grid
                       c111) *
                      (1.0 / 64.0);
     const unsigned f = at(g, 2 * I + a, 2 * J + b, 2 * K + c);
+    double* phi = ((a ^ b ^ c) & 1) != 0 ? black : red;
     phi[f] = phi[f] + v;
   }
 }
-__global__ __launch_bounds__(kBlock) void k_prolong(double* __restrict__ phi, Grid g,
+__global__ __launch_bounds__(kBlock) void k_prolong(double* red, double* black, Grid g,
                                                     const double* __restrict__ ec, Grid gc) {
   const unsigned C = xcd_linear_block() * kBlock + threadIdx.x;
-  if (C < gc.nx * gc.ny * gc.nz) prolong_cell(C, phi, g, ec, gc);
+  if (C < gc.nx * gc.ny * gc.nz) prolong_cell(C, red, black, g, ec, gc);
 }
 
 constexpr int kPre = 2, kPost = 2, kCoarseSweeps = 32;
@@ -602,7 +703,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse(CoarseArgs A) {
     const unsigned n = g.nx * g.ny * g.nz, nc = gc.nx * gc.ny * gc.nz;
     lds_smooth(sphi + o, sf + o, g, A.h2[l], kPre);
     for (unsigned C = threadIdx.x; C < nc; C += kCoarseThreads)
-      restrict_cell(C, sphi + o, sf + o, g, A.inv_h2[l], gc, sf + o + n, sphi + o + n);
+      restrict_cell(C, sphi + o, sphi + o, sf + o, g, A.inv_h2[l], gc, sf + o + n, sphi + o + n);
     __syncthreads();
     o += n;
   }
@@ -612,7 +713,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse(CoarseArgs A) {
     const unsigned nc = gc.nx * gc.ny * gc.nz, oc = o;
     o -= g.nx * g.ny * g.nz;
     for (unsigned C = threadIdx.x; C < nc; C += kCoarseThreads)
-      prolong_cell(C, sphi + o, g, sphi + oc, gc);
+      prolong_cell(C, sphi + o, sphi + o, g, sphi + oc, gc);
     __syncthreads();
     lds_smooth(sphi + o, sf + o, g, A.h2[l], kPost);
   }
@@ -713,6 +814,21 @@ static hipError_t smooth_tile(const Level& v, const double* src, double* dst, hi
   return hipGetLastError();
 }
 
+// two sweeps in one pass, black cells from one array to another
+static hipError_t smooth_march(const Level& v, const double* src, double* dst, hipStream_t s) {
+  const unsigned half = v.g.nx / 2, hn = half * v.g.ny * v.g.nz;
+  const unsigned tx = (half + kMarchOwnX - 1) / kMarchOwnX,
+                 ty = (v.g.ny + kMarchOwnY - 1) / kMarchOwnY;
+  // chunks of equal length, as many as give the chip a workgroup per CU
+  const unsigned want = std::max(1u, kMarchBlocks / std::max(1u, tx * ty));
+  const unsigned nz = std::min(want, std::max(1u, v.g.nz / kMarchPlanes));
+  const unsigned chunk = (v.g.nz + nz - 1) / nz;
+  hipLaunchKernelGGL(k_smooth_march, dim3(tx * ty * ((v.g.nz + chunk - 1) / chunk)),
+                     dim3(kMarchThreads), 0, s, src + hn, v.f, v.phi, dst + hn, v.g, tx, ty, chunk,
+                     v.h2);
+  return hipGetLastError();
+}
+
 static hipError_t vcycle(std::vector<Level>& L, size_t l, hipStream_t s) {
   if (cells(L[l].g) <= kSmallCells) {
     CoarseArgs A{};
@@ -733,14 +849,18 @@ static hipError_t vcycle(std::vector<Level>& L, size_t l, hipStream_t s) {
   Level& c = L[l + 1];
   const bool tiled = cells(f.g) <= kTileCells;
   double* u = tiled ? f.alt : f.phi;  // phi during the coarse correction
-  hipError_t e = tiled ? smooth_tile(f, f.phi, u, s) : smooth(f, kPre, s);
+  const bool march = cells(f.g) >= kMarchCells;
+  double* ub = march ? f.alt : u;        // its black cells
+  hipError_t e = tiled ? smooth_tile(f, f.phi, u, s)
+                       : (march ? smooth_march(f, f.phi, ub, s) : smooth(f, kPre, s));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_restrict, dim3(blocks_for(cells(c.g))), dim3(kBlock), 0, s, u, f.f, f.g,
+  hipLaunchKernelGGL(k_restrict, dim3(blocks_for(cells(c.g))), dim3(kBlock), 0, s, u, ub, f.f, f.g,
                      f.inv_h2, c.g, c.f, c.phi);
   if ((e = vcycle(L, l + 1, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_prolong, dim3(blocks_for(cells(c.g))), dim3(kBlock), 0, s, u, f.g, c.phi,
+  hipLaunchKernelGGL(k_prolong, dim3(blocks_for(cells(c.g))), dim3(kBlock), 0, s, u, ub, f.g, c.phi,
                      c.g);
-  return tiled ? smooth_tile(f, u, f.phi, s) : smooth(f, kPost, s);
+  return tiled ? smooth_tile(f, u, f.phi, s)
+               : (march ? smooth_march(f, ub, f.phi, s) : smooth(f, kPost, s));
 }
 
 // max |f - L phi| of a level into *out
@@ -830,10 +950,12 @@ int nyx_poisson_solve(const int32_t* dom, double dx, double coef, const double* 
     w += r256(cells(G[l]) * sizeof(double));
     h *= 2.0;
   }
-  // Second phi arrays for the tiled smoother: on the finest level the caller's
-  // phi, which after the right-hand side has been set up is not read before
-  // the end; the coarser levels' (together a seventh of its cells) lie in
-  // whichever of the finest level's two arrays is free while they are worked on.
+  // Second phi arrays for the smoothers that need one: on the finest level the
+  // caller's phi, which after the right-hand side has been set up is not read
+  // before the end; the coarser levels' (together a seventh of its cells) lie in
+  // whichever of the finest level's two arrays is free while they are worked on
+  // (the marching smoother uses only the second half of its level's, so the
+  // finest level's black cells and the coarser levels do not meet).
   L[0].alt = phi;
   double* spare = cells(L[0].g) <= kTileCells ? L[0].phi : phi;
   for (size_t l = 1; l < L.size(); ++l) {

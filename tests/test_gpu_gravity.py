@@ -165,6 +165,16 @@ def test_vcycles_equal_their_definition(nyx, dom):
     assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("dom", [(100, 92, 96), (200, 180, 120), (8, 16, 8192), (264, 4, 1024),
+                                 (128, 256, 128)])
+def test_large_vcycles_equal_their_definition(nyx, dom):
+    """The same for domains of 3 2^18 cells and more, whose finest levels are
+    swept in marching tiles of 64 x 16 columns: partial tiles in x and y, a
+    domain smaller than a tile and its halo (8 and 4 across), chunks of unequal
+    length, whole tiles."""
+    test_vcycles_equal_their_definition(nyx, dom)
+
+
 def _resid_ok(r, f, phi, dx, tol):
     """max|r| within tol max|f| plus the rounding of evaluating the 7-point
     residual in another order (terms of size 6 max|phi| / dx^2)."""
