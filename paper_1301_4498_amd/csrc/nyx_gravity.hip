@@ -315,8 +315,8 @@ __device__ __forceinline__ double div6(double x) {
 // one Gauss-Seidel half sweep: cells with (i + j + k) % 2 == color.  Bound by
 // memory (12 bytes a cell: 41 us at 256^3, 4.9 TB/s).  Workgroups are numbered
 // XCD by XCD, here and in the kernels below: the rows and planes beside a cell
-// are then read through the L2 that holds them (256^3: 42 us in launch order,
-// the residual's maximum 89 and 79, a solve 8045 and 7720).
+// are then read through the L2 that holds them (256^3 in place: 42 us in launch
+// order, the residual's maximum 89 and 79, a solve 8045 and 7720).
 __global__ __launch_bounds__(kBlock) void k_rbgs(double* __restrict__ phi,
                                                  const double* __restrict__ f, Grid g, double h2,
                                                  unsigned color) {
@@ -363,7 +363,8 @@ __device__ __forceinline__ double pair_sum(const double* other, const Pair& p, u
 
 // max |f - L phi|: one lane per pair of cells.  Bound by memory (16 bytes a
 // cell): 97 us at 256^3 with a lane per cell, its coordinates divided out, 89
-// with pairs, 79 with the workgroups numbered XCD by XCD.
+// with pairs, 79 with the workgroups numbered XCD by XCD, 92 behind the marching
+// smoother, which passes over more memory than the chip's last cache holds.
 __global__ __launch_bounds__(kBlock) void k_resid_max(const double* __restrict__ phi,
                                                       const double* __restrict__ f, Grid g,
                                                       FastDiv dh, FastDiv dy, double inv_h2,

@@ -74,9 +74,13 @@ __global__ void k_mlp_init(float* P, unsigned long long seed) {
 // The weights a wave needs stay in its registers (one 16-row tile of each
 // matrix and of its transpose), activations and deltas live in LDS as
 // [sample][feature] rows of kRow floats: a lane's four elements of D are four
-// neighbouring features (one 16-byte store), and the sums over features read
-// four neighbouring features per 16-byte load; with kRow = 68 neither these
-// nor the gradients' reads, which walk the samples, meet in a bank.  The
+// neighbouring places (one 16-byte store), and the sums over features read
+// four neighbouring places per 16-byte load; with kRow = 68 neither these
+// nor the gradients' reads, which walk the samples, meet in a bank.  Place p
+// of a row holds feature feat(p): the four steps that use one 16-byte load then
+// take the features 4 apart that make every sum run through its features in
+// order, from the bias on, as a plain loop does; a hidden unit near zero is
+// then on or off as it is there.  The
 // gradients accumulate in registers over all tiles of a workgroup and are
 // added to memory once at its end, 9349 atomics per workgroup.
 // What bounds it: up to one tile per CU the latency of a tile's nine
@@ -102,12 +106,15 @@ struct GradLds {
   float loss[kGradWaves];
 };
 
+// feature at place p of a row: each block of 16 as a transposed 4 x 4
+__device__ __forceinline__ int feat(int p) { return (p & ~15) + 4 * (p & 3) + (p >> 2 & 3); }
+
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
 // acc[t] += sum over 64 features of A (this wave's rows; element 4 q + r is
-// feature 16 q + 4 (l/16) + r) and the rows of samples s0 + 16 t of `rows`
+// place 16 q + 4 (l/16) + r) and the rows of samples s0 + 16 t of `rows`
 __device__ __forceinline__ void mm64(const f32x4* a, const float* rows, int s0, f32x4* acc) {
   const int l = threadIdx.x & 63, g = l >> 4, c = l & 15;
 #pragma unroll
@@ -168,24 +175,26 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_loss_grad(const float* __r
   // weights of this wave's rows: forward (row ot + c) and transposed
   f32x4 a1, a2[4], a3[4], a4[4], t2[4], t3[4];
   float t4[2];
+  const int fc = ot + feat(c);
   for (int r = 0; r < 4; ++r) {
-    const int k = 4 * g + r;
-    a1[r] = k < kMlpIn ? P[kOffW1 + (ot + c) * kMlpIn + k] : (k == kMlpIn ? P[kOffB1 + ot + c] : 0.0f);
+    const int k = feat(4 * g + r);
+    a1[r] = k < kMlpIn ? P[kOffW1 + fc * kMlpIn + k] : 0.0f;
   }
   for (int q = 0; q < 4; ++q)
     for (int r = 0; r < 4; ++r) {
-      const int k = 16 * q + 4 * g + r;
-      a2[q][r] = P[kOffW2 + (ot + c) * kMlpHid + k];
-      a3[q][r] = P[kOffW3 + (ot + c) * kMlpHid + k];
+      const int k = feat(16 * q + 4 * g + r);
+      a2[q][r] = P[kOffW2 + fc * kMlpHid + k];
+      a3[q][r] = P[kOffW3 + fc * kMlpHid + k];
       a4[q][r] = c < kMlpOut ? P[kOffW4 + c * kMlpHid + k] : 0.0f;
-      t2[q][r] = P[kOffW2 + k * kMlpHid + ot + c];
-      t3[q][r] = P[kOffW3 + k * kMlpHid + ot + c];
+      t2[q][r] = P[kOffW2 + k * kMlpHid + fc];
+      t3[q][r] = P[kOffW3 + k * kMlpHid + fc];
     }
-  for (int t = 0; t < 2; ++t) t4[t] = 4 * t + g < kMlpOut ? P[kOffW4 + (4 * t + g) * kMlpHid + ot + c] : 0.0f;
-  f32x4 bias2, bias3, bias4;
+  for (int t = 0; t < 2; ++t) t4[t] = 4 * t + g < kMlpOut ? P[kOffW4 + (4 * t + g) * kMlpHid + fc] : 0.0f;
+  f32x4 bias1, bias2, bias3, bias4;
   for (int v = 0; v < 4; ++v) {
-    bias2[v] = P[kOffB2 + ot + 4 * g + v];
-    bias3[v] = P[kOffB3 + ot + 4 * g + v];
+    bias1[v] = P[kOffB1 + feat(ot + 4 * g + v)];
+    bias2[v] = P[kOffB2 + feat(ot + 4 * g + v)];
+    bias3[v] = P[kOffB3 + feat(ot + 4 * g + v)];
     bias4[v] = 4 * g + v < kMlpOut ? P[kOffB4 + 4 * g + v] : 0.0f;
   }
   const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -207,7 +216,7 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_loss_grad(const float* __r
       for (int k = 0; k < kMlpOut; ++k) valid = valid && fabsf(y[k]) <= kMlpDomain;
     }
     for (int k = 0; k < 16; ++k)
-      S.x[tid * kXRow + k] = k < kMlpIn ? (valid ? x[k] : 0.0f) : (k == kMlpIn ? 1.0f : 0.0f);
+      S.x[tid * kXRow + feat(k)] = k < kMlpIn ? (valid ? x[k] : 0.0f) : (k == kMlpIn ? 1.0f : 0.0f);
     for (int k = 0; k < kMlpOut; ++k) S.y[tid * 8 + k] = valid ? y[k] : 0.0f;
     S.y[tid * 8 + kMlpOut] = valid ? 1.0f : 0.0f;
     __syncthreads();
@@ -219,7 +228,7 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_loss_grad(const float* __r
       // forward
       for (int t = 0; t < 2; ++t) {
         const f32x4 b = *(const f32x4*)(X + (s0 + 16 * t + c) * kXRow + 4 * g);
-        acc[t] = zero;
+        acc[t] = bias1;
         for (int r = 0; r < 4; ++r) acc[t] = mfma4(a1[r], b[r], acc[t]);
         *(f32x4*)(S.h[0] + (s0 + 16 * t + c) * kRow + ot + 4 * g) = relu4(acc[t]);
       }
@@ -284,7 +293,7 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_loss_grad(const float* __r
       }
       grad64(S.d[1], kRow, ot, S.h[0], kRow, it0, 2, dw2, w >= 4 ? &db : nullptr);
       __syncthreads();
-      // input layer: columns 0..9 its weights' gradient, column 10 the bias's
+      // input layer: features 0..9 its weights' gradient, feature 10 the bias's
       if (w < 4) grad64(S.d[0], kRow, ot, X, kXRow, 0, 1, &dw14, nullptr);
       __syncthreads();
     }
@@ -295,18 +304,18 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_loss_grad(const float* __r
   float* G = S.x;  // the inputs are no longer needed (the loop ends with a barrier)
   static_assert(kGradChunk * kXRow >= kMlpNParam, "gradient fits the input area");
   for (int v = 0; v < 4; ++v) {
-    const int o = ot + 4 * g + v;  // gradient row of this lane
+    const int o = feat(ot + 4 * g + v), ci = feat(c);  // gradient row and column of this lane
     for (int t = 0; t < 2; ++t) {
-      G[kOffW3 + o * kMlpHid + it0 + 16 * t + c] = dw3[t][v];
-      G[kOffW2 + o * kMlpHid + it0 + 16 * t + c] = dw2[t][v];
+      G[kOffW3 + o * kMlpHid + it0 + 16 * t + ci] = dw3[t][v];
+      G[kOffW2 + o * kMlpHid + it0 + 16 * t + ci] = dw2[t][v];
     }
     if (w < 4) {
-      if (c < kMlpIn) G[kOffW1 + o * kMlpIn + c] = dw14[v];
-      else if (c == kMlpIn) G[kOffB1 + o] = dw14[v];
+      if (ci < kMlpIn) G[kOffW1 + o * kMlpIn + ci] = dw14[v];
+      else if (ci == kMlpIn) G[kOffB1 + o] = dw14[v];
       if (c == 0) G[kOffB3 + o] = db[v];
     } else {
       const int k = 4 * g + v;
-      if (k < kMlpOut) G[kOffW4 + k * kMlpHid + ot + c] = dw14[v];
+      if (k < kMlpOut) G[kOffW4 + k * kMlpHid + fc] = dw14[v];
       if (c == 0) G[kOffB2 + o] = db[v];
       if (w == 4 && c == 0 && k < kMlpOut) G[kOffB4 + k] = db4[v];
     }
