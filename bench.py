@@ -165,8 +165,9 @@ def roofline_of(stage_ms, table, shapes, iters, step_ms, grav_bytes, form, workl
     return roof, hbm
 
 
-# the fused launch mode's kernels: "front" = trace + riem0 (k_front),
-# "final" = riem2 + update (k_final)
+# the fused launch mode's kernels: "front" = trace + riem0 (where flat and trace
+# run as one launch, k_edges, flat's own time is 0), "final" = riem2 + update
+# (k_final)
 FUSED_STAGES = ("prim", "flat", "front", "riem1", "final")
 FUSED_PARTS = {"front": ("trace", "riem0"), "final": ("riem2", "update")}
 
