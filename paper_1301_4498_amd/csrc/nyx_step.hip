@@ -347,21 +347,38 @@ __global__ __launch_bounds__(kBlock) void k_flat(StepArgs A) { flat_body(A, laun
 // stage 3: PPM (O3) and characteristic tracing (O4)
 // ---------------------------------------------------------------------------
 #if defined(NYX_PREC_MIXED)
-// Half the limited slope, h = minmod((q(j+1) - q(j-1)) / 4, q(j) - q(j-1),
-// q(j+1) - q(j)), as two medians: med(0, a, b) is the smaller of a and b where
-// they share a sign and 0 where they do not, and the centred difference has
-// the sign the one-sided ones share.  Scaling by 2 and 1/4 is exact, so 2 h is
-// the limited slope's own value (up to the sign of a zero slope and slopes
-// below the FP32 normal range): 4 instructions per slope where the clamped
-// minimum with its sign transfers took 9.
+// The limited slope as a clamped minimum: with s the sign of d2 = q(j+1) -
+// q(j-1), min(|dc|, 2|dl|, 2|dr|) = 2 min(|d2|/4, s dl, s dr) when dl dr > 0
+// (then dl, dr and d2 share their sign), and that minimum is <= 0 otherwise,
+// so clamping it at 0 gives the limiter's zero slope.
+__device__ __forceinline__ real lim_slope(real qm1, real q0, real qp1) {
+  const real d2 = qp1 - qm1;
+  const real dr = qp1 - q0;
+  const real dl = q0 - qm1;
+  const unsigned sg = __float_as_uint(d2) & 0x80000000u;
+  const real sdl = __uint_as_float(__float_as_uint(dl) ^ sg);
+  const real sdr = __uint_as_float(__float_as_uint(dr) ^ sg);
+  const real m = (real)2 * fmaxf(fminf(fminf((real)0.25 * fabsf(d2), sdl), sdr), (real)0);
+  return __uint_as_float(__float_as_uint(m) | sg);
+}
+// Half of it, h = minmod((q(j+1) - q(j-1)) / 4, q(j) - q(j-1), q(j+1) - q(j)),
+// as two medians: med(0, a, b) is the smaller of a and b where they share a
+// sign and 0 where they do not, and the centred difference has the sign the
+// one-sided ones share.  Scaling by 2 and 1/4 is exact, so 2 h is the limited
+// slope's own value (up to the sign of a zero slope and slopes below the FP32
+// normal range): 4 instructions per slope where the clamped minimum with its
+// sign transfers takes 9.  For values below kMedTop only: a median drops NaN
+// otherwise than the minimum does, and the minimum's doubled slope can overflow.
+constexpr real kMedTop = 0x1p125f;
+// the larger magnitude, NaN where either is
+__device__ __forceinline__ real max_mag(real a, real b) {
+  return __builtin_elementwise_maximum(fabsf(a), fabsf(b));
+}
 __device__ __forceinline__ real med3(real a, real b, real c) {
   return __builtin_amdgcn_fmed3f(a, b, c);
 }
 __device__ __forceinline__ real half_slope(real qm1, real q0, real qp1) {
   return med3((real)0, (real)0.25 * (qp1 - qm1), med3((real)0, q0 - qm1, qp1 - q0));
-}
-__device__ __forceinline__ real lim_slope(real qm1, real q0, real qp1) {
-  return (real)2 * half_slope(qm1, q0, qp1);
 }
 #else
 // Under dr dl > 0 neither dl nor dr is NaN, so fmin (one instruction) takes
@@ -387,66 +404,55 @@ __device__ __forceinline__ real ppm_face(real qa, real qb, real sa, real sb) {
   return (qa + (real)0.5 * (qb - qa)) - quot(sb - sa, make_recip(6.0));
 #endif
 }
-// edge values of the cell of q5[2] after flattening, before the monotonicity
-// limits
-__device__ __forceinline__ void ppm_flat(const real* q5, real chi, real& qm_o, real& qp_o) {
+// PPM edges of the cell of q5[2]: interface values from the slopes of cells
+// j-1, j, j+1 (each computed once), flattened, then the monotonicity limits of
+// the parabola (CW84 eq. 1.10).  med: the mixed build's slopes as medians.
+__device__ __forceinline__ void ppm_edges(const real* q5, bool med, real chi, real& qm_o,
+                                          real& qp_o) {
   const real qj = q5[2];
-  // slopes of cells j-1, j, j+1, each computed once
+  real h[3];
 #if defined(NYX_PREC_MIXED)
-  const real sm = half_slope(q5[0], q5[1], q5[2]);
-  const real s0 = half_slope(q5[1], q5[2], q5[3]);
-  const real sp = half_slope(q5[2], q5[3], q5[4]);
+  for (int k = 0; k < 3; ++k) h[k] = half_slope(q5[k], q5[k + 1], q5[k + 2]);
+  if (!med) {
+    asm volatile("");  // rare: a branch of its own
+    for (int k = 0; k < 3; ++k) h[k] = (real)0.5 * lim_slope(q5[k], q5[k + 1], q5[k + 2]);
+  }
 #else
-  const real sm = lim_slope(q5[0], q5[1], q5[2]);
-  const real s0 = lim_slope(q5[1], q5[2], q5[3]);
-  const real sp = lim_slope(q5[2], q5[3], q5[4]);
+  for (int k = 0; k < 3; ++k) h[k] = lim_slope(q5[k], q5[k + 1], q5[k + 2]);
 #endif
-  const real qp = ppm_face(q5[2], q5[3], s0, sp);
-  const real qm = ppm_face(q5[1], q5[2], sm, s0);
-  qp_o = chi * qp + ((real)1 - chi) * qj;
-  qm_o = chi * qm + ((real)1 - chi) * qj;
-}
-// monotonicity limits of the parabola (CW84 eq. 1.10)
-__device__ __forceinline__ void ppm_limit(real qj, real& qm, real& qp) {
+  real qp = ppm_face(q5[2], q5[3], h[1], h[2]);
+  real qm = ppm_face(q5[1], q5[2], h[0], h[1]);
+  qp = chi * qp + ((real)1 - chi) * qj;
+  qm = chi * qm + ((real)1 - chi) * qj;
+#if defined(NYX_PREC_MIXED)
+  // Selects of the limits' own comparisons (t > s and -s > t exclude each
+  // other).  In exact arithmetic the limited edges are the medians of q_j, the
+  // edge and its limit, at a third of the instructions, but not in FP32: where
+  // the limit and the edge agree to rounding the median takes the other value,
+  // and where dq dq overflows (velocities of floored cells) it limits an edge
+  // that the comparison leaves.  64 shocked 64^3 patches: 5217 us a step with
+  // the medians, 5264 with the selects (5300 with the check of the slopes' range).
+  const bool flat = (qp - qj) * (qj - qm) <= (real)0;
+  const real dq = qp - qm;
+  const real t = dq * (qj - (real)0.5 * (qm + qp));
+  const real s = dq * dq * (real)(1.0 / 6.0);
+  const real lm = (real)3 * qj - (real)2 * qp, lp = (real)3 * qj - (real)2 * qm;
+  qm_o = flat ? qj : (t > s ? lm : qm);
+  qp_o = flat ? qj : (-s > t ? lp : qp);
+#else
   if ((qp - qj) * (qj - qm) <= (real)0) {
     qp = qj;
     qm = qj;
   } else {
-    real dq = qp - qm;
-    real t = dq * (qj - (real)0.5 * (qm + qp));
-#if defined(NYX_PREC_MIXED)
-    real s = dq * dq * (real)(1.0 / 6.0);
-#else
-    real s = quot(dq * dq, make_recip(6.0));
-#endif
+    const real dq = qp - qm;
+    const real t = dq * (qj - (real)0.5 * (qm + qp));
+    const real s = quot(dq * dq, make_recip(6.0));
     if (t > s) qm = (real)3 * qj - (real)2 * qp;
     else if (-s > t) qp = (real)3 * qj - (real)2 * qm;
   }
-}
-#if defined(NYX_PREC_MIXED)
-// The same limits as two medians.  With a = q+ - q_j and b = q_j - q- of one
-// sign, t > s says b > 2a: the limit 3 q_j - 2 q+ = q_j - 2a then lies between
-// q_j and q-; otherwise q- lies nearer.  Where a and b differ in sign, q- and
-// the limit lie on either side of q_j and the median is q_j, the flat value.
-// Likewise for q+.  Finite edges only (a median drops NaN).
-__device__ __forceinline__ void ppm_limit_med(real qj, real& qm, real& qp) {
-  const real lm = (real)3 * qj - (real)2 * qp, lp = (real)3 * qj - (real)2 * qm;
-  qm = med3(qj, qm, lm);
-  qp = med3(qj, qp, lp);
-}
+  qm_o = qm;
+  qp_o = qp;
 #endif
-// PPM edges of the five variables of a cell
-__device__ __forceinline__ void ppm_cell(const real (*qs)[5], real chi, real* qm, real* qp) {
-  for (int v = 0; v < 5; ++v) ppm_flat(qs[v], chi, qm[v], qp[v]);
-#if defined(NYX_PREC_MIXED)
-  real sum = (real)0;  // finite where every edge is
-  for (int v = 0; v < 5; ++v) sum += fabsf(qm[v]) + fabsf(qp[v]);
-  if (sum <= 3.402823466e+38f) {
-    for (int v = 0; v < 5; ++v) ppm_limit_med(qs[v][2], qm[v], qp[v]);
-    return;
-  }
-#endif
-  for (int v = 0; v < 5; ++v) ppm_limit(qs[v][2], qm[v], qp[v]);
 }
 // PLM variant (Sec. 3.2): the limited centred slope times the flattening
 // coefficient gives the edge values q_j -/+ ds/2 (the tracing below then
@@ -538,10 +544,11 @@ __device__ __forceinline__ void trace_side(const real* qc, real c, const real* q
 // + 2], its flattening coefficient, sound speed and gravity: the low- and
 // high-side edge states after the half-step sources and the floors, in lo and
 // hi; returns the floors applied.  Instantiated per direction, so component
-// choices are compile-time constants.
+// choices are compile-time constants.  med: every stencil value lies below
+// kMedTop (mixed build).
 template <int D>
 __device__ __forceinline__ unsigned trace_core(const StepArgs& A, const StepC& C,
-                                               const real (*qs)[5], real chi, real c,
+                                               const real (*qs)[5], bool med, real chi, real c,
                                                const real* g, real* lo, real* hi) {
   constexpr int d = D;
   unsigned floors = 0;
@@ -549,7 +556,7 @@ __device__ __forceinline__ unsigned trace_core(const StepArgs& A, const StepC& C
   if (A.recon == NYX_RECON_PLM) {
     for (int v = 0; v < 5; ++v) plm_edges(qs[v], chi, qm[v], qp[v]);
   } else {
-    ppm_cell(qs, chi, qm, qp);
+    for (int v = 0; v < 5; ++v) ppm_edges(qs[v], med, chi, qm[v], qp[v]);
   }
   for (int v = 0; v < 5; ++v) {
     qc[v] = qs[v][2];
@@ -595,7 +602,14 @@ __device__ __forceinline__ unsigned trace_cell(const StepArgs& A, const BoxDev& 
   const real c = ldw(prim + 5 * b.P, c0);
   const real* G = (const real*)A.grav + b.goff;
   const real g[3] = {ldw(G, c0), ldw(G + b.gstride, c0), ldw(G + 2 * b.gstride, c0)};
-  return trace_core<D>(A, C, qs, chi, c, g, lo, hi);
+  bool med = true;
+#if defined(NYX_PREC_MIXED)
+  real top = (real)0;
+  for (int v = 0; v < 5; ++v)
+    for (int o = 0; o < 5; ++o) top = max_mag(top, qs[v][o]);
+  med = top < kMedTop;
+#endif
+  return trace_core<D>(A, C, qs, med, chi, c, g, lo, hi);
 }
 template <int D>
 __device__ __forceinline__ void store_edges(const StepArgs& A, const BoxDev& b, unsigned e,
@@ -645,11 +659,14 @@ __global__ __launch_bounds__(kBlock) void k_trace(StepArgs A) { trace_body(A, la
 // loads and the 30 stores of the edge states.  64 shocked 64^3 patches: 791 us
 // at 4.5 TB/s (vector issue 77%) against 171 us of flattening and the tracing
 // behind it, the whole step 5610 -> 5200 us; 256^3 5215 -> 4915.
+// 128 VGPRs (two workgroups a CU) need the slopes' general form in branches of
+// its own: both forms side by side took 144, one workgroup.
 // Neighbouring tiles in x are launched next to each other, so that the cache
 // lines that their rows share are completed in one L2 (256^3 with y first: 5450).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kEdgeBlock) void k_edges(StepArgs A) {
+__global__ __launch_bounds__(kEdgeBlock, 4) void k_edges(StepArgs A) {
   __shared__ real pl[5 * kEdgeLds];
+  __shared__ int high;  // a value of kMedTop or more has been loaded
   const int lin = (int)xcd_linear_block(true);
   const int* pre = A.prefix[kSpaceF];
   int lo_ = 0, hi_ = A.nb;
@@ -716,6 +733,15 @@ __global__ __launch_bounds__(kEdgeBlock) void k_edges(StepArgs A) {
   for (int k = 0; k < 2; ++k)
     if (hl[k] >= 0)
       for (int v = 0; v < 5; ++v) halo[k][v] = ldw(prim + v * b.P, hg[k]);
+  if (t == 0) high = 0;
+  __syncthreads();
+  {
+    real top = (real)0;
+    for (int v = 0; v < 4; ++v)
+      for (int o = 0; o < 5; ++o) top = max_mag(top, col[v][o]);
+    for (int o = 1; o < 6; ++o) top = max_mag(top, pz[o]);
+    if (!(top < kMedTop)) high = 1;
+  }
   unsigned floors = 0;
   for (int z = z0; z < z1; ++z) {
     if (lane) {
@@ -723,9 +749,16 @@ __global__ __launch_bounds__(kEdgeBlock) void k_edges(StepArgs A) {
       pl[4 * kEdgeLds + li] = pz[3];
     }
     for (int k = 0; k < 2; ++k)
-      if (hl[k] >= 0)
-        for (int v = 0; v < 5; ++v) pl[v * kEdgeLds + hl[k]] = halo[k][v];
+      if (hl[k] >= 0) {
+        real top = (real)0;
+        for (int v = 0; v < 5; ++v) {
+          pl[v * kEdgeLds + hl[k]] = halo[k][v];
+          top = max_mag(top, halo[k][v]);
+        }
+        if (!(top < kMedTop)) high = 1;
+      }
     __syncthreads();
+    const bool med = __builtin_amdgcn_readfirstlane(high) == 0;
     // the next plane's values are on their way during this plane's arithmetic
     const real c = cg[0], g[3] = {cg[1], cg[2], cg[3]};
     real nc[4] = {}, np = (real)0;
@@ -757,17 +790,17 @@ __global__ __launch_bounds__(kEdgeBlock) void k_edges(StepArgs A) {
       real qs[5][5], lo[5], hi[5];
       for (int v = 0; v < 5; ++v)
         for (int o = -2; o <= 2; ++o) qs[v][o + 2] = pl[v * kEdgeLds + li + o];
-      floors += trace_core<0>(A, C, qs, chi, c, g, lo, hi);
+      floors += trace_core<0>(A, C, qs, med, chi, c, g, lo, hi);
       store_edges<0>(A, b, e, lo, hi);
       for (int v = 0; v < 5; ++v)
         for (int o = -2; o <= 2; ++o) qs[v][o + 2] = pl[v * kEdgeLds + li + o * LX];
-      floors += trace_core<1>(A, C, qs, chi, c, g, lo, hi);
+      floors += trace_core<1>(A, C, qs, med, chi, c, g, lo, hi);
       store_edges<1>(A, b, e, lo, hi);
       for (int o = -2; o <= 2; ++o) {
         for (int v = 0; v < 4; ++v) qs[v][o + 2] = col[v][o + 2];
         qs[4][o + 2] = pz[o + 3];
       }
-      floors += trace_core<2>(A, C, qs, chi, c, g, lo, hi);
+      floors += trace_core<2>(A, C, qs, med, chi, c, g, lo, hi);
       store_edges<2>(A, b, e, lo, hi);
     }
     for (int v = 0; v < 4; ++v) {
@@ -776,6 +809,7 @@ __global__ __launch_bounds__(kEdgeBlock) void k_edges(StepArgs A) {
     }
     for (int o = 0; o < 6; ++o) pz[o] = pz[o + 1];
     pz[6] = np;
+    if (!(max_mag(max_mag(max_mag(nc[0], nc[1]), max_mag(nc[2], nc[3])), pz[5]) < kMedTop)) high = 1;
     e += (unsigned)b.ex * (unsigned)b.ey;
     __syncthreads();
   }

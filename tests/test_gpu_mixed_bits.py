@@ -1,0 +1,99 @@
+"""The FP32-mixed step's result bits, pinned on inputs where rewriting an FP32
+expression into one that is equal in exact arithmetic shows: parabolas whose
+monotonicity limit and edge agree to rounding, velocities near 1e20 (a floored
+cell's) whose squared edge differences overflow, and NaN and infinite cells.
+The digests are of the step with the limits as comparisons and the slopes as
+clamped minima (cells beside a NaN included).  One box takes flattening and
+tracing as separate kernels, one as the marching pass."""
+import hashlib
+
+import numpy as np
+import pytest
+
+from gpu_harness import NG, aligned_ws, to_dev
+from paper_1301_4498_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# densities of five neighbouring cells (FP32 values) whose middle parabola's
+# limit is within rounding of its edge
+TIES = [
+    (0.981012523, 1.57682848, 1.73675334, 1.89667833, 1.02416885),
+    (1.46500885, 1.20545113, 1.03864956, 1.0027467, 1.90418005),
+    (4.36245251, 2.2700758, 1.91378284, 1.30937791, 0.673226953),
+    (1.75857341, 1.10645032, 1.54449534, 1.76703966, 1.89591992),
+    (1.16632426, 0.518385351, 0.56394136, 0.863281429, 1.63108504),
+    (2.03633046, 0.225429878, 0.514221549, 1.26507998, 0.514289558),
+    (0.718430281, 1.66217494, 1.69502079, 1.70323241, 1.97635508),
+    (1.2771157, 0.718861282, 0.822803974, 1.15542376, 1.23858285),
+    (1.47356558, 0.706299782, 1.14944315, 1.42708087, 1.84623086),
+    (2.25946188, 0.433362812, 0.636743784, 0.840124547, 2.78529167),
+    (1.42007792, 0.818296134, 0.953231514, 1.08816695, 1.80859387),
+    (0.847707868, 0.685203314, 0.517548025, 0.475312322, 0.64812386),
+]
+
+
+def _input(n, kind):
+    """Integer-made fields (no generator's stream enters): density and velocity
+    on a lattice of 1/128, uniform pressure, with the kind's cells put in."""
+    nx, ny, nz = n
+    k, j, i = np.meshgrid(np.arange(nz), np.arange(ny), np.arange(nx), indexing="ij")
+    h = (i * 7919 + j * 104729 + k * 1299709) % 1009
+    rho = 1.0 + (h % 64) / 128.0
+    m = np.stack([rho * (((h * (c + 3)) % 61) - 30) / 128.0 for c in range(3)])
+    if kind == "ties":
+        for q, t in enumerate(TIES):
+            row = np.float64(np.float32(t))
+            rho[3 + q % 5, 2 + q % 7 * 3, 4:9] = row
+            rho[9 + q % 4, 6:11, 3 + q * 2] = row
+            rho[14:19, 4 + q, 20 + q % 3 * 3] = row
+        m *= 0.0
+    re = np.full(rho.shape, 0.25 * 0.9)
+    U = np.stack([rho, *m, re + 0.5 * (m ** 2).sum(0) / rho, re])
+    at = [(5 * q % nz, 11 * q % ny, 7 * q % nx) for q in range(1, 9)]
+    for q, c in enumerate(at):
+        if kind == "fast":
+            U[(1 + q % 3,) + c] = 0.7e20 * (1.0 + q / 8.0) * (-1.0) ** q
+        elif kind == "nan":
+            U[(q % 6,) + c] = np.nan
+        elif kind == "inf":
+            U[(q % 6,) + c] = np.inf
+    g = np.stack([((h + c) % 17 - 8) / 128.0 for c in range(3)])
+    return synth.pad_periodic(U), synth.pad_periodic(g)
+
+
+def step_digest(nyx, n, kind):
+    import torch
+    U, g = _input(n, kind)
+    prm = nyx.default_params(precision=nyx.NYX_MIXED)
+    box = nyx.make_box(n, NG, 1.0 / 64)
+    A, G = to_dev(U), to_dev(g, torch.float32)
+    B = torch.zeros_like(A)
+    nyx.hydro_step(prm, box, A, G, 1e-4 if kind != "fast" else 1e-22, 0.5, 0.5005, B,
+                   workspace=aligned_ws(nyx.workspace_bytes(prm, box)))
+    out = B.cpu().numpy()[:, NG:-NG, NG:-NG, NG:-NG] + 0.0
+    out = np.where(np.isnan(out), np.nan, out)
+    return hashlib.sha256(np.ascontiguousarray(out).tobytes()).hexdigest()[:16]
+
+
+SMALL, LARGE = (34, 30, 26), (112, 110, 114)
+BITS = {
+    (SMALL, "ties"): "4f79ead6a66da113",
+    (SMALL, "fast"): "3eadcc0203613207",
+    (SMALL, "nan"): "07efec04b5b03454",
+    (SMALL, "inf"): "1226dd271ff73f42",
+    (LARGE, "ties"): "a3c4c31506246ea3",
+    (LARGE, "fast"): "679fa1f80ac07586",
+    (LARGE, "nan"): "fbe8cc18acf2c0f4",
+    (LARGE, "inf"): "6cbe697c9fb1742c",
+}
+
+
+@pytest.mark.parametrize("kind", ["ties", "fast", "nan", "inf"])
+@pytest.mark.parametrize("n", [SMALL, LARGE])
+def test_mixed_step_bits(n, kind):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1301_4498_amd as nyx
+    assert step_digest(nyx, n, kind) == BITS[n, kind]
