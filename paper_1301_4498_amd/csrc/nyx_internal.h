@@ -293,6 +293,7 @@ __device__ __forceinline__ unsigned long long wave_base(const void* p) {
 // A descriptor that no kernel of the step writes while it runs (a box, its
 // step constants), through a scalar pointer into the constant address space:
 // its reads stay scalar loads, also behind branches and the stage's stores.
+// The same object in every lane of the wavefront: the first lane's is read.
 template <class T>
 __device__ __forceinline__ const T& scalar_ref(const T& r) {
   return *(const T*)(const T __attribute__((address_space(4)))*)wave_base(&r);

@@ -141,7 +141,8 @@ __device__ __forceinline__ Loc locate(const StepArgs& A, int stage, int space, c
 #define NYX_REAL(x) x
 #endif
 
-// per-box constants of the step, computed once per box by the prologue
+// per-box constants of the step, computed once per box by the prologue; b is the
+// same box in every lane of the wavefront
 __device__ __forceinline__ const StepC& step_consts(const StepArgs& A, const BoxDev& b) {
   return scalar_ref(A.consts[b.gidx]);
 }
@@ -2347,7 +2348,7 @@ __global__ __launch_bounds__(kBlock) void k_flux_record(StepArgs A, const BoxDev
   if (r >= nrec) return;
   const FluxRec R = recs[r];
   const BoxDev& b = table[R.box];
-  const StepC& C = step_consts(A, b);
+  const StepC& C = A.consts[b.gidx];  // per lane: a wavefront's records may be of several boxes
   const int d = R.d;
   const unsigned e = ((unsigned)(R.f[2] + 1) * (unsigned)b.ey + (unsigned)(R.f[1] + 1)) *
                          (unsigned)b.ex + (unsigned)(R.f[0] + 1);

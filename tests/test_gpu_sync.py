@@ -266,6 +266,47 @@ def test_fp64_fine_level_covering_the_domain(nyx):
     for a, b in zip(got_c, csync):
         assert np.array_equal(_valid(a), _valid(b))
 
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_flux_register_of_boxes_with_their_own_dt(nyx, prec):
+    """Boxes small enough that several share a wavefront of flux records (at
+    most 40 each), every box with a dt of its own: the register of a plan in one
+    group equals that of one-box groups, whose wavefronts hold one box."""
+    import torch
+    rng = np.random.default_rng(36)
+    cdom, dom = (16, 16, 16), (32, 32, 32)
+    cboxes = [((4, 8, 8), (4 * x, 8 * y, 8 * z)) for z in (0, 1) for y in (0, 1) for x in range(4)]
+    fboxes = [((4, 4, 8), (4 + 8 * (q % 3), 4 + 12 * (q // 3 % 2), 6 + 14 * (q // 6)))
+              for q in range(9)]
+    cboxes, cdatas, fboxes, fdatas, cdom, dom = _fields(rng, cboxes, fboxes, cdom, dom)
+    cb, cflat, cg = _pack(nyx, cboxes, cdatas, 1.0 / cdom[0])
+    fb, fflat, fg = _pack(nyx, fboxes, fdatas, 1.0 / dom[0])
+    clo, flo = [lo for _, lo in cboxes], [lo for _, lo in fboxes]
+    p = nyx.NYX_FP64 if prec == "fp64" else nyx.NYX_MIXED
+    prm = nyx.default_params(precision=p)
+    gdt = torch.float64 if prec == "fp64" else torch.float32
+    cst, fst = to_dev(cflat), to_dev(fflat)
+    nyx.FillPlan(cb, clo, cdom).fill(cst)
+    nyx.FillPlan(fb, flo, dom, coarse=(cb, clo)).fill(fst, cst)
+    sync = nyx.SyncPlan((fb, flo), (cb, clo), dom)
+    for level, boxes, st, ng in ((0, cb, cst, cg), (1, fb, fst, fg)):
+        grav = torch.zeros(ng, dtype=gdt, device="cuda")
+        dt = 1e-3 * (1.0 + torch.arange(len(boxes), dtype=torch.float64, device="cuda"))
+        regs = []
+        mn, one = nyx.Batch.workspace_bytes(prm, boxes)
+        for ws in (one, mn):
+            plan = nyx.Batch(prm, boxes, aligned_ws(ws))
+            assert plan.num_groups == (1 if ws == one else len(boxes))
+            reg = sync.register()
+            plan.set_flux_register(sync, level, reg)
+            plan.step(st, grav, dt, 0.5, 0.505, torch.empty_like(st))
+            torch.cuda.synchronize()
+            regs.append(reg.cpu().numpy())
+            plan.set_flux_register(None, level, None)
+            plan.close()
+        assert np.abs(regs[0]).max() > 0 and np.array_equal(regs[0], regs[1])
+
+
 def test_two_level_cycle_graph_replay_matches_eager(nyx, reference):
     """Two two-level cycles (coarse fills and step feeding the register, fine
     fills in time and two substeps, reflux, average-down; the coarse state
