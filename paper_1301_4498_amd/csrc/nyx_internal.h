@@ -421,6 +421,7 @@ struct StepArgs {
   double igm1;   // 1 / (gamma - 1), for the mixed build's products
   float igm1f;   // the same in FP32 (the FP32 flux formulas)
   double mixed_stop;  // FP32-mixed stopping rule (see two_shock)
+  int plain;     // gamma and the pressure floor allow the FP64 solver's short divisions
   int maxiter;
   nyx_stats* stats;
   unsigned long long* slots;  // kStatSlots x kStatFields partial counters (when stats)

@@ -857,15 +857,18 @@ struct FullOps {
   static __device__ __forceinline__ double root(double x) { return sqrt(x); }
 };
 // densities and pressures of both states between 2^-100 and 2^100, normal
-// velocities 0 or likewise, and gamma away from 1: every product, quotient and
-// square root of the two-shock relations then stays between 2^-700 and 2^700
-// (or is 0), far from where a division or square root scales its operands
-__device__ __forceinline__ bool in_plain_range(double gamma, const double* qL, const double* qR) {
+// velocities 0 or likewise, the pressure floor, which a star pressure may take,
+// in that range too, and gamma - 1 between 2^-20 and 2^20 (both once per step,
+// on the host: StepArgs::plain): every product, quotient and square root of the
+// two-shock relations then stays between 2^-700 and 2^700 (or is 0), far from
+// where a division or square root scales its operands
+__device__ __forceinline__ bool in_plain_range(const StepArgs& A, const double* qL,
+                                               const double* qR) {
   auto expo = [](double x) { return (unsigned)__double2hiint(x) & 0x7fffffffu; };
   constexpr unsigned lo = (1023u - 100u) << 20, span = 200u << 20;
   auto in = [&](unsigned h) { return h - lo < span; };
   const unsigned ul = expo(qL[1]), ur = expo(qR[1]);
-  return gamma > 1.0 + 0x1p-20 && in(expo(qL[0])) && in(expo(qR[0])) && in(expo(qL[4])) &&
+  return A.plain && in(expo(qL[0])) && in(expo(qR[0])) && in(expo(qL[4])) &&
          in(expo(qR[4])) && (in(ul) || ul == 0u) && (in(ur) || ur == 0u);
 }
 
@@ -1342,7 +1345,7 @@ __device__ __forceinline__ RiemannOut two_shock_ops(const StepArgs& A, const dou
 template <bool BOTH = false, int RS = 0>
 __device__ __forceinline__ RiemannOut two_shock(const StepArgs& A, const double* qL,
                                                 const double* qR) {
-  if (in_plain_range(A.gamma, qL, qR)) return two_shock_ops<BOTH, PlainOps>(A, qL, qR);
+  if (in_plain_range(A, qL, qR)) return two_shock_ops<BOTH, PlainOps>(A, qL, qR);
   return two_shock_ops<BOTH, FullOps>(A, qL, qR);
 }
 #endif  // NYX_PREC_MIXED

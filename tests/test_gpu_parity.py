@@ -197,3 +197,26 @@ def test_fp64_step_out_of_ordinary_range(nyx, lo, hi):
     got, _, gst = gpu_run(U, g, n, dx, [a0, a1], [dt], prm, periodic=False)
     assert np.array_equal(got[:, NG:-NG, NG:-NG, NG:-NG], ref[:, NG:-NG, NG:-NG, NG:-NG])
     assert gst[0]["riemann_iters"] == st["riemann_iters"]
+
+
+@pytest.mark.parametrize("small_pres,dens,gamma", [(1e-315, 1e10, 5.0 / 3.0), (1e-300, 1e25, 5.0 / 3.0),
+                                                   (1e-300, 1.0, 5.0 / 3.0), (1e-20, 1.0, 1e100)])
+def test_fp64_star_pressure_at_a_tiny_floor(nyx, small_pres, dens, gamma):
+    """Streams that separate faster than their sound speed, whose star pressure
+    is the floor: ordinary states with a floor so small that the star state's
+    sound speed underflows or its square root's remainder does, and an adiabatic
+    index beyond the ordinary; bit for bit the oracle's step."""
+    n, a0, a1, dx = (14, 10, 12), 0.5, 0.5025, 1.0 / 16
+    U, g = synth.random_box(n, seed=37, a=a0)
+    U[0] *= dens
+    U[1:4] *= dens * 8.0
+    U[4] = U[5] + 0.5 * (U[1:4] ** 2).sum(0) / U[0]
+    par = oracle.Params(small_pres=small_pres, gamma=gamma)
+    prm = nyx.default_params(small_pres=small_pres, gamma=gamma)
+    dt = 0.1 * oracle.estimate_dt(U, NG, a0, dx, 0.5, par)
+    ref, st = oracle.hydro_step(U, g, NG, dt, dx, a0, a1, par)
+    got, _, gst = gpu_run(U, g, n, dx, [a0, a1], [dt], prm, periodic=False)
+    print(small_pres, dens, gamma, st, flush=True)
+    assert np.array_equal(got[:, NG:-NG, NG:-NG, NG:-NG], ref[:, NG:-NG, NG:-NG, NG:-NG],
+                          equal_nan=True)
+    assert gst[0]["riemann_iters"] == st["riemann_iters"]
