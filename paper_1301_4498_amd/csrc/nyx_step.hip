@@ -496,7 +496,9 @@ __device__ __forceinline__ void trace_side(const real* qc, real c, const real* q
   // The fastest wave's own difference to the reference state is 0: it is the
   // reference where it moves toward the face and carries nothing where it does
   // not.  Only the contact's and the slow wave's amplitudes remain (an FP64
-  // cell is spared four divisions, an FP32 one 8 of its instructions).
+  // cell is spared four divisions, an FP32 one 8 of its instructions), except
+  // beside overflowed values, where the difference or its products are NaN and
+  // so is the fastest wave's amplitude.
   real D[3][3];
   for (int w = 0; w < 3; ++w) {
     if (w == fast) continue;
@@ -504,24 +506,30 @@ __device__ __forceinline__ void trace_side(const real* qc, real c, const real* q
     for (int k = 0; k < 3; ++k) D[w][k] = in ? ref[k] - I[w][k] : (real)0;
   }
   const real* S = D[slow];
+  const real range = fabs(ref[1]) + fabs(ref[2]);  // finite where the difference is 0
+  const real df[2] = {fast_in ? ref[1] - ref[1] : (real)0, fast_in ? ref[2] - ref[2] : (real)0};
 #if defined(NYX_PREC_MIXED)
   const real ic = (real)1 / c;
   const real icsq = ic * ic;
-  const real as = SIDE > 0 ? (real)0.5 * (S[2] * icsq - (rho * S[1]) * ic)
-                           : (real)0.5 * (S[2] * icsq + (rho * S[1]) * ic);
+  real as = SIDE > 0 ? (real)0.5 * (S[2] * icsq - (rho * S[1]) * ic)
+                     : (real)0.5 * (S[2] * icsq + (rho * S[1]) * ic);
+  if (!(range + (icsq + rho) <= 3.402823466e+38f)) {
+    asm volatile("");  // rare: a branch of its own
+    as += df[1] * icsq + (rho * df[0]) * ic;
+  }
   const real a0 = D[1][0] - D[1][2] * icsq;
   out[0] = ref[0] - (SIDE > 0 ? as + a0 : a0 + as);
   out[nv] = ref[1] - (c * __builtin_amdgcn_rcpf(rho)) * (SIDE > 0 ? -as : as);
 #else
   real s2, s1, d2, cr;  // S[2] / csq, rho S[1] / c, D[1][2] / csq, c / rho
-  if (wide_range(csq) && wide_range(rho)) {
+  if (wide_range(csq) && wide_range(rho) && range <= 1.7976931348623157e308) {
     const Recip rcs = make_recip(csq), rc = make_recip(c);
     s2 = quot(S[2], rcs);
     s1 = quot(rho * S[1], rc);
     d2 = quot(D[1][2], rcs);
     cr = quot(c, make_recip(rho));
   } else {
-    s2 = S[2] / csq;
+    s2 = S[2] / csq + (df[1] / csq + (rho * df[0]) / c);
     s1 = (rho * S[1]) / c;
     d2 = D[1][2] / csq;
     cr = c / rho;

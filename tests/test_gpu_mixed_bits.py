@@ -1,7 +1,8 @@
-"""The FP32-mixed step's result bits, pinned on inputs where rewriting an FP32
+"""The FP32-mixed step's result bits and counters, pinned on inputs where rewriting an FP32
 expression into one that is equal in exact arithmetic shows: parabolas whose
 monotonicity limit and edge agree to rounding, velocities near 1e20 (a floored
-cell's) whose squared edge differences overflow, and NaN and infinite cells.
+cell's) whose squared edge differences overflow, sound speeds near 1e18 whose waves'
+averages overflow, and NaN and infinite cells.
 The digests are of the step with the limits as comparisons and the slopes as
 clamped minima (cells beside a NaN included).  One box takes flattening and
 tracing as separate kernels, one as the marching pass."""
@@ -58,6 +59,10 @@ def _input(n, kind):
             U[(q % 6,) + c] = np.nan
         elif kind == "inf":
             U[(q % 6,) + c] = np.inf
+    if kind == "hot":
+        z, y, x = np.indices((7, 6, 5))
+        e = 1e19 * (1.0 + 0.3 * (x - 1.5) ** 2 + 0.5 * y + 0.2 * z * (7 - z))
+        U[:, 9:16, 8:14, 10:15] = [np.full(e.shape, 1e-16), 0.0 * e, 0.0 * e, 0.0 * e, e, e]
     g = np.stack([((h + c) % 17 - 8) / 128.0 for c in range(3)])
     return synth.pad_periodic(U), synth.pad_periodic(g)
 
@@ -69,27 +74,32 @@ def step_digest(nyx, n, kind):
     box = nyx.make_box(n, NG, 1.0 / 64)
     A, G = to_dev(U), to_dev(g, torch.float32)
     B = torch.zeros_like(A)
-    nyx.hydro_step(prm, box, A, G, 1e-4 if kind != "fast" else 1e-22, 0.5, 0.5005, B,
+    st = torch.zeros(10, dtype=torch.int64, device="cuda")
+    nyx.hydro_step(prm, box, A, G, 1e-4 if kind != "fast" else 1e-22, 0.5, 0.5005, B, stats=st,
                    workspace=aligned_ws(nyx.workspace_bytes(prm, box)))
     out = B.cpu().numpy()[:, NG:-NG, NG:-NG, NG:-NG] + 0.0
     out = np.where(np.isnan(out), np.nan, out)
-    return hashlib.sha256(np.ascontiguousarray(out).tobytes()).hexdigest()[:16]
+    h = hashlib.sha256(np.ascontiguousarray(out).tobytes())
+    h.update(st.cpu().numpy().tobytes())
+    return h.hexdigest()[:16]
 
 
 SMALL, LARGE = (34, 30, 26), (112, 110, 114)
 BITS = {
-    (SMALL, "ties"): "4f79ead6a66da113",
-    (SMALL, "fast"): "3eadcc0203613207",
-    (SMALL, "nan"): "07efec04b5b03454",
-    (SMALL, "inf"): "1226dd271ff73f42",
-    (LARGE, "ties"): "a3c4c31506246ea3",
-    (LARGE, "fast"): "679fa1f80ac07586",
-    (LARGE, "nan"): "fbe8cc18acf2c0f4",
-    (LARGE, "inf"): "6cbe697c9fb1742c",
+    (SMALL, "ties"): "3f5ad03d2728de71",
+    (SMALL, "fast"): "e9f68f09651c403d",
+    (SMALL, "hot"): "dd14dad804616981",
+    (SMALL, "nan"): "794de7adfce03024",
+    (SMALL, "inf"): "6d3cc91cd951f170",
+    (LARGE, "ties"): "33c67f24394b87aa",
+    (LARGE, "fast"): "a24b20c3433a2091",
+    (LARGE, "hot"): "c53935dcce2466c8",
+    (LARGE, "nan"): "af2b2e590583de76",
+    (LARGE, "inf"): "c69a8b3f03ff32ad",
 }
 
 
-@pytest.mark.parametrize("kind", ["ties", "fast", "nan", "inf"])
+@pytest.mark.parametrize("kind", ["ties", "fast", "hot", "nan", "inf"])
 @pytest.mark.parametrize("n", [SMALL, LARGE])
 def test_mixed_step_bits(n, kind):
     import torch

@@ -220,3 +220,24 @@ def test_fp64_star_pressure_at_a_tiny_floor(nyx, small_pres, dens, gamma):
     assert np.array_equal(got[:, NG:-NG, NG:-NG, NG:-NG], ref[:, NG:-NG, NG:-NG, NG:-NG],
                           equal_nan=True)
     assert gst[0]["riemann_iters"] == st["riemann_iters"]
+
+
+@pytest.mark.parametrize("dens,pres", [(1e14, 1e163), (1e-10, 1e140), (1e-10, 1e220)])
+def test_fp64_step_beside_overflowing_waves(nyx, dens, pres):
+    """A region so hot that a wave's average over its domain of dependence
+    overflows: the fastest wave's difference to its own, infinite, reference is
+    NaN there, as in the oracle's tracing; bit for bit its step and counters,
+    non-finite cells included."""
+    n, a0, a1, dx = (14, 10, 12), 0.5, 0.5025, 1.0 / 16
+    U, g = synth.random_box(n, seed=41, a=a0)
+    V = U[:, NG:-NG, NG:-NG, NG:-NG]
+    z, y, x = np.indices((7, 6, 5))
+    e = a0 * a0 * pres * (1.0 + 0.3 * (x - 1.5) ** 2 + 0.5 * y + 0.2 * z * (7 - z))
+    V[:, 2:9, 2:8, 4:9] = [np.full(e.shape, dens), 0.0 * e, 0.0 * e, 0.0 * e, e, e]
+    synth.fill_periodic_inplace(U)
+    ref, st = oracle.hydro_step(U, g, NG, 1e-3, dx, a0, a1)
+    got, _, gst = gpu_run(U, g, n, dx, [a0, a1], [1e-3], nyx.default_params(), periodic=False)
+    print("non-finite:", np.isnan(ref).sum(), np.isinf(ref).sum(), flush=True)
+    assert np.array_equal(got[:, NG:-NG, NG:-NG, NG:-NG], ref[:, NG:-NG, NG:-NG, NG:-NG],
+                          equal_nan=True)
+    assert gst[0]["floor_hits"] == st["floor_hits"]
