@@ -45,8 +45,9 @@ namespace NYX_NS {
 // Quotients by one divisor: its reciprocal, refined as the compiler's division
 // does, serves every numerator, and the special cases (0, infinity, NaN) are
 // mended as there.  The same bits as a / b at 5 + 4 instructions per numerator
-// instead of 11 each, for divisors of ordinary magnitude (wide_range; the
-// general division also scales denormal and huge operands).
+// instead of 11 each, for divisors of ordinary magnitude (wide_range) and
+// numerators that are 0 or at least 2^-901 (quot_exp): a smaller one's remainder
+// is inexact or its quotient denormal, which the general division scales.
 struct Recip {
   double b, y;
 };
@@ -60,6 +61,14 @@ __device__ __forceinline__ double quot(double a, const Recip& r) {
   const double q = a * r.y;
   return __builtin_amdgcn_div_fixup(fma(fma(-r.b, q, a), r.y, q), r.b, a);
 }
+// Exponent of a numerator: 0 for 0, infinity and NaN, e for a magnitude in
+// [2^(e-1), 2^e); of several the least.
+__device__ __forceinline__ int quot_exp(double a) { return __builtin_amdgcn_frexp_exp(a); }
+template <class... T>
+__device__ __forceinline__ int quot_exp(double a, T... rest) {
+  const int e = quot_exp(a), f = quot_exp(rest...);
+  return e < f ? e : f;
+}
 // magnitude between 2^-500 and 2^500
 __device__ __forceinline__ bool wide_range(double b) {
   const unsigned h = (unsigned)__double2hiint(b) & 0x7fffffffu;
@@ -71,6 +80,19 @@ __device__ __forceinline__ bool wide_range(double b) {
 #define FLAT_EPS 0.33
 #define FLAT_OMEGA1 0.75
 #define FLAT_OMEGA2 10.0
+
+// Whether numerators made of velocities need the general division, from the
+// least exponent of these velocities; with parameters out of the ordinary
+// (StepArgs::plain) they do.  Densities and pressures start from their floors,
+// and a sum or difference of doubles is 0 or at least the last place of its
+// smaller operand, so that no other numerator of a step is small.
+//   kTraceExp: velocities of a stencil; their differences, flattened (by at
+//     least 2^-53) and squared, then exceed 2^-920;
+//   kFluxExp: the velocity of a face, whose pressure exceeds 2^-180.
+constexpr int kTraceExp = -300, kFluxExp = -700, kQuotExp = -900;
+__device__ __forceinline__ bool general_div(const StepArgs& A, int e, int least) {
+  return !A.plain || e < least;
+}
 
 template <class T>
 __device__ __forceinline__ T vmax(T a, T b) { return a > b ? a : b; }
@@ -398,16 +420,19 @@ __device__ __forceinline__ real lim_slope(real qm1, real q0, real qp1) {
 // interface value between cells a and b from their limited slopes sa, sb (in
 // the mixed build from the half slopes: a third of their difference is a sixth
 // of the slopes', bit for bit)
+template <bool GEN>
 __device__ __forceinline__ real ppm_face(real qa, real qb, real sa, real sb) {
 #if defined(NYX_PREC_MIXED)
   return (qa + (real)0.5 * (qb - qa)) - (sb - sa) * (real)(1.0 / 3.0);
 #else
-  return (qa + (real)0.5 * (qb - qa)) - quot(sb - sa, make_recip(6.0));
+  return (qa + (real)0.5 * (qb - qa)) - (GEN ? (sb - sa) / 6.0 : quot(sb - sa, make_recip(6.0)));
 #endif
 }
 // PPM edges of the cell of q5[2]: interface values from the slopes of cells
 // j-1, j, j+1 (each computed once), flattened, then the monotonicity limits of
-// the parabola (CW84 eq. 1.10).  med: the mixed build's slopes as medians.
+// the parabola (CW84 eq. 1.10).  med: the mixed build's slopes as medians.  GEN:
+// the FP64 build's general divisions.
+template <bool GEN>
 __device__ __forceinline__ void ppm_edges(const real* q5, bool med, real chi, real& qm_o,
                                           real& qp_o) {
   const real qj = q5[2];
@@ -421,8 +446,8 @@ __device__ __forceinline__ void ppm_edges(const real* q5, bool med, real chi, re
 #else
   for (int k = 0; k < 3; ++k) h[k] = lim_slope(q5[k], q5[k + 1], q5[k + 2]);
 #endif
-  real qp = ppm_face(q5[2], q5[3], h[1], h[2]);
-  real qm = ppm_face(q5[1], q5[2], h[0], h[1]);
+  real qp = ppm_face<GEN>(q5[2], q5[3], h[1], h[2]);
+  real qm = ppm_face<GEN>(q5[1], q5[2], h[0], h[1]);
   qp = chi * qp + ((real)1 - chi) * qj;
   qm = chi * qm + ((real)1 - chi) * qj;
 #if defined(NYX_PREC_MIXED)
@@ -447,7 +472,7 @@ __device__ __forceinline__ void ppm_edges(const real* q5, bool med, real chi, re
   } else {
     const real dq = qp - qm;
     const real t = dq * (qj - (real)0.5 * (qm + qp));
-    const real s = quot(dq * dq, make_recip(6.0));
+    const real s = GEN ? dq * dq / 6.0 : quot(dq * dq, make_recip(6.0));
     if (t > s) qm = (real)3 * qj - (real)2 * qp;
     else if (-s > t) qp = (real)3 * qj - (real)2 * qm;
   }
@@ -474,10 +499,10 @@ __device__ __forceinline__ real avg_lo(real qm, real dq, real q6, real sig) {
 // One side of the tracing: side = +1 (right face, waves with lam > 0) or -1.
 // v[] indexes: 0 rho, nv normal velocity, t1/t2 transverse, 4 p.
 template <int SIDE>
-__device__ __forceinline__ void trace_side(const real* qc, real c, const real* qe,
-                                           const real* dq, const real* q6, const real* lam,
-                                           const real* sig, int nv, int t1, int t2,
-                                           real* out) {
+__device__ __forceinline__ void trace_side(const StepArgs& A, const real* qc, real c,
+                                           const real* qe, const real* dq, const real* q6,
+                                           const real* lam, const real* sig, int nv, int t1,
+                                           int t2, real* out) {
   const real rho = qc[0];
   const real csq = c * c;
   // averages over each wave's domain of dependence for rho, u_n, p
@@ -522,15 +547,17 @@ __device__ __forceinline__ void trace_side(const real* qc, real c, const real* q
   out[nv] = ref[1] - (c * __builtin_amdgcn_rcpf(rho)) * (SIDE > 0 ? -as : as);
 #else
   real s2, s1, d2, cr;  // S[2] / csq, rho S[1] / c, D[1][2] / csq, c / rho
-  if (wide_range(csq) && wide_range(rho) && range <= 1.7976931348623157e308) {
+  const double rs = rho * S[1];
+  if (wide_range(csq) && wide_range(rho) && range <= 1.7976931348623157e308 &&
+      !general_div(A, quot_exp(rs), kQuotExp)) {
     const Recip rcs = make_recip(csq), rc = make_recip(c);
     s2 = quot(S[2], rcs);
-    s1 = quot(rho * S[1], rc);
+    s1 = quot(rs, rc);
     d2 = quot(D[1][2], rcs);
     cr = quot(c, make_recip(rho));
   } else {
     s2 = S[2] / csq + (df[1] / csq + (rho * df[0]) / c);
-    s1 = (rho * S[1]) / c;
+    s1 = rs / c;
     d2 = D[1][2] / csq;
     cr = c / rho;
   }
@@ -565,7 +592,18 @@ __device__ __forceinline__ unsigned trace_core(const StepArgs& A, const StepC& C
   if (A.recon == NYX_RECON_PLM) {
     for (int v = 0; v < 5; ++v) plm_edges(qs[v], chi, qm[v], qp[v]);
   } else {
-    for (int v = 0; v < 5; ++v) ppm_edges(qs[v], med, chi, qm[v], qp[v]);
+#if !defined(NYX_PREC_MIXED)
+    int e = 0;
+    for (int v = 1; v < 4; ++v)
+      for (int o = 0; o < 5; ++o) {
+        const int f = quot_exp(qs[v][o]);
+        e = f < e ? f : e;
+      }
+    if (general_div(A, e, kTraceExp)) {
+      for (int v = 0; v < 5; ++v) ppm_edges<true>(qs[v], med, chi, qm[v], qp[v]);
+    } else
+#endif
+      for (int v = 0; v < 5; ++v) ppm_edges<false>(qs[v], med, chi, qm[v], qp[v]);
   }
   for (int v = 0; v < 5; ++v) {
     qc[v] = qs[v][2];
@@ -578,8 +616,8 @@ __device__ __forceinline__ unsigned trace_core(const StepArgs& A, const StepC& C
   const real kh = C.NYX_REAL(kh);
   real sig[3];
   for (int w = 0; w < 3; ++w) sig[w] = fabs(lam[w]) * kh;
-  trace_side<+1>(qc, c, qp, dq, q6, lam, sig, nv, t1, t2, hi);
-  trace_side<-1>(qc, c, qm, dq, q6, lam, sig, nv, t1, t2, lo);
+  trace_side<+1>(A, qc, c, qp, dq, q6, lam, sig, nv, t1, t2, hi);
+  trace_side<-1>(A, qc, c, qm, dq, q6, lam, sig, nv, t1, t2, lo);
   // half-step gravity and expansion sources, then floors
   const real hdt_a = C.NYX_REAL(hdt_a), hda_a = C.NYX_REAL(hda_a), pexp = C.NYX_REAL(pexp);
   const real sd_ = A.NYX_REAL(small_dens), sp_ = A.NYX_REAL(small_pres);
@@ -1405,9 +1443,27 @@ __device__ __forceinline__ void face_flux(const StepArgs& A, int d, const God& g
   f[6] = p;
   f[7] = u;
 }
-__device__ __forceinline__ void face_flux(const StepArgs& A, int d, const real* G, long long E,
-                                          unsigned i, real* f) {
-  face_flux(A, d, ld_god(G, E, i), f);
+// Whether the energy fluxes of faces with these normal velocities need the
+// general divisions (FP64 build).  Rare, so the callers take the fluxes as they
+// are and then put the two energy components (energy_flux) right from reloaded
+// states: nothing is kept in registers for that (FP64 final states 127 VGPRs;
+// with a choice in face_flux 152, and one wavefront a SIMD less).  128^3: riem2
+// 327 us without the test, 350 with it, 376 with the choice.
+template <class... T>
+__device__ __forceinline__ bool slow_faces(const StepArgs& A, T... u) {
+#if defined(NYX_PREC_MIXED)
+  return false;
+#else
+  return __builtin_expect(general_div(A, quot_exp(u...), kFluxExp), 0);
+#endif
+}
+// f_E and f_e of face_flux with general divisions
+__device__ __forceinline__ void energy_flux(const StepArgs& A, const God& g, double* f) {
+  const double gm1 = A.gamma - 1.0;
+  const double r = g.r, u = g.u, v = g.v, w = g.w, p = g.p;
+  const double rE = p / gm1 + (0.5 * r) * ((u * u + v * v) + w * w);
+  f[0] = u * (rE + p);
+  f[1] = (u * p) / gm1;
 }
 
 __device__ __forceinline__ void e_coords(const BoxDev& b, unsigned e, int* c) {
@@ -1448,11 +1504,29 @@ __device__ __forceinline__ void tdiff(const StepArgs& A, int t, const God& glo, 
 #endif
   De = FIRST ? de : De + de;
 }
+// the energy components of tdiff with general divisions, the states reloaded
+template <bool FIRST>
+__device__ __forceinline__ void tdiff_energy(const StepArgs& A, const real* Glo, const real* Ghi,
+                                             unsigned i, long long E, double* Dc, double& De) {
+  asm volatile("" ::: "memory");
+  const God lo = ld_god(Glo, E, i), hi = ld_god(Ghi, E, i);
+  double fm[2], fp[2];
+  energy_flux(A, lo, fm);
+  energy_flux(A, hi, fp);
+  const double dd = fp[0] - fm[0];
+  const double de = (fp[1] - fm[1]) +
+                    (0.5 * ((double)hi.p + (double)lo.p)) * ((double)hi.u - (double)lo.u);
+  Dc[4] = FIRST ? dd : Dc[4] + dd;
+  De = FIRST ? de : De + de;
+}
 template <bool FIRST>
 __device__ __forceinline__ void tdiff(const StepArgs& A, int t, const real* Glo, const real* Ghi,
                                       unsigned i, long long E, double* Dc, double& De) {
+  static_assert(FIRST, "a second direction's sums cannot be put right");
   i = local_idx(i);
-  tdiff<FIRST>(A, t, ld_god(Glo, E, i), ld_god(Ghi, E, i), Dc, De);
+  const God lo = ld_god(Glo, E, i), hi = ld_god(Ghi, E, i);
+  tdiff<FIRST>(A, t, lo, hi, Dc, De);
+  if (slow_faces(A, lo.u, hi.u)) tdiff_energy<FIRST>(A, Glo, Ghi, i, E, Dc, De);
 }
 
 __device__ __forceinline__ bool trans_correct(const StepArgs& A, const double* q,
@@ -1473,7 +1547,7 @@ __device__ __forceinline__ bool trans_correct(const StepArgs& A, const double* q
   U[4] = Ue + (0.5 * rho) * ((ux * ux + uy * uy) + uz * uz);
   double Un[5];
   for (int c = 0; c < 5; ++c) Un[c] = U[c] - kap * Dc[c];
-  const double Uen = Ue - kap * De;
+  double Uen = Ue - kap * De;
 #if defined(NYX_PREC_MIXED)
   const double iU0 = rcp64(Un[0]);
   const double ke = (0.5 * ((Un[1] * Un[1] + Un[2] * Un[2]) + Un[3] * Un[3])) * iU0;
@@ -1481,11 +1555,15 @@ __device__ __forceinline__ bool trans_correct(const StepArgs& A, const double* q
   // the kinetic energy and the velocities by one reciprocal
   const double m2 = 0.5 * ((Un[1] * Un[1] + Un[2] * Un[2]) + Un[3] * Un[3]);
   double ke, vel[3];
-  if (wide_range(Un[0])) {
+  // m2 holds squares: twice the exponent
+  if (wide_range(Un[0]) && !general_div(A, 2 * quot_exp(Un[1], Un[2], Un[3]), kQuotExp)) {
     const Recip r0 = make_recip(Un[0]);
     ke = quot(m2, r0);
     for (int d = 0; d < 3; ++d) vel[d] = quot(Un[1 + d], r0);
   } else {
+    const double Ug = p / gm1;
+    Un[4] = (Ug + (0.5 * rho) * ((ux * ux + uy * uy) + uz * uz)) - kap * Dc[4];
+    Uen = Ug - kap * De;
     ke = m2 / Un[0];
     for (int d = 0; d < 3; ++d) vel[d] = Un[1 + d] / Un[0];
   }
@@ -1857,6 +1935,11 @@ __device__ __forceinline__ void final_states(const StepArgs& A, const BoxDev& b,
     } else {
       tdiff<true>(A, t1, ga[s][0], ga[s][1], Dc, De);   // t1-flux corrected by t2
       tdiff<false>(A, t2, gb[s][0], gb[s][1], Dc, De);  // t2-flux corrected by t1
+      if (slow_faces(A, ga[s][0].u, ga[s][1].u, gb[s][0].u, gb[s][1].u)) {
+        const long long sh = s == 0 ? -sdd : 0;
+        tdiff_energy<true>(A, G1a + sh, G1a + sh + s1, e, b.E, Dc, De);
+        tdiff_energy<false>(A, G1b + sh, G1b + sh + s2, e, b.E, Dc, De);
+      }
     }
     if (CARRY != 0 && s == 1) {
       for (int c = 0; c < 5; ++c) carry[c] = Dc[c];
@@ -2057,6 +2140,29 @@ __device__ __forceinline__ void flux_diff(const StepArgs& A, real ah, const God*
   }
 }
 
+// the same with the faces from load(low, high); the energy components put right
+// where a face is slow
+template <class LOAD>
+__device__ __forceinline__ void flux_diff(const StepArgs& A, real ah, LOAD load, double* D,
+                                          double& Pi) {
+  God gl[3], gh[3];
+  load(gl, gh);
+  flux_diff(A, ah, gl, gh, D, Pi);
+  if (slow_faces(A, gl[0].u, gl[1].u, gl[2].u, gh[0].u, gh[1].u, gh[2].u)) {
+    asm volatile("" ::: "memory");
+    load(gl, gh);
+    for (int d = 0; d < 3; ++d) {
+      double fl[2], fh[2];
+      energy_flux(A, gl[d], fl);
+      energy_flux(A, gh[d], fh);
+      for (int c = 0; c < 2; ++c) {
+        const double dF = (double)ah * fh[c] - (double)ah * fl[c];
+        D[4 + c] = d == 0 ? dF : D[4 + c] + dF;
+      }
+    }
+  }
+}
+
 struct CellCount {
   unsigned nsync = 0, nnf = 0, nnd = 0, nne = 0;
 };
@@ -2161,17 +2267,16 @@ __device__ __forceinline__ void update_body(const StepArgs& A, const Item& it) {
     const real* G2 = (const real*)A.work + b.w_f2;
     const unsigned id = ((unsigned)(k + b.ng) * (unsigned)b.py + (unsigned)(j + b.ng)) *
                             (unsigned)b.px + (unsigned)(i + b.ng);
-    // every load of the cell is issued before any arithmetic
     const unsigned le = local_idx(e);
-    God gl[3], gh[3];
-    for (int d = 0; d < 3; ++d) {
-      const real* G = G2 + (long long)d * kGod * b.E;
-      gl[d] = ld_god(G, b.E, le);
-      gh[d] = ld_god(G + (long long)e_stride(b, d), b.E, le);
-    }
     const CellIn x = load_cell(A, b, id);
     double D[6], Pi;
-    flux_diff(A, (real)C.a_h, gl, gh, D, Pi);
+    flux_diff(A, (real)C.a_h, [&](God* gl, God* gh) {
+      for (int d = 0; d < 3; ++d) {
+        const real* G = G2 + (long long)d * kGod * b.E;
+        gl[d] = ld_god(G, b.E, le);
+        gh[d] = ld_god(G + (long long)e_stride(b, d), b.E, le);
+      }
+    }, D, Pi);
     smax = update_apply(A, C, b, id, x, D, Pi, n);
   }
   count_cells(A, n);
@@ -2318,12 +2423,15 @@ __global__ __launch_bounds__(kFinBlock, kFinWaves) void k_final(StepArgs A) {
     if (cell) x = load_cell(A, b, id);
     __syncthreads();
     if (cell) {
-      const God gl[3] = {lds_get(fx, kFinXs, tj * (TX + 1) + ti), lds_get(fy, kFinYs, tj * TX + ti),
-                         zl};
-      const God gh[3] = {lds_get(fx, kFinXs, tj * (TX + 1) + ti + 1),
-                         lds_get(fy, kFinYs, (tj + 1) * TX + ti), zh};
       double D[6], Pi;
-      flux_diff(A, ah, gl, gh, D, Pi);
+      flux_diff(A, ah, [&](God* gl, God* gh) {
+        gl[0] = lds_get(fx, kFinXs, tj * (TX + 1) + ti);
+        gl[1] = lds_get(fy, kFinYs, tj * TX + ti);
+        gl[2] = zl;
+        gh[0] = lds_get(fx, kFinXs, tj * (TX + 1) + ti + 1);
+        gh[1] = lds_get(fy, kFinYs, (tj + 1) * TX + ti);
+        gh[2] = zh;
+      }, D, Pi);
       smax = vmax(smax, update_apply(A, C, b, id, x, D, Pi, n));
     }
     zl = zh;
@@ -2367,14 +2475,24 @@ __global__ __launch_bounds__(kBlock) void k_flux_record(StepArgs A, const BoxDev
   const real ah = (real)C.a_h;
   double acc[6];
   real f[8];
-  final_flux(A, d, ld_god_any(G, b.E, e), ah, f);
+  auto flux = [&](unsigned i) {
+    const God g = ld_god_any(G, b.E, i);
+    final_flux(A, d, g, ah, f);
+#if !defined(NYX_PREC_MIXED)
+    double en[2];
+    energy_flux(A, g, en);
+    f[4] = ah * en[0];
+    f[5] = ah * en[1];
+#endif
+  };
+  flux(e);
   for (int c = 0; c < 6; ++c) acc[c] = (double)f[c];
   if (R.nsub == 2) {
     const int t1 = d == 0 ? 1 : 0, t2 = d == 2 ? 1 : 2;
     const unsigned o1 = e_stride(b, t1), o2 = e_stride(b, t2);
     const unsigned sub[3] = {e + o1, e + o2, e + o1 + o2};
     for (int q = 0; q < 3; ++q) {
-      final_flux(A, d, ld_god_any(G, b.E, sub[q]), ah, f);
+      flux(sub[q]);
       for (int c = 0; c < 6; ++c) acc[c] = acc[c] + (double)f[c];
     }
   }

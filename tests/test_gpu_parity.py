@@ -241,3 +241,28 @@ def test_fp64_step_beside_overflowing_waves(nyx, dens, pres):
     assert np.array_equal(got[:, NG:-NG, NG:-NG, NG:-NG], ref[:, NG:-NG, NG:-NG, NG:-NG],
                           equal_nan=True)
     assert gst[0]["floor_hits"] == st["floor_hits"]
+
+
+@pytest.mark.parametrize("recon", ["ppm", "plm"])
+@pytest.mark.parametrize("lo", [-1074, -1030, -1024, -1016, -1000])
+def test_fp64_step_with_tiny_velocities(nyx, lo, recon):
+    """A flow along x that carries transverse velocities of 2^-1074 to 2^-1000
+    (the far tail of a pulse), where a quotient by a shared reciprocal has an
+    inexact remainder or a denormal result; bit for bit the oracle's step."""
+    n, a0, a1, dx = (14, 10, 12), 0.5, 0.5025, 1.0 / 16
+    rng = np.random.default_rng(43)
+    U, g = synth.random_box(n, seed=43, a=a0)
+    V = U[:, NG:-NG, NG:-NG, NG:-NG]
+    V[...] = V[:, :1, :1, :]  # functions of x
+    V[2:4] = np.ldexp(rng.uniform(1.0, 2.0, (2,) + V.shape[1:]), lo)
+    V[2:4, ::3] = 0.0
+    V[4] = V[5] + 0.5 * V[1] ** 2 / V[0]
+    synth.fill_periodic_inplace(U)
+    r = 1 if recon == "plm" else 0
+    par, prm = oracle.Params(recon=r), nyx.default_params(recon=r)
+    dt = oracle.estimate_dt(U, NG, a0, dx, 0.8, par)
+    ref, _ = oracle.hydro_step(U, 0.0 * g, NG, dt, dx, a0, a1, par)
+    got, _, _ = gpu_run(U, 0.0 * g, n, dx, [a0, a1], [dt], prm, periodic=False)
+    want = ref[:, NG:-NG, NG:-NG, NG:-NG]
+    assert 0 < np.abs(want[2:4]).max() < 2.0 ** (lo + 10)
+    assert np.array_equal(got[:, NG:-NG, NG:-NG, NG:-NG], want)
