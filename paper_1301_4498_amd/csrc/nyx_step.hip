@@ -1866,8 +1866,11 @@ __device__ __forceinline__ void riem1_body(const StepArgs& A, const Item& it, __
   }
   count_tally<LEARNED>(A, T, true);
 }
+// The learned forms are bound to 4 wavefronts a SIMD (128 VGPRs, no spill):
+// left alone they take 130 and run at 3 (256^3, transverse stage 5570 us against
+// 4840, final stage 2825 against 2525).
 template <bool LEARNED, bool PAIRS = LEARNED>
-__global__ __launch_bounds__(kBlock) void k_riem1(StepArgs A) {
+__global__ __launch_bounds__(kBlock, LEARNED ? 4 : 1) void k_riem1(StepArgs A) {
   __shared__ __bf16 mlp_lds[LEARNED ? (kBlock / 64) * kMlpWaveLds : 1];
   __shared__ double park[PAIRS ? 1 : kPark * kBlock];
   riem1_body<LEARNED, PAIRS>(A, launch_item(A, kStRiem1), mlp_lds, park);
@@ -2003,7 +2006,7 @@ __device__ __forceinline__ void riem2_body(const StepArgs& A, const Item& it, __
   count_tally<LEARNED>(A, T, true);
 }
 template <int MODE>
-__global__ __launch_bounds__(kBlock) void k_riem2(StepArgs A) {
+__global__ __launch_bounds__(kBlock, MODE == 1 ? 4 : 1) void k_riem2(StepArgs A) {
   __shared__ __bf16 mlp_lds[MODE == 1 ? (kBlock / 64) * kMlpWaveLds : 1];
   riem2_body<MODE>(A, launch_item(A, kStRiem2), mlp_lds);
 }
