@@ -280,6 +280,9 @@ __device__ __forceinline__ void stu(T* base, unsigned i, T v) {
 // and spends a 64-bit vector add on most of them; this way each access takes
 // the scalar-base form.  With the index extended in the block of the accesses
 // (local_idx, called once in front of them) that costs no vector instruction.
+// Not a gain everywhere: kernels of many loads from one offset with registers to
+// spare (flattening, the separate tracing, the staged final stage) are faster
+// with plain loads (ldu).
 __device__ __forceinline__ unsigned local_idx(unsigned i) {
   asm("" : "+v"(i));
   return i;

@@ -349,17 +349,17 @@ __device__ __forceinline__ void flat_body(const StepArgs& A, const Item& it) {
   const int ie = ec[0], je = ec[1], ke = ec[2];
   const real* prim = (const real*)A.work + b.w_prim;
   const real* P = prim + 4 * b.P;
-  const unsigned c0 = local_idx(pidx_e(b, ie, je, ke));
+  const unsigned c0 = pidx_e(b, ie, je, ke);
   const unsigned sd[3] = {1u, (unsigned)b.px, (unsigned)b.px * (unsigned)b.py};
   // neighbour shifts go into the (uniform) base; all loads share c0 and are
   // issued before any arithmetic, so a wave waits once for all of them
   real pd[3][7], ud[3][5];
-  const real pc = ldw(P, c0);
+  const real pc = ldu(P, c0);
   for (int d = 0; d < 3; ++d) {
     const unsigned s = sd[d];
     const real* U = prim + (1 + d) * b.P;
-    for (int o = -3; o <= 3; ++o) pd[d][o + 3] = o == 0 ? pc : ldw(P + (long long)o * s, c0);
-    for (int o = -2; o <= 2; ++o) ud[d][o + 2] = ldw(U + (long long)o * s, c0);
+    for (int o = -3; o <= 3; ++o) pd[d][o + 3] = o == 0 ? pc : ldu(P + (long long)o * s, c0);
+    for (int o = -2; o <= 2; ++o) ud[d][o + 2] = ldu(U + (long long)o * s, c0);
   }
   const real cmin = flat_core((real)A.small_pres, pd, ud);
   stw((real*)A.work + b.w_chi, local_idx(e), cmin);
@@ -638,17 +638,17 @@ __device__ __forceinline__ unsigned trace_cell(const StepArgs& A, const BoxDev& 
                                                unsigned e, int ie, int je, int ke, real* lo,
                                                real* hi) {
   const real* prim = (const real*)A.work + b.w_prim;
-  const unsigned c0 = local_idx(pidx_e(b, ie, je, ke));
+  const unsigned c0 = pidx_e(b, ie, je, ke);
   const unsigned s = D == 0 ? 1u : (D == 1 ? (unsigned)b.px : (unsigned)b.px * (unsigned)b.py);
   // every load of the cell is issued before any arithmetic, so a wave
   // waits once for all of them instead of once per variable
-  const real chi = ldw((const real*)A.work + b.w_chi, local_idx(e));
+  const real chi = ldu((const real*)A.work + b.w_chi, e);
   real qs[5][5];
   for (int v = 0; v < 5; ++v)
-    for (int o = -2; o <= 2; ++o) qs[v][o + 2] = ldw(prim + v * b.P + (long long)o * s, c0);
-  const real c = ldw(prim + 5 * b.P, c0);
+    for (int o = -2; o <= 2; ++o) qs[v][o + 2] = ldu(prim + v * b.P + (long long)o * s, c0);
+  const real c = ldu(prim + 5 * b.P, c0);
   const real* G = (const real*)A.grav + b.goff;
-  const real g[3] = {ldw(G, c0), ldw(G + b.gstride, c0), ldw(G + 2 * b.gstride, c0)};
+  const real g[3] = {ldu(G, c0), ldu(G + b.gstride, c0), ldu(G + 2 * b.gstride, c0)};
   bool med = true;
 #if defined(NYX_PREC_MIXED)
   real top = (real)0;
@@ -1902,7 +1902,10 @@ __device__ __forceinline__ unsigned face_hash(unsigned long long seed, int box, 
 // walking faces along d carries them: CARRY = 1 stores the upper cell's
 // differences (Dc, De) in carry[6]; CARRY = 2 also takes the lower cell's
 // from it instead of loading and differencing its stage-1 states.
-template <int D, int CARRY = 0>
+// WB: scalar-base loads (ldw), which pay in the fused kernel and beside the
+// network; the staged kernel has registers for the addresses (256^3 FP32-mixed
+// 1292 us with them, 1233 without, 128^3 FP64 350 and 331; fused 1543 and 1560).
+template <int D, int CARRY = 0, bool WB = true>
 __device__ __forceinline__ void final_states(const StepArgs& A, const BoxDev& b, const StepC& C,
                                              unsigned e, double* ql, double* qr,
                                              unsigned* reverts, double* carry = nullptr) {
@@ -1914,18 +1917,24 @@ __device__ __forceinline__ void final_states(const StepArgs& A, const BoxDev& b,
   const real* G1b = (const real*)A.work + b.w_f1 + (long long)pair_index(t2, t1) * kGod * b.E;
   // both cells' loads are issued before any arithmetic, so a wave waits
   // once for all of them
+  auto ld = [](const real* G, long long E, unsigned i) {
+    return WB ? ld_god(G, E, i) : ld_god_any(G, E, i);
+  };
   real qe[2][5];
   God ga[2][2], gb[2][2];
-  e = local_idx(e);
+  if (WB) e = local_idx(e);
   for (int s = 0; s < 2; ++s) {
     const long long sh = s == 0 ? -sdd : 0;  // cell shift in the bases, offset e
     const int side = s == 0 ? 1 : 0;
-    for (int v = 0; v < 5; ++v) qe[s][v] = ldw(W + ((d * 2 + side) * 5 + v) * b.E + sh, e);
+    for (int v = 0; v < 5; ++v) {
+      const real* Wv = W + ((d * 2 + side) * 5 + v) * b.E + sh;
+      qe[s][v] = WB ? ldw(Wv, e) : ldu(Wv, e);
+    }
     if (CARRY == 2 && s == 0) continue;
-    ga[s][0] = ld_god(G1a + sh, b.E, e);
-    ga[s][1] = ld_god(G1a + sh + s1, b.E, e);
-    gb[s][0] = ld_god(G1b + sh, b.E, e);
-    gb[s][1] = ld_god(G1b + sh + s2, b.E, e);
+    ga[s][0] = ld(G1a + sh, b.E, e);
+    ga[s][1] = ld(G1a + sh + s1, b.E, e);
+    gb[s][0] = ld(G1b + sh, b.E, e);
+    gb[s][1] = ld(G1b + sh + s2, b.E, e);
   }
   double qs[2][5];
   for (int s = 0; s < 2; ++s) {
@@ -1967,7 +1976,7 @@ __device__ __forceinline__ void riem2_dir(const StepArgs& A, const BoxDev& box, 
   const bool active = idx < b.E && c[d] >= 1 && c[t1] >= 1 && c[t1] <= b.n[t1] && c[t2] >= 1 &&
                       c[t2] <= b.n[t2];
   double ql[5], qr[5];
-  if (active) final_states<D>(A, b, step_consts(A, b), e, ql, qr, &T.reverts);
+  if (active) final_states<D, 0, LEARNED>(A, b, step_consts(A, b), e, ql, qr, &T.reverts);
   RiemannOut g = solve<LEARNED, MODE == 2>(A, active, ql, qr, lds, &T.used, &T.fb);
   if (active) {
     T.calls = 1;
