@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_loss_grad(const float* __r
   for (int i = tid; i < kMlpNParam; i += kGradThreads) {
     int k = i + rot;
     k = k < kMlpNParam ? k : k - kMlpNParam;
-    unsafeAtomicAdd(grad + k, G[k]);
+    atomicAdd(grad + k, G[k]);
   }
   for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, 64);
   if (l == 0) S.loss[w] = lsum;
