@@ -111,57 +111,6 @@ __global__ __launch_bounds__(NT) void k_cic(const double* __restrict__ pos,
       u[d] = on ? (long long)fl : 0;
     }
   }
-  if (threadIdx.x == 0) first = NT;
-  if (threadIdx.x < 3) {
-    lo_sh[threadIdx.x] = 1 << 30;
-    hi_sh[threadIdx.x] = -(1 << 30);
-  }
-  __syncthreads();
-  // the box of cells, relative to the first particle's
-  if (on) atomicMin(&first, (int)threadIdx.x);
-  __syncthreads();
-  if (first == NT) return;  // no particle left (uniform)
-  if ((int)threadIdx.x == first)
-    for (int d = 0; d < 3; ++d) ref[d] = u[d];
-  __syncthreads();
-  int r[3];
-  for (int d = 0; d < 3; ++d) {
-    const long long v = u[d] - ref[d];
-    r[d] = v > (1 << 24) ? 1 << 24 : (v < -(1 << 24) ? -(1 << 24) : (int)v);
-    int a = on ? r[d] : 1 << 30, b = on ? r[d] : -(1 << 30);
-    for (int o = 32; o > 0; o >>= 1) {
-      a = min(a, __shfl_xor(a, o, 64));
-      b = max(b, __shfl_xor(b, o, 64));
-    }
-    if ((threadIdx.x & 63) == 0) {
-      atomicMin(&lo_sh[d], a);
-      atomicMax(&hi_sh[d], b);
-    }
-  }
-  __syncthreads();
-  int lo[3];
-  long long ext[3];
-  for (int d = 0; d < 3; ++d) {
-    lo[d] = lo_sh[d];
-    ext[d] = (long long)hi_sh[d] - lo[d] + 2;  // the upper cells included
-  }
-  // an axis the box spans whole is indexed by the wrapped cell itself
-  bool whole[3];
-  for (int d = 0; d < 3; ++d) {
-    whole[d] = ext[d] >= (long long)n[d];
-    if (whole[d]) ext[d] = n[d];
-  }
-  const bool fits = ext[0] * ext[1] <= CELLS && ext[0] * ext[1] * ext[2] <= CELLS;
-  unsigned c0[3], c1[3];  // lower and upper cell: in the box, or wrapped in the domain
-  for (int d = 0; d < 3; ++d) {
-    if (fits && !whole[d]) {
-      c0[d] = (unsigned)(r[d] - lo[d]);
-      c1[d] = c0[d] + 1;
-    } else {
-      c0[d] = wrap_mod(u[d], n[d]);
-      c1[d] = c0[d] + 1 == n[d] ? 0 : c0[d] + 1;
-    }
-  }
   auto weight = [&](int q) {
     double w = 1.0;
     w = w * (q & 1 ? f[0] : 1.0 - f[0]);
@@ -169,12 +118,91 @@ __global__ __launch_bounds__(NT) void k_cic(const double* __restrict__ pos,
     w = w * (q & 4 ? f[2] : 1.0 - f[2]);
     return m * w;
   };
-  if (!fits) {
-    if (on)
-      for (int q = 0; q < 8; ++q)
-        unsafeAtomicAdd(rho + nat(g, q & 1 ? c1[0] : c0[0], q & 2 ? c1[1] : c0[1], q & 4 ? c1[2] : c0[2]),
-                        weight(q));
+  // extents of the box between the lower cells lo and hi, the upper cells
+  // included; an axis it spans whole is indexed by the wrapped cell itself
+  auto extents = [&](const int* lo, const int* hi, long long* ext, bool* whole) {
+    for (int d = 0; d < 3; ++d) {
+      ext[d] = (long long)hi[d] - lo[d] + 2;
+      whole[d] = ext[d] >= (long long)n[d];
+      if (whole[d]) ext[d] = n[d];
+    }
+    return ext[0] * ext[1] <= CELLS && ext[0] * ext[1] * ext[2] <= CELLS;
+  };
+  auto add_direct = [&]() {
+    unsigned a[3], b[3];  // lower and upper cell in the domain
+    for (int d = 0; d < 3; ++d) {
+      a[d] = wrap_mod(u[d], n[d]);
+      b[d] = a[d] + 1 == n[d] ? 0 : a[d] + 1;
+    }
+    for (int q = 0; q < 8; ++q)
+      unsafeAtomicAdd(rho + nat(g, q & 1 ? b[0] : a[0], q & 2 ? b[1] : a[1], q & 4 ? b[2] : a[2]),
+                      weight(q));
+  };
+  auto clamped = [](long long v) {
+    return v > (1 << 24) ? 1 << 24 : (v < -(1 << 24) ? -(1 << 24) : (int)v);
+  };
+  if (threadIdx.x == 0) first = NT;
+  if (threadIdx.x < 3) {
+    lo_sh[threadIdx.x] = 1 << 30;
+    hi_sh[threadIdx.x] = -(1 << 30);
+  }
+  // the box of a wavefront's cells, relative to its first particle's
+  const unsigned long long lanes = __ballot(on);
+  long long wref[3];
+  int wlo[3], whi[3];
+  long long ext[3];
+  bool whole[3];
+  for (int d = 0; d < 3; ++d) {
+    wref[d] = __shfl(u[d], lanes ? __ffsll((long long)lanes) - 1 : 0, 64);
+    const int r = clamped(u[d] - wref[d]);
+    int a = on ? r : 1 << 24, b = on ? r : -(1 << 24);
+    for (int o = 32; o > 0; o >>= 1) {
+      a = min(a, __shfl_xor(a, o, 64));
+      b = max(b, __shfl_xor(b, o, 64));
+    }
+    wlo[d] = a;
+    whi[d] = b;
+  }
+  // particles that lie apart already in a wavefront go to memory without
+  // waiting for the rest of the workgroup
+  bool apart = lanes != 0 && !extents(wlo, whi, ext, whole);
+  if (apart) {
+    if (on) add_direct();
+    on = false;
+  }
+  __syncthreads();
+  // the workgroup's box, relative to its first particle's
+  const bool lead = lanes != 0 && !apart && (threadIdx.x & 63) == 0;
+  if (lead) atomicMin(&first, (int)threadIdx.x);
+  __syncthreads();
+  if (first == NT) return;  // no particle left (uniform)
+  if ((int)threadIdx.x == first)
+    for (int d = 0; d < 3; ++d) ref[d] = wref[d];
+  __syncthreads();
+  if (lead)
+    for (int d = 0; d < 3; ++d) {
+      atomicMin(&lo_sh[d], clamped(wref[d] - ref[d] + wlo[d]));
+      atomicMax(&hi_sh[d], clamped(wref[d] - ref[d] + whi[d]));
+    }
+  __syncthreads();
+  int lo[3], hi[3];
+  for (int d = 0; d < 3; ++d) {
+    lo[d] = lo_sh[d];
+    hi[d] = hi_sh[d];
+  }
+  if (!extents(lo, hi, ext, whole)) {
+    if (on) add_direct();
     return;
+  }
+  unsigned c0[3], c1[3];  // lower and upper cell in the box
+  for (int d = 0; d < 3; ++d) {
+    if (!whole[d]) {
+      c0[d] = (unsigned)(clamped(u[d] - ref[d]) - lo[d]);
+      c1[d] = c0[d] + 1;
+    } else {
+      c0[d] = wrap_mod(u[d], n[d]);
+      c1[d] = c0[d] + 1 == n[d] ? 0 : c0[d] + 1;
+    }
   }
   const int e0 = (int)ext[0], e01 = e0 * (int)ext[1], vol = e01 * (int)ext[2];
   for (int i = threadIdx.x; i < vol; i += NT) acc[i] = 0.0;
