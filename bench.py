@@ -132,7 +132,7 @@ def step_bytes(shapes, grav_bytes):
 
 
 def roofline_of(stage_ms, table, shapes, iters, step_ms, grav_bytes, form, workload,
-                tune=None, persistent_ms=None, fused=False):
+                tune=None, persistent_ms=None, fused=False, edges=False):
     """The dominant kernel's figures: algorithmic TFLOP/s against the vector
     ALU peak (the dominant stage kernel, the fused final-stage kernel, or the
     persistent step kernel, which runs every stage), and the whole step's
@@ -141,14 +141,15 @@ def roofline_of(stage_ms, table, shapes, iters, step_ms, grav_bytes, form, workl
         dom, ms = "step_persistent", persistent_ms
         fl = sum(stage_flops(table, st, shapes, iters) for st in STAGES)
     else:
-        dom = max(kernel_stages(fused), key=lambda s: kernel_ms(stage_ms, s))
-        ms = kernel_ms(stage_ms, dom)
-        fl = kernel_flops(table, dom, shapes, iters)
+        dom = max(kernel_stages(fused, edges), key=lambda s: kernel_ms(stage_ms, s, edges))
+        ms = kernel_ms(stage_ms, dom, edges)
+        fl = kernel_flops(table, dom, shapes, iters, edges)
     ach = fl / (ms * 1e-3) / 1e12
     t = None
     if tune is not None and persistent_ms is None and dom in STAGES:
         t = measured_traffic(dom, form, tune[STAGES.index(dom)], workload)
-    roof = {"bound": "alu" if dom in RIEMANN + ("trace", "step_persistent", "front", "final")
+    roof = {"bound": "alu" if dom in RIEMANN + ("trace", "edges", "step_persistent", "front",
+                                                "final")
             else "hbm",
             "kernel": dom, "ms_per_launch": round(ms, 4),
             "flops_per_launch": fl, "achieved": round(ach, 3), "peak": ALU_PEAK_TFLOPS,
@@ -165,34 +166,49 @@ def roofline_of(stage_ms, table, shapes, iters, step_ms, grav_bytes, form, workl
     return roof, hbm
 
 
-# the fused launch mode's kernels: "front" = trace + riem0 (where flat and trace
-# run as one launch, k_edges, flat's own time is 0), "final" = riem2 + update
-# (k_final)
+# the entries of the fused launch mode: "front" = trace + riem0, "final" = riem2 +
+# update (k_final)
 FUSED_STAGES = ("prim", "flat", "front", "riem1", "final")
 FUSED_PARTS = {"front": ("trace", "riem0"), "final": ("riem2", "update")}
+# where flattening and tracing run as one launch (k_edges), they are one entry,
+# "edges", or belong to "front" together
+EDGE_PARTS = {"edges": ("flat", "trace"), "front": ("flat", "trace", "riem0")}
 
 
-def kernel_stages(fused):
-    return FUSED_STAGES if fused else STAGES
+def kernel_stages(fused, edges=False):
+    if not edges:
+        return FUSED_STAGES if fused else STAGES
+    return tuple(s for s in (FUSED_STAGES if fused else
+                             ("prim", "edges") + tuple(STAGES[3:])) if s != "flat")
 
 
-def kernel_ms(stage_ms, stage):
+def kernel_parts(stage, edges=False):
+    return (EDGE_PARTS if edges and stage in EDGE_PARTS else FUSED_PARTS).get(stage, (stage,))
+
+
+def kernel_ms(stage_ms, stage, edges=False):
     """ms of a stage kernel; a fused kernel's time is what the library's
-    events report for its first stage (the second stage's interval is
+    events report for one of its stages (the other stage's interval is
     empty), so the sum of both is the fused launch's."""
-    return sum(stage_ms[s] for s in FUSED_PARTS.get(stage, (stage,)))
+    return sum(stage_ms[s] for s in kernel_parts(stage, edges))
 
 
-def kernel_flops(table, stage, shapes, iters):
-    return sum(stage_flops(table, s, shapes, iters) for s in FUSED_PARTS.get(stage, (stage,)))
+def kernel_flops(table, stage, shapes, iters, edges=False):
+    return sum(stage_flops(table, s, shapes, iters) for s in kernel_parts(stage, edges))
 
 
-def stage_rates(stage_ms, table, shapes, iters, fused=False):
+def edge_pass(plan):
+    """Whether every group of the plan runs flattening and tracing as one
+    launch (with some groups only, the stages stay booked separately)."""
+    return plan.num_groups > 0 and plan.edge_groups == plan.num_groups
+
+
+def stage_rates(stage_ms, table, shapes, iters, fused=False, edges=False):
     """Per-kernel ms, algorithmic TFLOP/s (oracle op counts)."""
     out = {}
-    for s in kernel_stages(fused):
-        ms = kernel_ms(stage_ms, s)
-        fl = kernel_flops(table, s, shapes, iters)
+    for s in kernel_stages(fused, edges):
+        ms = kernel_ms(stage_ms, s, edges)
+        fl = kernel_flops(table, s, shapes, iters, edges)
         out[s] = {"ms": round(ms, 4), "tflops": round(fl / max(ms, 1e-9) / 1e9, 3)}
     return out
 KERNEL_SOURCES = ("paper_1301_4498_amd/csrc/nyx_step.hip", "paper_1301_4498_amd/csrc/nyx_internal.h",
@@ -366,6 +382,7 @@ def run_box(nyx, torch, w, prm, steps, warmup, table):
     stage_ms = {s: v / max(seq, 1) for s, v in stage_ms.items()}
     rho = bufs[k % 2].reshape(6, n + 8, n + 8, n + 8)[0, 4:-4, 4:-4, 4:-4].cpu().numpy()
     finite = bool(torch.isfinite(bufs[k % 2]).all().item())
+    edges = edge_pass(plan)
     plan.close()
     del ws, U, Uo, G, bufs
     torch.cuda.empty_cache()
@@ -373,10 +390,10 @@ def run_box(nyx, torch, w, prm, steps, warmup, table):
     roof, hbm = roofline_of(stage_ms, table, [w.n], it, ms / steps, 4 if mixed else 8,
                             "fp64" if not mixed else "mixed", "box256_smooth", tune,
                             persistent_ms=ms / steps if persistent else None,  # the whole step
-                            fused=fused)
+                            fused=fused, edges=edges)
     return {"zone_updates_per_s": n ** 3 * steps / (ms * 1e-3), "ms_per_step": ms / steps,
             "launch_mode": MODE_NAMES[mode], "mode_step_ms": dict(zip(MODE_NAMES, mode_ms)),
-            "stage": None if persistent else stage_rates(stage_ms, table, [w.n], it, fused),
+            "stage": None if persistent else stage_rates(stage_ms, table, [w.n], it, fused, edges),
             "mean_riemann_iters": it,
             "stats_first_step": stats, "finite": finite, "rho": rho, "tuning": tune,
             "tuning_ms": tune_ms, "roofline": roof, "hbm_step": hbm}
@@ -550,12 +567,13 @@ def headline_leg(nyx, torch, synth, learn, steps, warmup, log, n=512, m=64, lear
         roof, hbm = roofline_of(stage_ms, table, shapes, it, ms, 4, "mixed",
                                 "box512_stress_patches", tune,
                                 persistent_ms=stage_ms["step_call"] if persistent else None,
-                                fused=fused)
+                                fused=fused, edges=edge_pass(plan))
         r = {"zone_updates_per_s": zones / (ms * 1e-3), "ms_per_step": ms,
              "rho_l1_vs_fp64": l1, "finite": bool(torch.isfinite(fin).all().item()),
              "launch_mode": MODE_NAMES[mode],
              "mode_step_ms": dict(zip(MODE_NAMES, mode_ms)),
-             "stage": None if persistent else stage_rates(stage_ms, table, shapes, it, fused),
+             "stage": None if persistent else stage_rates(stage_ms, table, shapes, it, fused,
+                                                          edge_pass(plan)),
              "step_call_ms": stage_ms["step_call"], "mean_riemann_iters": it,
              "stats": st, "tuning": tune, "roofline": roof, "hbm_step": hbm}
         if name.startswith("learned"):
@@ -689,12 +707,13 @@ def level_leg(nyx, torch, synth, learn, flux, steps, warmup, log):
         roof, hbm = roofline_of(stage_ms, table, shapes, it, ms, 8 if form == "fp64" else 4,
                                 form, "level4096", tune,
                                 persistent_ms=stage_ms["step_call"] if persistent else None,
-                                fused=fused)
+                                fused=fused, edges=edge_pass(plan))
         r = {"batched_zone_updates_per_s": V / (ms * 1e-3), "batched_ms_per_step": ms,
              "groups": plan.num_groups, "tuning": tune, "finite": finite,
              "launch_mode": MODE_NAMES[plan.launch_mode],
              "mode_step_ms": dict(zip(MODE_NAMES, mode_ms)) if mode_ms else None,
-             "stage": None if persistent else stage_rates(stage_ms, table, shapes, it, fused),
+             "stage": None if persistent else stage_rates(stage_ms, table, shapes, it, fused,
+                                                          edge_pass(plan)),
              "mean_riemann_iters": it, "roofline": roof, "hbm_step": hbm}
         if form != "fp64":
             r["rho_l1_vs_fp64"] = float(num / den)

@@ -200,6 +200,10 @@ int nyx_batch_create(const nyx_params* p, int nbox, const nyx_box* boxes,
                      void* workspace, size_t ws_bytes, void* stream, nyx_batch** out);
 int nyx_batch_destroy(nyx_batch* plan);
 int nyx_batch_num_groups(const nyx_batch* plan);
+/* Groups whose steps, in the plan's launch mode, run flattening and tracing as
+ * one launch (large FP32-mixed groups in the staged and fused modes; stage 2's
+ * interval of nyx_profile_* is then empty and stage 3's holds both). */
+int nyx_batch_edge_groups(const nyx_batch* plan);
 
 /* Per-box CFL time steps into dt (device, nbox doubles). */
 int nyx_batch_estimate_dt(nyx_batch* plan, const double* state, double a, double cfl,

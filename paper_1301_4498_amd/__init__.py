@@ -152,6 +152,11 @@ class Batch:
     def num_groups(self) -> int:
         return lib().nyx_batch_num_groups(self.handle)
 
+    @property
+    def edge_groups(self) -> int:
+        """Groups that run flattening and tracing as one launch."""
+        return lib().nyx_batch_edge_groups(self.handle)
+
     def estimate_dt(self, state, a, cfl, dt, stream=None):
         check("nyx_batch_estimate_dt", lib().nyx_batch_estimate_dt(
             self.handle, _ptr(state), a, cfl, _ptr(dt), _stream(stream)))

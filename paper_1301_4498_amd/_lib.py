@@ -97,6 +97,7 @@ def lib():
             "nyx_batch_create": (i, [P, i, B, vp, sz, vp, ctypes.POINTER(vp)]),
             "nyx_batch_destroy": (i, [vp]),
             "nyx_batch_num_groups": (i, [vp]),
+            "nyx_batch_edge_groups": (i, [vp]),
             "nyx_batch_estimate_dt": (i, [vp, vp, d, d, vp, vp]),
             "nyx_batch_min_dt": (i, [vp, vp, vp]),
             "nyx_hydro_step_batched": (i, [vp, vp, vp, vp, d, d, vp, vp, vp, vp]),
@@ -164,7 +165,7 @@ def check(fn: str, rc: int) -> None:
 def exported_symbols():
     return ["nyx_default_params", "nyx_status_string", "nyx_workspace_bytes", "nyx_estimate_dt",
             "nyx_hydro_step", "nyx_batch_workspace_bytes", "nyx_batch_create",
-            "nyx_batch_destroy", "nyx_batch_num_groups", "nyx_batch_estimate_dt",
+            "nyx_batch_destroy", "nyx_batch_num_groups", "nyx_batch_edge_groups", "nyx_batch_estimate_dt",
             "nyx_batch_min_dt", "nyx_hydro_step_batched", "nyx_fill_ghosts_periodic",
             "nyx_batch_fill_ghosts", "nyx_batch_set_ghost_source", "nyx_profile_enable",
             "nyx_profile_read",

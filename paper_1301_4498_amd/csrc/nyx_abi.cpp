@@ -555,6 +555,12 @@ int nyx_batch_destroy(nyx_batch* plan) {
 
 int nyx_batch_num_groups(const nyx_batch* plan) { return plan ? (int)plan->groups.size() : 0; }
 
+int nyx_batch_edge_groups(const nyx_batch* plan) {
+  if (!plan || (plan->mode == NYX_LAUNCH_PERSISTENT && !plan->harvest)) return 0;
+  return (int)std::count_if(plan->groups.begin(), plan->groups.end(),
+                            [](const nyx_batch::Group& g) { return g.edges; });
+}
+
 }  // extern "C"
 
 namespace {

@@ -86,3 +86,29 @@ def test_fused_stage_accounting():
     roof, _ = bench.roofline_of(stage_ms, table, shapes, 3.4, 20.0, 4, "mixed",
                                 "box512_stress_patches", fused=True)
     assert roof["kernel"] == "front" and roof["bound"] == "alu" and roof["traffic"] is None
+
+
+def test_edge_pass_accounting():
+    # where flattening and tracing run as one launch the events leave flat's
+    # interval empty: the benchmark books both stages' time and flops as one
+    # entry, so that no entry shows a rate of work it did not do
+    import bench
+    table = bench.flop_table("box512_stress")
+    shapes = [(64, 64, 64)] * 2
+    stage_ms = {"prim": 1.0, "flat": 0.005, "trace": 2.0, "riem0": 3.0, "riem1": 1.5,
+                "riem2": 4.5, "update": 0.001}
+    assert bench.kernel_stages(True, True) == ("prim", "front", "riem1", "final")
+    assert bench.kernel_stages(False, True) == ("prim", "edges", "riem0", "riem1", "riem2", "update")
+    for fused in (False, True):
+        rates = bench.stage_rates(stage_ms, table, shapes, 3.4, fused=fused, edges=True)
+        assert "flat" not in rates
+        ms = sum(v["ms"] for v in rates.values())
+        fl = sum(bench.kernel_flops(table, s, shapes, 3.4, True) for s in rates)
+        assert abs(ms - sum(stage_ms.values())) < 1e-9
+        assert fl == sum(bench.stage_flops(table, s, shapes, 3.4) for s in bench.STAGES)
+    two = sum(bench.stage_flops(table, s, shapes, 3.4) for s in ("flat", "trace"))
+    assert bench.kernel_flops(table, "edges", shapes, 3.4, True) == two
+    stage_ms["trace"] = 9.0
+    roof, _ = bench.roofline_of(stage_ms, table, shapes, 3.4, 20.0, 4, "mixed",
+                                "box512_stress_patches", edges=True)
+    assert roof["kernel"] == "edges" and roof["bound"] == "alu" and roof["flops_per_launch"] == two
