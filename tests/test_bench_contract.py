@@ -112,3 +112,19 @@ def test_edge_pass_accounting():
     roof, _ = bench.roofline_of(stage_ms, table, shapes, 3.4, 20.0, 4, "mixed",
                                 "box512_stress_patches", edges=True)
     assert roof["kernel"] == "edges" and roof["bound"] == "alu" and roof["flops_per_launch"] == two
+
+
+def test_headline_form_and_the_reason_others_are_dropped():
+    import bench
+    F = {"fp64_one_box": {"zone_updates_per_s": 1.0, "finite": True},
+         "mixed_patches": {"zone_updates_per_s": 3.0, "finite": True, "rho_l1_vs_fp64": 1e-8},
+         "mixed_patches_fp64_stop": {"zone_updates_per_s": 9.0, "finite": True, "rho_l1_vs_fp64": 1e-8},
+         "learned_patches": {"zone_updates_per_s": 2.0, "finite": True, "rho_l1_vs_fp64": 1e-7}}
+    assert bench.choose_form(F) == ("mixed_patches", {})
+    F["mixed_patches"]["finite"] = False
+    chosen, dropped = bench.choose_form(F)
+    assert chosen == "learned_patches" and "non-finite" in dropped["mixed_patches"]
+    F["learned_patches"]["rho_l1_vs_fp64"] = float("nan")
+    chosen, dropped = bench.choose_form(F)
+    assert chosen == "fp64_one_box" and set(dropped) == {"mixed_patches", "learned_patches"}
+    assert "density" in dropped["learned_patches"]
