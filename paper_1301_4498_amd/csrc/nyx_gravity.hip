@@ -486,7 +486,7 @@ __device__ __forceinline__ void lds_smooth(double* phi, const double* f, const G
 // (128^3 takes 28 us in place, and its tiles alone would load 268 MB).
 constexpr int kTileThreads = 512;
 constexpr int kTB = 16, kTBHalf = 8, kTileOwn = 8, kTileHalo = 4;
-constexpr size_t kTileCells = 1 << 18;
+constexpr size_t kTileCells = 1 << 18, kTileBlocks = 768;
 __global__ __launch_bounds__(kTileThreads) void k_smooth_tile(const double* __restrict__ src,
                                                               double* __restrict__ dst,
                                                               const double* __restrict__ f, Grid g,
@@ -571,10 +571,6 @@ constexpr int kMarchOwnX = 32, kMarchOwnY = 16;
 constexpr int kMarchThreads = kMarchX * kMarchY;
 // one workgroup per CU, whose chunk is at least kMarchPlanes planes
 constexpr unsigned kMarchBlocks = 256, kMarchPlanes = 8;
-// Levels of at least this many cells are swept so: a V-cycle of 80^3 106 us in
-// place and 111 marching, of 96^3 125 and 120, 128^3 171 and 152, 192^3 309 and
-// 253, 256^3 673 and 546, 320^3 1410 and 1010.
-constexpr size_t kMarchCells = 3 << 18;
 __global__ __launch_bounds__(kMarchThreads) void k_smooth_march(
     const double* __restrict__ bsrc, const double* __restrict__ f, double* __restrict__ red,
     double* __restrict__ bdst, Grid g, unsigned tx, unsigned ty, unsigned chunk, double h2) {
@@ -834,6 +830,42 @@ static hipError_t smooth(const Level& v, int iters, hipStream_t s) {
       hipLaunchKernelGGL(k_rbgs, dim3(nb), dim3(kBlock), 0, s, v.phi, v.f, v.g, v.h2, color);
   return hipGetLastError();
 }
+// Tiled sweeps: levels of at most kTileCells cells, unless they are so thin that
+// most of a block is halo (4 x 4 x 8192: 1024 blocks, a V-cycle 225 us against
+// 194 in place).
+static bool tiled(const Grid& g) {
+  const size_t b = (size_t)((g.nx + kTileOwn - 1) / kTileOwn) * ((g.ny + kTileOwn - 1) / kTileOwn) *
+                   ((g.nz + kTileOwn - 1) / kTileOwn);
+  return cells(g) <= kTileCells && b <= kTileBlocks;
+}
+// The marching sweep's tiles, and chunks of equal length, as many as give the
+// chip a workgroup per CU.
+struct March {
+  unsigned tx, ty, chunk, blocks;
+};
+static March march_of(const Grid& g) {
+  March m;
+  m.tx = (g.nx / 2 + kMarchOwnX - 1) / kMarchOwnX;
+  m.ty = (g.ny + kMarchOwnY - 1) / kMarchOwnY;
+  const unsigned want = std::max(1u, kMarchBlocks / std::max(1u, m.tx * m.ty));
+  const unsigned nz = std::min(want, std::max(1u, g.nz / kMarchPlanes));
+  m.chunk = (g.nz + nz - 1) / nz;
+  m.blocks = m.tx * m.ty * ((g.nz + m.chunk - 1) / m.chunk);
+  return m;
+}
+// Marching sweeps where their steps of 1.2 us, chunk + 11 for each round of
+// workgroups, take less time than two sweeps in place, 15.4 us and 10 us per
+// million cells.  V-cycles in place and marching (us): 80^3 106 and 111, 96^3
+// 125 and 120, 128^3 171 and 152, 192^3 309 and 253, 256^3 673 and 546, 320^3
+// 1410 and 1010; of thin domains, whose tiles are mostly halo, 8 x 16 x 8192 234
+// and 251.
+static bool marching(const Grid& g) {
+  if (tiled(g)) return false;
+  const March m = march_of(g);
+  const size_t rounds = (m.blocks + kMarchBlocks - 1) / kMarchBlocks;
+  return 1.2 * (double)(rounds * (m.chunk + 11)) < 15.4 + 1e-5 * (double)cells(g);
+}
+
 // two sweeps from src to dst
 static hipError_t smooth_tile(const Level& v, const double* src, double* dst, hipStream_t s) {
   const unsigned tx = (v.g.nx + kTileOwn - 1) / kTileOwn, ty = (v.g.ny + kTileOwn - 1) / kTileOwn,
@@ -845,16 +877,10 @@ static hipError_t smooth_tile(const Level& v, const double* src, double* dst, hi
 
 // two sweeps in one pass, black cells from one array to another
 static hipError_t smooth_march(const Level& v, const double* src, double* dst, hipStream_t s) {
-  const unsigned half = v.g.nx / 2, hn = half * v.g.ny * v.g.nz;
-  const unsigned tx = (half + kMarchOwnX - 1) / kMarchOwnX,
-                 ty = (v.g.ny + kMarchOwnY - 1) / kMarchOwnY;
-  // chunks of equal length, as many as give the chip a workgroup per CU
-  const unsigned want = std::max(1u, kMarchBlocks / std::max(1u, tx * ty));
-  const unsigned nz = std::min(want, std::max(1u, v.g.nz / kMarchPlanes));
-  const unsigned chunk = (v.g.nz + nz - 1) / nz;
-  hipLaunchKernelGGL(k_smooth_march, dim3(tx * ty * ((v.g.nz + chunk - 1) / chunk)),
-                     dim3(kMarchThreads), 0, s, src + hn, v.f, v.phi, dst + hn, v.g, tx, ty, chunk,
-                     v.h2);
+  const unsigned hn = v.g.nx / 2 * v.g.ny * v.g.nz;
+  const March m = march_of(v.g);
+  hipLaunchKernelGGL(k_smooth_march, dim3(m.blocks), dim3(kMarchThreads), 0, s, src + hn, v.f, v.phi,
+                     dst + hn, v.g, m.tx, m.ty, m.chunk, v.h2);
   return hipGetLastError();
 }
 
@@ -876,20 +902,19 @@ static hipError_t vcycle(std::vector<Level>& L, size_t l, hipStream_t s) {
   static_assert(kPre == 2 && kPost == 2, "the tiled smoother does two sweeps");
   const Level& f = L[l];
   Level& c = L[l + 1];
-  const bool tiled = cells(f.g) <= kTileCells;
-  double* u = tiled ? f.alt : f.phi;  // phi during the coarse correction
-  const bool march = cells(f.g) >= kMarchCells;
-  double* ub = march ? f.alt : u;        // its black cells
-  hipError_t e = tiled ? smooth_tile(f, f.phi, u, s)
-                       : (march ? smooth_march(f, f.phi, ub, s) : smooth(f, kPre, s));
+  const bool tile = tiled(f.g), march = marching(f.g);
+  double* u = tile ? f.alt : f.phi;  // phi during the coarse correction
+  double* ub = march ? f.alt : u;       // its black cells
+  hipError_t e = tile ? smooth_tile(f, f.phi, u, s)
+                      : (march ? smooth_march(f, f.phi, ub, s) : smooth(f, kPre, s));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_restrict, dim3(blocks_for(cells(c.g))), dim3(kBlock), 0, s, u, ub, f.f, f.g,
                      f.inv_h2, c.g, c.f, c.phi);
   if ((e = vcycle(L, l + 1, s)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_prolong, dim3(blocks_for(cells(c.g))), dim3(kBlock), 0, s, u, ub, f.g, c.phi,
                      c.g);
-  return tiled ? smooth_tile(f, u, f.phi, s)
-               : (march ? smooth_march(f, ub, f.phi, s) : smooth(f, kPost, s));
+  return tile ? smooth_tile(f, u, f.phi, s)
+              : (march ? smooth_march(f, ub, f.phi, s) : smooth(f, kPost, s));
 }
 
 // max |f - L phi| of a level into *out
@@ -986,7 +1011,7 @@ int nyx_poisson_solve(const int32_t* dom, double dx, double coef, const double* 
   // (the marching smoother uses only the second half of its level's, so the
   // finest level's black cells and the coarser levels do not meet).
   L[0].alt = phi;
-  double* spare = cells(L[0].g) <= kTileCells ? L[0].phi : phi;
+  double* spare = tiled(L[0].g) ? L[0].phi : phi;
   for (size_t l = 1; l < L.size(); ++l) {
     L[l].alt = spare;
     spare += cells(L[l].g);

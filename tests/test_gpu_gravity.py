@@ -175,6 +175,37 @@ def test_large_vcycles_equal_their_definition(nyx, dom):
     test_vcycles_equal_their_definition(nyx, dom)
 
 
+@pytest.mark.parametrize("dom", [(4, 4, 8192), (12, 20, 1088), (32, 32, 1024), (64, 512, 64)])
+def test_thin_vcycles_equal_their_definition(nyx, dom):
+    """The same for long domains on either side of the rules for tiles (at most
+    768 blocks) and for marching sweeps (an estimate of their steps): in place
+    although small, and marching with a halo that wraps around the domain."""
+    test_vcycles_equal_their_definition(nyx, dom)
+
+
+@pytest.mark.parametrize("order", ["lattice", "every_third_wave", "scattered"])
+def test_wide_cic_deposit_by_particle_order(nyx, order):
+    """2^18 particles and more, in workgroups of 1024: all of them close
+    together, single wavefronts of 64 that lie apart from the rest of their
+    workgroup, every wavefront apart; a partly filled last workgroup.  The bound
+    is that of the atomic sums: 1e-13 of each cell."""
+    rng = np.random.default_rng(6)
+    n, dx = 64, 1.0 / 64
+    npart = 2**18 + 100
+    i = np.arange(npart)
+    pos = np.stack([i % n + 0.5, i // n % n + 0.5, i // n**2 % n + 0.5]) * dx
+    pos += 0.3 * dx * rng.normal(size=pos.shape)
+    far = {"lattice": np.zeros(npart, bool), "every_third_wave": i // 64 % 3 == 1,
+           "scattered": np.ones(npart, bool)}[order]
+    pos[:, far] = rng.uniform(0, 1, (3, int(far.sum())))
+    mass = rng.uniform(0.5, 2.0, npart)
+    import torch
+    rho = torch.zeros((n, n, n), dtype=torch.float64, device="cuda")
+    nyx.cic_deposit(to_dev(pos), to_dev(mass), (n, n, n), dx, rho)
+    ref = oracle.cic_deposit(np.ascontiguousarray(pos), mass, (n, n, n), dx)
+    assert np.allclose(rho.cpu().numpy(), ref, rtol=1e-13, atol=0)
+
+
 def _resid_ok(r, f, phi, dx, tol):
     """max|r| within tol max|f| plus the rounding of evaluating the 7-point
     residual in another order (terms of size 6 max|phi| / dx^2)."""
