@@ -114,7 +114,7 @@ void fill_physics(StepArgs& a, const nyx_params* p) {
   a.small_densf = (float)p->small_dens;
   a.small_presf = (float)p->small_pres;
   const double g1 = p->gamma - 1.0;
-  a.plain = g1 > 0x1p-20 && g1 < 0x1p20 && p->small_pres >= 0x1p-100 && p->small_pres < 0x1p100 &&
+  a.plain = g1 > 0x1p-20 && g1 < 0x1p20 && p->small_pres >= 0x1p-200 && p->small_pres < 0x1p100 &&
             p->small_dens >= 0x1p-200;
   a.riemann_tol = p->riemann_tol;
   // FP32-mixed stopping step: the star state is stored in FP32, so the

@@ -148,7 +148,7 @@ inline long long edge_tiles(int nbox, const nyx_box* boxes, int planes) {
   }
   return n;
 }
-// Planes per chunk: the longest chunk that gives the launch kFinTiles tiles.
+// Planes per chunk: the longest chunk that gives the launch kEdgeWant tiles.
 inline int edge_planes(int nbox, const nyx_box* boxes) {
   int planes = kEdgePlanes;
   while (planes > kEdgeMinPlanes && edge_tiles(nbox, boxes, planes) < kEdgeWant) planes /= 2;
@@ -424,7 +424,7 @@ struct StepArgs {
   double igm1;   // 1 / (gamma - 1), for the mixed build's products
   float igm1f;   // the same in FP32 (the FP32 flux formulas)
   double mixed_stop;  // FP32-mixed stopping rule (see two_shock)
-  int plain;     // gamma and the pressure floor allow the FP64 solver's short divisions
+  int plain;     // gamma and the floors allow the FP64 build's short divisions
   int maxiter;
   nyx_stats* stats;
   unsigned long long* slots;  // kStatSlots x kStatFields partial counters (when stats)

@@ -88,8 +88,9 @@ __device__ __forceinline__ bool wide_range(double b) {
 // smaller operand, so that no other numerator of a step is small.
 //   kTraceExp: velocities of a stencil; their differences, flattened (by at
 //     least 2^-53) and squared, then exceed 2^-920;
-//   kFluxExp: the velocity of a face, whose pressure exceeds 2^-180.
-constexpr int kTraceExp = -300, kFluxExp = -700, kQuotExp = -900;
+//   kFluxExp: the velocity of a face, whose pressure exceeds 2^-280 (a
+//     corrected one's energy is a difference of numbers above 2^-200 / 2^20).
+constexpr int kTraceExp = -300, kFluxExp = -600, kQuotExp = -900;
 __device__ __forceinline__ bool general_div(const StepArgs& A, int e, int least) {
   return !A.plain || e < least;
 }
@@ -904,8 +905,8 @@ struct FullOps {
 };
 // densities and pressures of both states between 2^-100 and 2^100, normal
 // velocities 0 or likewise, the pressure floor, which a star pressure may take,
-// in that range too, and gamma - 1 between 2^-20 and 2^20 (both once per step,
-// on the host: StepArgs::plain): every product, quotient and square root of the
+// at least 2^-200, and gamma - 1 between 2^-20 and 2^20 (both once per step, on
+// the host: StepArgs::plain): every product, quotient and square root of the
 // two-shock relations then stays between 2^-700 and 2^700 (or is 0), far from
 // where a division or square root scales its operands
 __device__ __forceinline__ bool in_plain_range(const StepArgs& A, const double* qL,

@@ -200,7 +200,9 @@ def test_fp64_step_out_of_ordinary_range(nyx, lo, hi):
 
 
 @pytest.mark.parametrize("small_pres,dens,gamma", [(1e-315, 1e10, 5.0 / 3.0), (1e-300, 1e25, 5.0 / 3.0),
-                                                   (1e-300, 1.0, 5.0 / 3.0), (1e-20, 1.0, 1e100)])
+                                                   (1e-300, 1.0, 5.0 / 3.0), (1e-20, 1.0, 1e100),
+                                                   (2.0**-200, 1.0, 5.0 / 3.0), (2.0**-200, 1e25, 1.2),
+                                                   (2.0**-201, 1.0, 5.0 / 3.0)])
 def test_fp64_star_pressure_at_a_tiny_floor(nyx, small_pres, dens, gamma):
     """Streams that separate faster than their sound speed, whose star pressure
     is the floor: ordinary states with a floor so small that the star state's
