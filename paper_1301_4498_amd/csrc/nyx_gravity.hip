@@ -71,13 +71,17 @@ __device__ __forceinline__ double nb_sum(const double* p, const Grid& g, unsigne
 // its NT particles in LDS where they lie close together, as particles kept in
 // any spatial order do: the box of cells they touch, at most CELLS, is
 // accumulated with LDS atomics and added to memory row by row, full requests
-// and each cell once.  Particles that lie further apart go to memory directly.
+// and each cell once.  Particles that lie further apart go to memory directly, a
+// wavefront whose own 64 do so at once, before the workgroup's box is formed
+// (waiting for it, 2^18 scattered particles took 100 us).
 // Sizes: 1024 particles and 80 KB keep two workgroups (32 waves) on a CU, so
-// that the direct path loses nothing; below kCicWide particles, where these
+// that the direct path loses little; below kCicWide particles, where these
 // would leave CUs idle, 256 particles and 48 KB.
-// Measured (us): 256^3 particles near their lattice points 3409 -> 572, 64^3
-// 60 -> 19, 2^18 clustered 677 -> 18; scattered over the domain, where every
-// workgroup takes the direct path, 5953 -> 6234 for 2^24 on 512^3.
+// Measured (us, particles added one by one, and this): 256^3 particles near
+// their lattice points 3440 and 478, 64^3 53 and 13.5, 2^18 clustered 1070 and
+// 20; scattered over the domain, where every wavefront takes the direct path,
+// 2^18 on 128^3 93 and 94.5, 2^22 on 256^3 1432 and 1431, 2^24 on 512^3 5950 and
+// 6200; every second one of 256^3 scattered 5230 and 4890.
 constexpr int kCicBlock = 1024, kCicCells = 10000;
 constexpr int kCicSmallBlock = 256, kCicSmallCells = 6144;
 constexpr long long kCicWide = 1 << 18;
@@ -333,7 +337,9 @@ __global__ __launch_bounds__(kBlock) void k_sub_mean(const double* __restrict__ 
 // range-scaled division: y = RN(1/6) is within 2^-54 of 1/6, so x y rounded is
 // within one unit in the last place of x / 6, the remainder x - 6 q is exact,
 // and adding its quotient to q rounds to the correctly rounded x / 6
-// (Markstein's theorem).
+// (Markstein's theorem).  For finite x with a normal quotient, or 0: below
+// 2^-1019 the last bit may differ, and an infinite x gives NaN, which the next
+// sweep's differences of infinities give anyway.
 __device__ __forceinline__ double div6(double x) {
   constexpr double y = 1.0 / 6.0;
   const double q = x * y;
@@ -831,8 +837,8 @@ static hipError_t smooth(const Level& v, int iters, hipStream_t s) {
   return hipGetLastError();
 }
 // Tiled sweeps: levels of at most kTileCells cells, unless they are so thin that
-// most of a block is halo (4 x 4 x 8192: 1024 blocks, a V-cycle 225 us against
-// 194 in place).
+// most of a block is halo (a V-cycle, tiled and in place: 12 x 20 x 1088, 816
+// blocks, 176 and 156 us; 4 x 4 x 8192, 1024 blocks, 160 and 154).
 static bool tiled(const Grid& g) {
   const size_t b = (size_t)((g.nx + kTileOwn - 1) / kTileOwn) * ((g.ny + kTileOwn - 1) / kTileOwn) *
                    ((g.nz + kTileOwn - 1) / kTileOwn);
@@ -857,8 +863,8 @@ static March march_of(const Grid& g) {
 // workgroups, take less time than two sweeps in place, 15.4 us and 10 us per
 // million cells.  V-cycles in place and marching (us): 80^3 106 and 111, 96^3
 // 125 and 120, 128^3 171 and 152, 192^3 309 and 253, 256^3 673 and 546, 320^3
-// 1410 and 1010; of thin domains, whose tiles are mostly halo, 8 x 16 x 8192 234
-// and 251.
+// 1410 and 1010; of thin domains, whose tiles are mostly halo, 8 x 16 x 8192 219
+// and 245, 264 x 4 x 1024 217 and 227, 16 x 256 x 512 161 and 171.
 static bool marching(const Grid& g) {
   if (tiled(g)) return false;
   const March m = march_of(g);

@@ -255,10 +255,10 @@ def test_edge_pass_equals_separate_kernels(nyx, recon, mode):
 
 @pytest.mark.parametrize("stages", [3, 4, 7])
 def test_fused_with_learned_flux(nyx, stages):
-    """The learned flux on stages 0-1 (the x front stays staged, the fused
-    final stage runs the plain solver), on the final stage only (the x front
-    is fused, the final stage stays staged) and on all three (both staged):
-    the fused mode gives the staged launches' bits, counters included."""
+    """The learned flux on stages 0-1 (the fused final stage runs the plain
+    solver), on the final stage only and on all three (the final stage stays
+    staged): the fused mode gives the staged launches' bits, counters
+    included."""
     import torch
     from paper_1301_4498_amd import learn
     f = learn.LearnedFlux(seed=9)

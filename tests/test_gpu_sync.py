@@ -130,9 +130,8 @@ def test_fp64_sync_bitwise(nyx, reference, groups):
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
 def test_sync_in_the_fused_launch_mode(nyx, reference, prec):
-    # plans that feed flux registers keep the staged final stage but fuse the
-    # x tracing and stage-0 solves: the same bits as the staged launches, and
-    # (FP64) as the oracle
+    # plans that feed flux registers keep the staged final stage: the same bits
+    # as the staged launches, and (FP64) as the oracle
     p = nyx.NYX_FP64 if prec == "fp64" else nyx.NYX_MIXED
     prm = nyx.default_params(precision=p)
     print("two-level sync, fused mode,", prec, flush=True)
