@@ -36,12 +36,12 @@ constexpr long long kEdgeWant = 4096;
 // Whether an FP32 launch over `cells` cells, whose tiles have `slots` lanes in
 // all planes together, takes the pass.  It has to fill the chip several times
 // over, as each workgroup marches up its planes, and a third of its lanes have
-// to have a cell.  Step in us, separate kernels against the pass: 64^3 168 and
-// 189, 96^3 379 and 389, 112^3 522 and 509, 160^3 1377 and 1323, 256^3 5215 and
-// 4915; 3000 boxes of 8^3 (20% of the lanes) 1394 and 1450, 900 of 12^3 (38%)
-// 962 and 933, 256 of 16^3 536 and 510, 64 of 64^3 5610 and 5200.  In FP64 the
-// pass needs 228 registers, two wavefronts a SIMD, and loses: 256 boxes of 16^3
-// 1204 and 1240 us, 128^3 1631 and 1652.
+// to have a cell.  Step in us, separate kernels against the pass: 64^3 187 and
+// 212, 96^3 381 and 400, 104^3 443 and 451, 108^3 477 and 477, 112^3 510 and 503,
+// 160^3 1376 and 1330; 3000 boxes of 8^3 (20% of the lanes) 1394 and 1450, 900
+// of 12^3 (38%) 962 and 933, 256 of 16^3 536 and 510, 64 of 64^3 5610 and 5300.
+// In FP64 the pass needs 228 registers, two wavefronts a SIMD, and loses: 256
+// boxes of 16^3 1204 and 1240 us, 128^3 1631 and 1652.
 inline bool edges_pay(long long cells, long long slots) {
   return cells >= 5 * (1ll << 18) && 3 * cells >= slots;
 }

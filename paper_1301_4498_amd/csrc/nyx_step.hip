@@ -706,7 +706,9 @@ __global__ __launch_bounds__(kBlock) void k_trace(StepArgs A) { trace_body(A, la
 // issue 42%, memory 2.9 TB/s), not by what these move.  Here it is about 14
 // loads and the 30 stores of the edge states.  64 shocked 64^3 patches: 791 us
 // at 4.5 TB/s (vector issue 77%) against 171 us of flattening and the tracing
-// behind it, the whole step 5610 -> 5200 us; 256^3 5215 -> 4915.
+// behind it, the whole step 5610 -> 5200 us; 256^3 5215 -> 4915 (all with the
+// limits as medians; with their comparisons and the range test of the slopes
+// the pass takes 892 us on 256^3 for 873, the patches' step 5270).
 // 128 VGPRs (two workgroups a CU) need the slopes' general form in branches of
 // its own: both forms side by side took 144, one workgroup.
 // Neighbouring tiles in x are launched next to each other, so that the cache
